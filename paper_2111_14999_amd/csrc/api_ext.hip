@@ -56,7 +56,6 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
             cd* E2 = ar.take<cd>((size_t)nqp * nm * nm);
             cd* E3 = ar.take<cd>((size_t)nq * nqp * nm * nm);
             double* qpp = ar.take<double>((size_t)nq * nqp * 3);
-            cd* phi3c = ar.take<cd>((size_t)n1 * n2 * m3);
             cd* P1 = ar.take<cd>((size_t)qb * n1);
             cd* P2 = ar.take<cd>((size_t)nqp * n2);
             cd* S = ar.take<cd>((size_t)qb * n2 * m3);
@@ -75,7 +74,6 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
                 ar.used = std::max(std::max(a1.used, a2.used), a3.used);
             }
             if (!ar.base) return;
-            HIPCHK(h, launch_real_to_complex(sys->phi3, (int64_t)n1 * n2 * m3, phi3c, s));
             HIPCHK(h, launch_phase_table(qp_frac, nullptr, Mesh{1, 1, 1}, nqp, r2, n2, P2, n2, s));
             for (int64_t i0 = 0; i0 < nq; i0 += qb) {
                 const int64_t nb = std::min(qb, nq - i0);
@@ -83,8 +81,8 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
                                              n1, s));
                 // S[i, (R', sa, s'b, s''c)] = sum_R e^{-i 2 pi q.R} Phi3[R, ...]
                 Timer t1(h, s, "v3_stage1");
-                HIPCHK(h, launch_zgemm(P1, n1, phi3c, (int64_t)n2 * m3, S, (int64_t)n2 * m3, nb,
-                                       (int64_t)n2 * m3, n1, s));
+                HIPCHK(h, launch_zgemm_real_b(P1, n1, sys->phi3, (int64_t)n2 * m3, S,
+                                              (int64_t)n2 * m3, nb, (int64_t)n2 * m3, n1, s));
                 t1.done();
                 HIPCHK(h, launch_v3_fold(S, nb, n2, nm, E1 + i0 * nm * nm, T, s));
                 for (int64_t i = 0; i < nb; ++i) {

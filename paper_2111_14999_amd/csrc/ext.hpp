@@ -86,8 +86,6 @@ hipError_t launch_gather_rows32(const uint32_t* src, int64_t words, const int32_
 // *flag |= 1 if any of the n doubles is NaN or infinite.
 hipError_t launch_nonfinite(const double* x, int64_t n, int32_t* flag, hipStream_t s);
 
-// 3-phonon coupling helpers.
-hipError_t launch_real_to_complex(const double* x, int64_t n, cd* out, hipStream_t s);
 // out[p] = -(q[i] + qp[j]) for p = i nqp + j
 hipError_t launch_neg_pair_sum(const double* q, int64_t nq, const double* qp, int64_t nqp,
                                double* out, hipStream_t s);

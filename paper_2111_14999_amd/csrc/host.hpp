@@ -285,15 +285,15 @@ inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int
                 double kT, double* omega, cd* E, double* nb, cd* z_out, hipStream_t s) {
     const int nm = 3 * sys->n_atoms, nR = sys->n_rd;
     cd* P = ar.take<cd>((size_t)np * nR);
-    cd* phic = ar.take<cd>((size_t)nR * nm * nm);
+    double* phic = ar.take<double>((size_t)nR * nm * nm);
     cd* D = ar.take<cd>((size_t)np * nm * nm);
     double* lam = ar.take<double>((size_t)np * nm);
     cd* z = z_out ? z_out : ar.take<cd>((size_t)np * nm * nm);
     if (!ar.base) return;
     HIPCHK(h, launch_phase_table(frac, idx, m, np, rd_d, nR, P, nR, s));
     HIPCHK(h, launch_mass_weight(sys->phi_r, sys->mass, nR, nm, phic, s));
-    HIPCHK(h, launch_zgemm(P, nR, phic, (int64_t)nm * nm, D, (int64_t)nm * nm, np,
-                           (int64_t)nm * nm, nR, s));
+    HIPCHK(h, launch_zgemm_real_b(P, nR, phic, (int64_t)nm * nm, D, (int64_t)nm * nm, np,
+                                  (int64_t)nm * nm, nR, s));
     HIPCHK(h, launch_eig_herm(D, nm, np, lam, z, s));
     HIPCHK(h, launch_phonon_post(lam, z, sys->mass, sys->n_atoms, np, omega_min, kT, omega, E, nb,
                                  s));

@@ -17,8 +17,12 @@ hipError_t launch_phase_table(const double* frac, const int32_t* idx, Mesh m, in
 hipError_t launch_zgemm(const cd* A, int64_t lda, const cd* B, int64_t ldb, cd* C, int64_t ldc,
                         int64_t M, int64_t N, int K, hipStream_t s);
 
-// Real force constants -> complex mass-weighted Phi(R)/sqrt(M_s M_s').
-hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int nm, cd* out,
+// The same with a real B (half its bytes, two MFMAs per product).
+hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_t ldb, cd* C,
+                               int64_t ldc, int64_t M, int64_t N, int K, hipStream_t s);
+
+// Mass-weighted force constants Phi(R)/sqrt(M_s M_s').
+hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int nm, double* out,
                               hipStream_t s);
 
 // In-place batched Hermitian eigensolver (cyclic Jacobi, FP64).  A [batch, n, n]

@@ -635,18 +635,6 @@ hipError_t launch_nonfinite(const double* x, int64_t n, int32_t* flag, hipStream
 // ---------------------------------------------------------------------------
 // 3-phonon coupling (Phonon Properties; Kokkos section, generic contraction)
 // ---------------------------------------------------------------------------
-__global__ void real_to_complex_kernel(const double* x, int64_t n, cd* out) {
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
-         t += (int64_t)gridDim.x * blockDim.x)
-        out[t] = cd{x[t], 0.0};
-}
-
-hipError_t launch_real_to_complex(const double* x, int64_t n, cd* out, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(real_to_complex_kernel, dim3(grid_n(n, 256)), dim3(256), 0, s, x, n, out);
-    return hipGetLastError();
-}
-
 __global__ void neg_pair_sum_kernel(const double* q, int64_t nq, const double* qp, int64_t nqp,
                                     double* out) {
     const int64_t total = nq * nqp;

@@ -61,12 +61,39 @@ hipError_t launch_phase_table(const double* frac, const int32_t* idx, Mesh m, in
 // of 16 x 16.  MFMA operand layouts (16x16x4 f64): lane l holds A[l%16][l/16],
 // B[l/16][l%16]; result v (0..3) of lane l is D[l/16 + 4v][l%16].
 // Complex product with 4 real MFMAs: Cr += Ar Br - Ai Bi, Ci += Ar Bi + Ai Br.
+// BT = double: a real B (force constants), two MFMAs and half the B bytes.
+//
+// Rows and columns past the matrix read a clamped address (their results are not
+// stored) and k past K meets a zero A, so that no load sits under a lane branch.
 // ---------------------------------------------------------------------------
-template <int TM, int TN>
-__global__ __launch_bounds__(256, 2) void zgemm_kernel(const cd* __restrict__ A, int64_t lda,
-                                                    const cd* __restrict__ B, int64_t ldb,
-                                                    cd* __restrict__ C, int64_t ldc, int64_t M,
-                                                    int64_t N, int K) {
+template <class BT>
+struct ZgemmB;
+template <>
+struct ZgemmB<cd> {
+    static __device__ inline void step1(const cd& a, const cd& b, d4& cr, d4& ci) {
+        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, cr, 0, 0, 0);
+        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, ci, 0, 0, 0);
+    }
+    static __device__ inline void step2(const cd& a, const cd& b, d4& cr, d4& ci) {
+        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, cr, 0, 0, 0);
+        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, ci, 0, 0, 0);
+    }
+};
+template <>
+struct ZgemmB<double> {
+    static __device__ inline void step1(const cd& a, const double& b, d4& cr, d4& ci) {
+        cr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b, cr, 0, 0, 0);
+        ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b, ci, 0, 0, 0);
+    }
+    static __device__ inline void step2(const cd&, const double&, d4&, d4&) {}
+};
+
+template <int TM, int TN, int WPS, class BT>
+__global__ __launch_bounds__(256, WPS) void zgemm_kernel(const cd* __restrict__ A, int64_t lda,
+                                                      const BT* __restrict__ B, int64_t ldb,
+                                                      cd* __restrict__ C, int64_t ldc, int64_t M,
+                                                      int64_t N, int K) {
+    using Z = ZgemmB<BT>;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
     const int64_t m0 = (int64_t)blockIdx.y * (16 * TM);
@@ -80,44 +107,46 @@ __global__ __launch_bounds__(256, 2) void zgemm_kernel(const cd* __restrict__ A,
             cr[i][j] = d4{0, 0, 0, 0};
             ci[i][j] = d4{0, 0, 0, 0};
         }
-    cd a_cur[TM], b_cur[TN];
-    auto load = [&](int k0, cd* av, cd* bv) {
+    const cd* A0 = A + m0 * lda;
+    const BT* B0 = B + n0;
+    const int mr = M - m0 < 16 * TM ? (int)(M - m0) : 16 * TM;  // rows and columns of this tile
+    const int nc = N - n0 < 16 * TN ? (int)(N - n0) : 16 * TN;
+    int ra[TM], cb[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) ra[i] = min(16 * i + li, mr - 1) * (int)lda;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) cb[j] = min(16 * j + li, nc - 1);
+    auto load = [&](int k0, cd* av, BT* bv) {
         const int k = k0 + lk;
+        const int kc = k < K ? k : K - 1;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int64_t row = m0 + 16 * i + li;
-            av[i] = (row < M && k < K) ? A[row * lda + k] : cd{0.0, 0.0};
+            av[i] = A0[ra[i] + kc];
+            if (k >= K) av[i] = cd{0.0, 0.0};
         }
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int64_t col = n0 + 16 * j + li;
-            bv[j] = (col < N && k < K) ? B[(int64_t)k * ldb + col] : cd{0.0, 0.0};
-        }
+        for (int j = 0; j < TN; ++j) bv[j] = B0[(int64_t)kc * ldb + cb[j]];
     };
     // operands are prefetched two k-steps ahead: one step of MFMA work is
     // shorter than the HBM latency of the streamed B operand
-    cd a_n1[TM], b_n1[TN];
+    cd a_cur[TM], a_n1[TM];
+    BT b_cur[TN], b_n1[TN];
     load(0, a_cur, b_cur);
-    load(4, a_n1, b_n1);  // zeros where k >= K
+    load(4, a_n1, b_n1);
     for (int k0 = 0; k0 < K; k0 += 4) {
-        cd a_n2[TM], b_n2[TN];
-        load(k0 + 8, a_n2, b_n2);  // zeros past K
+        cd a_n2[TM];
+        BT b_n2[TN];
+        load(k0 + 8, a_n2, b_n2);
         // two passes over the tiles, so that dependent MFMAs on one accumulator
         // are 2 TM TN - 1 instructions apart
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_cur[i].x, b_cur[j].x, cr[i][j], 0, 0, 0);
-                ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_cur[i].x, b_cur[j].y, ci[i][j], 0, 0, 0);
-            }
+            for (int j = 0; j < TN; ++j) Z::step1(a_cur[i], b_cur[j], cr[i][j], ci[i][j]);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a_cur[i].y, b_cur[j].y, cr[i][j], 0, 0, 0);
-                ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a_cur[i].y, b_cur[j].x, ci[i][j], 0, 0, 0);
-            }
+            for (int j = 0; j < TN; ++j) Z::step2(a_cur[i], b_cur[j], cr[i][j], ci[i][j]);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             a_cur[i] = a_n1[i];
@@ -141,31 +170,81 @@ __global__ __launch_bounds__(256, 2) void zgemm_kernel(const cd* __restrict__ A,
             }
 }
 
-hipError_t launch_zgemm(const cd* A, int64_t lda, const cd* B, int64_t ldb, cd* C, int64_t ldc,
+// The same product where the tiles alone leave most of the chip idle (a few hundred
+// points): a work-group owns one 16 x 16 tile and its kKSplit waves take the k-steps
+// in turn (wave w steps w, w + kKSplit, ...); their sums meet in LDS in wave order.
+constexpr int kKSplit = 8;
+template <class BT>
+__global__ __launch_bounds__(64 * kKSplit) void zgemm_ksplit_kernel(
+    const cd* __restrict__ A, int64_t lda, const BT* __restrict__ B, int64_t ldb,
+    cd* __restrict__ C, int64_t ldc, int64_t M, int64_t N, int K) {
+    using Z = ZgemmB<BT>;
+    __shared__ cd sC[kKSplit][256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int64_t m0 = (int64_t)blockIdx.y * 16, n0 = (int64_t)blockIdx.x * 16;
+    const int64_t row = m0 + li < M ? m0 + li : M - 1, col = n0 + li < N ? n0 + li : N - 1;
+    d4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int k0 = 4 * wave; k0 < K; k0 += 4 * kKSplit) {
+        const int k = k0 + lk, kc = k < K ? k : K - 1;
+        cd a = A[row * lda + kc];
+        const BT b = B[(int64_t)kc * ldb + col];
+        if (k >= K) a = cd{0.0, 0.0};
+        Z::step1(a, b, cr, ci);
+        Z::step2(a, b, cr, ci);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sC[wave][(lk + 4 * v) * 16 + li] = cd{cr[v], ci[v]};
+    __syncthreads();
+    for (int e = threadIdx.x; e < 256; e += 64 * kKSplit) {
+        cd s = sC[0][e];
+#pragma unroll
+        for (int w = 1; w < kKSplit; ++w) s = cd{s.x + sC[w][e].x, s.y + sC[w][e].y};
+        const int64_t r = m0 + (e >> 4), c = n0 + (e & 15);
+        if (r < M && c < N) C[r * ldc + c] = s;
+    }
+}
+
+template <class BT>
+static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* C, int64_t ldc,
                         int64_t M, int64_t N, int K, hipStream_t s) {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (K <= 0) return hipErrorInvalidValue;
-    // Tall-and-narrow products (Fourier transforms over many points) use 4 row
-    // tiles per wave; short-and-wide ones (stage 1, M = a batch of k) cover all
-    // rows of up to 128 in one work-group so each B column is read once.
-    if (M <= 64) {
-        const int TM = 4, TN = 2;
-        dim3 grid((unsigned)((N + 4 * 16 * TN - 1) / (4 * 16 * TN)), (unsigned)((M + 63) / 64));
-        hipLaunchKernelGGL((zgemm_kernel<TM, TN>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
-                           M, N, K);
-    } else if (M <= 128) {
-        const int TM = 8, TN = 1;
-        dim3 grid((unsigned)((N + 4 * 16 * TN - 1) / (4 * 16 * TN)), (unsigned)((M + 127) / 128));
-        hipLaunchKernelGGL((zgemm_kernel<TM, TN>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
-                           M, N, K);
-    } else {
-        const int TM = 4, TN = 1;
-        dim3 grid((unsigned)((N + 4 * 16 * TN - 1) / (4 * 16 * TN)),
-                  (unsigned)((M + 16 * TM - 1) / (16 * TM)));
-        hipLaunchKernelGGL((zgemm_kernel<TM, TN>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
-                           M, N, K);
-    }
-    return hipGetLastError();
+    auto go = [&](auto kernel, int tm, int tn) {
+        dim3 grid((unsigned)((N + 64 * tn - 1) / (64 * tn)), (unsigned)((M + 16 * tm - 1) / (16 * tm)));
+        // Under four work-groups (one wave per SIMD each) per CU the tiles wait on their
+        // loads: 13,824 points x 256 x 343, 864 work-groups, 243 us against 187 us with K
+        // split; 301 points, 20 work-groups, 47 against 12 us.  (Also rows too long for
+        // the tiles' 32-bit offsets.)
+        if ((int64_t)grid.x * grid.y < 1024 || lda > ((int64_t)1 << 24)) {
+            grid = dim3((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16));
+            hipLaunchKernelGGL(zgemm_ksplit_kernel<BT>, grid, dim3(64 * kKSplit), 0, s, A, lda, B,
+                               ldb, C, ldc, M, N, K);
+        } else {
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, M, N, K);
+        }
+        return hipGetLastError();
+    };
+    // Short-and-wide products (stage 1, M = a batch of up to 64 k) cover all rows in one
+    // work-group, so each B column is read once, with no more row tiles than the rows
+    // fill: up to 32 rows the product is bound by the read of B, above by its MFMAs
+    // (4 k x 343 Re x 1.3M columns, 7.2 GB: 4.05 ms with four row tiles, 1.36 ms with
+    // one).  Tall-and-narrow ones (Fourier transforms over many points) use 4 row tiles
+    // per wave.
+    if (M <= 16) return go(zgemm_kernel<1, 4, 3, BT>, 1, 4);
+    if (M <= 32) return go(zgemm_kernel<2, 2, 3, BT>, 2, 2);
+    if (M <= 64) return go(zgemm_kernel<4, 2, 2, BT>, 4, 2);
+    return go(zgemm_kernel<4, 1, 2, BT>, 4, 1);
+}
+
+hipError_t launch_zgemm(const cd* A, int64_t lda, const cd* B, int64_t ldb, cd* C, int64_t ldc,
+                        int64_t M, int64_t N, int K, hipStream_t s) {
+    return zgemm<cd>(A, lda, B, ldb, C, ldc, M, N, K, s);
+}
+hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_t ldb, cd* C,
+                               int64_t ldc, int64_t M, int64_t N, int K, hipStream_t s) {
+    return zgemm<double>(A, lda, B, ldb, C, ldc, M, N, K, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -197,17 +276,18 @@ hipError_t launch_transpose_batch(cd* U, int64_t count, int n, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Mass weighting of the force constants: D-kernel entries Phi(R)/sqrt(M_s M_s')
 // ---------------------------------------------------------------------------
-__global__ void mass_weight_kernel(const double* phi, const double* mass, int nR, int nm, cd* out) {
+__global__ void mass_weight_kernel(const double* phi, const double* mass, int nR, int nm,
+                                   double* out) {
     const int64_t total = (int64_t)nR * nm * nm;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
          t += (int64_t)gridDim.x * blockDim.x) {
         const int j = (int)(t % nm);
         const int i = (int)((t / nm) % nm);
-        out[t] = cd{phi[t] / sqrt(mass[i / 3] * mass[j / 3]), 0.0};
+        out[t] = phi[t] / sqrt(mass[i / 3] * mass[j / 3]);
     }
 }
 
-hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int nm, cd* out,
+hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int nm, double* out,
                               hipStream_t s) {
     hipLaunchKernelGGL(mass_weight_kernel, dim3(grid_for((int64_t)nR * nm * nm, 256)), dim3(256),
                        0, s, phi, mass, nR, nm, out);

@@ -270,3 +270,19 @@ def test_realistic_size_mesh_launch_fp32(lib):
     print("GPU done", flush=True)
     ref = coupling.coupling(k, _mesh_frac(mesh, iq), s)
     _compare(got, ref, 1e-6)
+
+
+@pytest.mark.parametrize("nk", [1, 16, 17, 32, 33, 64])
+def test_stage1_row_tiles(lib, nk):
+    """Re sum of 1..64 k over 270,000 columns: one, two and four row tiles per work-group
+    (full and ragged), a K remainder (7 Re) and a ragged last column block."""
+    s = synth.small_system(58, n_wannier=12, n_atoms=5, r=1)
+    rng = np.random.default_rng(58)
+    s.re = np.ascontiguousarray(s.re[rng.choice(27, size=7, replace=False)])
+    s.rp = synth.box_vectors(2)
+    shape = (7, 125, 15, 12, 12)
+    s.g_rr = (rng.standard_normal(shape) + 1j * rng.standard_normal(shape)) * \
+        np.exp(-np.linalg.norm(s.rp, axis=1) / 0.8)[None, :, None, None, None]
+    k = rng.uniform(-1, 1, size=(nk, 3))
+    q = rng.uniform(-1, 1, size=(2, 3))
+    _compare(_run(lib, s, k, q), coupling.coupling(k, q, s), 1e-11)
