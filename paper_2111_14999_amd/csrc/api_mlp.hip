@@ -29,79 +29,187 @@ void check_net(Handle* h, int n_in, int width, int depth) {
             "network shape out of range (n_in %d, width %d, depth %d)", n_in, width, depth);
 }
 
-template <class T>
-void forward_impl(Handle* h, const Net& net, const T* P, const T* X, int64_t B, T* out,
-                  std::vector<T*>& Z, std::vector<T*>& A, hipStream_t s) {
-    const T* a = X;
-    int64_t off = 0;
+// Forward pass of B samples.  FP64 keeps every layer's z and silu(z) for the gradient;
+// FP32 storage writes z only where Z[l] is set (the activations are all that inference
+// needs) and, for the last layer, to `out` when it is set.
+void forward_impl(Handle* h, const Net& net, const double* P, const double* X, int64_t B, double* out,
+                  std::vector<double*>& Z, std::vector<double*>& A, hipStream_t s) {
+    const double* a = X;
     for (size_t l = 0; l < net.shape.size(); ++l) {
         const int o = net.shape[l].first, i = net.shape[l].second;
-        const T* W = P + off;
-        const T* b = P + off + (int64_t)o * i;
-        off += (int64_t)o * i + o;
-        T* z = (l + 1 == net.shape.size() && out) ? out : Z[l];
         const bool hidden = l + 1 < net.shape.size();
-        // hidden layers: z and silu(z) from the same pass
-        HIPCHK(h, launch_mlp_gemm<T>(false, true, a, i, W, i, z, o, B, o, i, b, 0, s,
-                                     hidden ? A[l] : nullptr));
-        if (hidden) a = A[l];
+        double* z = !hidden && out ? out : Z[l];
+        HIPCHK(h, launch_mlp_gemm_f64(false, true, a, i, P, i, z, o, B, o, i, P + (int64_t)o * i,
+                                      s));
+        if (hidden) {
+            HIPCHK(h, launch_silu_fwd<double>(z, A[l], B * o, s));
+            a = A[l];
+        }
+        P += (int64_t)o * i + o;
+    }
+}
+void forward_impl(Handle* h, const Net& net, const float* P, const float* X, int64_t B, float* out,
+                  std::vector<float*>& Z, std::vector<float*>& A, hipStream_t s) {
+    const float* a = X;
+    for (size_t l = 0; l < net.shape.size(); ++l) {
+        const int o = net.shape[l].first, i = net.shape[l].second;
+        const bool hidden = l + 1 < net.shape.size();
+        MlpJob g{};
+        g.A = a;
+        g.lda = i;
+        g.B = P;
+        g.ldb = i;
+        g.C = !hidden && out ? out : Z[l];
+        g.M = B;
+        g.N = o;
+        g.K = g.kchunk = i;
+        g.nsplit = 1;
+        g.bias = P + (int64_t)o * i;
+        g.act = hidden ? A[l] : nullptr;
+        HIPCHK(h, launch_mlp_forward(g, s));
+        a = A[l];
+        P += (int64_t)o * i + o;
     }
 }
 
-template <class T>
-void grad_impl(Handle* h, const Net& net, const T* P, const T* X, const T* target, int64_t B,
-               T* grad, double* loss, hipStream_t s) {
+// offsets of each layer's parameters in the packed vector
+std::vector<int64_t> layer_offsets(const Net& net) {
+    std::vector<int64_t> offs;
+    int64_t off = 0;
+    for (const auto& sh : net.shape) {
+        offs.push_back(off);
+        off += (int64_t)sh.first * sh.second + sh.first;
+    }
+    return offs;
+}
+
+void read_loss(Handle* h, const double* sums, int nblk, int64_t B, double* loss, hipStream_t s) {
+    if (!loss) return;
+    std::vector<double> hs(nblk);
+    HIPCHK(h, hipMemcpyAsync(hs.data(), sums, sizeof(double) * nblk, hipMemcpyDeviceToHost, s));
+    HIPCHK(h, hipStreamSynchronize(s));
+    double t = 0.0;
+    for (double v : hs) t += v;
+    *loss = t / (double)B;
+}
+
+void grad_impl(Handle* h, const Net& net, const double* P, const double* X, const double* target,
+               int64_t B, double* grad, double* loss, hipStream_t s) {
     const size_t L = net.shape.size();
-    auto plan = [&](Arena& ar, std::vector<T*>& Z, std::vector<T*>& A, T*& dZ, T*& dA,
-                    double*& sums) {
+    std::vector<double*> Z(L), A(L);
+    double *dZ, *dA, *sums;
+    auto plan = [&](Arena& ar) {
         for (size_t l = 0; l < L; ++l) {
-            Z[l] = ar.take<T>((size_t)B * net.shape[l].first);
-            A[l] = ar.take<T>((size_t)B * net.shape[l].first);
+            Z[l] = ar.take<double>((size_t)B * net.shape[l].first);
+            A[l] = ar.take<double>((size_t)B * net.shape[l].first);
         }
-        dZ = ar.take<T>((size_t)B * std::max(net.width, 1));
-        dA = ar.take<T>((size_t)B * std::max(net.width, 1));
+        dZ = ar.take<double>((size_t)B * std::max(net.width, 1));
+        dA = ar.take<double>((size_t)B * std::max(net.width, 1));
         sums = ar.take<double>(256);
     };
-    std::vector<T*> Z(L), A(L);
-    T *dZ, *dA;
-    double* sums;
     Arena dry(nullptr);
-    plan(dry, Z, A, dZ, dA, sums);
+    plan(dry);
     ensure_ws(h, dry.used + 256);
     Arena ar(h->ws, h->ws_cap);
-    plan(ar, Z, A, dZ, dA, sums);
-    forward_impl<T>(h, net, P, X, B, nullptr, Z, A, s);
+    plan(ar);
+    forward_impl(h, net, P, X, B, nullptr, Z, A, s);
     const int nblk = (int)std::min<int64_t>(256, (B + 255) / 256);
-    HIPCHK(h, launch_mse_grad<T>(Z[L - 1], target, dZ, B, sums, nblk, s));
-    // offsets of each layer's parameters
-    std::vector<int64_t> offs(L);
-    int64_t off = 0;
-    for (size_t l = 0; l < L; ++l) {
-        offs[l] = off;
-        off += (int64_t)net.shape[l].first * net.shape[l].second + net.shape[l].first;
-    }
+    HIPCHK(h, launch_mse_grad<double>(Z[L - 1], target, dZ, B, sums, nblk, s));
+    const std::vector<int64_t> offs = layer_offsets(net);
     for (int l = (int)L - 1; l >= 0; --l) {
         const int o = net.shape[l].first, i = net.shape[l].second;
-        const T* aprev = l == 0 ? X : A[l - 1];
+        const double* aprev = l == 0 ? X : A[l - 1];
         // dW[o, i] = dZ^T[o, B] a_prev[B, i]
-        HIPCHK(h, launch_mlp_gemm<T>(true, false, dZ, o, aprev, i, grad + offs[l], i, o, i, B, nullptr,
-                                     0, s));
-        HIPCHK(h, launch_colsum<T>(dZ, B, o, grad + offs[l] + (int64_t)o * i, s));
+        HIPCHK(h, launch_mlp_gemm_f64(true, false, dZ, o, aprev, i, grad + offs[l], i, o, i, B,
+                                      nullptr, s));
+        HIPCHK(h, launch_colsum<double>(dZ, B, o, grad + offs[l] + (int64_t)o * i, s));
         if (l > 0) {
             // dA[B, i] = dZ[B, o] W[o, i]; dZ_prev = dA * silu'(z_prev)
-            HIPCHK(h, launch_mlp_gemm<T>(false, false, dZ, o, P + offs[l], i, dA, i, B, i, o, nullptr,
-                                         0, s));
-            HIPCHK(h, launch_silu_bwd<T>(dA, Z[l - 1], dZ, B * i, s));
+            HIPCHK(h, launch_mlp_gemm_f64(false, false, dZ, o, P + offs[l], i, dA, i, B, i, o, nullptr,
+                                          s));
+            HIPCHK(h, launch_silu_bwd<double>(dA, Z[l - 1], dZ, B * i, s));
         }
     }
-    if (loss) {
-        std::vector<double> hs(nblk);
-        HIPCHK(h, hipMemcpyAsync(hs.data(), sums, sizeof(double) * nblk, hipMemcpyDeviceToHost, s));
-        HIPCHK(h, hipStreamSynchronize(s));
-        double t = 0.0;
-        for (double v : hs) t += v;
-        *loss = t / (double)B;
+    read_loss(h, sums, nblk, B, loss, s);
+}
+
+void grad_impl(Handle* h, const Net& net, const float* P, const float* X, const float* target,
+               int64_t B, float* grad, double* loss, hipStream_t s) {
+    const size_t L = net.shape.size();
+    const std::vector<int64_t> offs = layer_offsets(net);
+    std::vector<float*> Z(L), A(L), W(L);
+    float* dZ[2];
+    double* sums;
+    std::vector<double*> bs(L);
+    std::vector<int> split(L);
+    std::vector<int64_t> kchunk(L);
+    bool splits = true;  // weight gradients as split partial sums, where the budget holds them
+    auto plan = [&](Arena& ar) {
+        for (size_t l = 0; l < L; ++l) {
+            const int o = net.shape[l].first, i = net.shape[l].second;
+            Z[l] = ar.take<float>((size_t)B * o);
+            A[l] = l + 1 < L ? ar.take<float>((size_t)B * o) : nullptr;
+            split[l] = splits ? mlp_splits(o, i, B, &kchunk[l]) : 1;
+            if (split[l] == 1) kchunk[l] = B;
+            W[l] = split[l] > 1 ? ar.take<float>((size_t)split[l] * o * i) : nullptr;
+            bs[l] = ar.take<double>((size_t)split[l] * o);
+        }
+        for (auto& d : dZ) d = ar.take<float>((size_t)B * std::max(net.width, 1));
+        sums = ar.take<double>(256);
+    };
+    Arena dry(nullptr);
+    plan(dry);
+    if (dry.used + 256 > std::max(h->budget, h->ws_cap)) {
+        splits = false;
+        dry = Arena(nullptr);
+        plan(dry);
     }
+    ensure_ws(h, dry.used + 256);
+    Arena ar(h->ws, h->ws_cap);
+    plan(ar);
+    forward_impl(h, net, P, X, B, nullptr, Z, A, s);
+    const int nblk = (int)std::min<int64_t>(256, (B + 255) / 256);
+    HIPCHK(h, launch_mse_grad<float>(Z[L - 1], target, dZ[0], B, sums, nblk, s));
+    MlpGradParts parts{};
+    parts.layers = (int)L;
+    parts.total = net.count;
+    for (int l = (int)L - 1, cur = 0; l >= 0; --l, cur ^= 1) {
+        const int o = net.shape[l].first, i = net.shape[l].second;
+        MlpJob dw{};  // dW[o, i] = dZ^T[o, B] a_prev[B, i], db[o] = dZ's column sums
+        dw.A = dZ[cur];
+        dw.lda = o;
+        dw.B = l == 0 ? X : A[l - 1];
+        dw.ldb = i;
+        dw.C = split[l] > 1 ? W[l] : grad + offs[l];
+        dw.M = o;
+        dw.N = i;
+        dw.K = B;
+        dw.kchunk = kchunk[l];
+        dw.nsplit = split[l];
+        dw.colsum = bs[l];
+        MlpJob da{};  // dZ_prev[B, i] = (dZ[B, o] W[o, i]) silu'(z_prev)
+        if (l > 0) {
+            da.A = dZ[cur];
+            da.lda = o;
+            da.B = P + offs[l];
+            da.ldb = i;
+            da.C = dZ[cur ^ 1];
+            da.M = B;
+            da.N = i;
+            da.K = da.kchunk = o;
+            da.nsplit = 1;
+            da.zprev = Z[l - 1];
+        }
+        HIPCHK(h, launch_mlp_backward(l > 0 ? &da : nullptr, dw, s));
+        parts.off[l] = offs[l];
+        parts.out[l] = o;
+        parts.in[l] = i;
+        parts.split[l] = split[l];
+        parts.w[l] = W[l];
+        parts.b[l] = bs[l];
+    }
+    HIPCHK(h, launch_mlp_grad_reduce(parts, grad, s));
+    read_loss(h, sums, nblk, B, loss, s);
 }
 
 }  // namespace
@@ -132,7 +240,8 @@ phoebe_status phoebe_gpu_mlp_forward(void* handle, phoebe_precision prec, const 
             std::vector<T*> Z(net.shape.size()), A(net.shape.size());
             auto plan = [&](Arena& ar) {
                 for (size_t l = 0; l < net.shape.size(); ++l) {
-                    Z[l] = ar.take<T>((size_t)batch * net.shape[l].first);
+                    // (FP32 storage: z of the hidden layers is not written)
+                    Z[l] = sizeof(T) == 8 ? ar.take<T>((size_t)batch * net.shape[l].first) : nullptr;
                     A[l] = ar.take<T>((size_t)batch * net.shape[l].first);
                 }
             };
@@ -141,7 +250,7 @@ phoebe_status phoebe_gpu_mlp_forward(void* handle, phoebe_precision prec, const 
             ensure_ws(h, dry.used + 256);
             Arena ar(h->ws, h->ws_cap);
             plan(ar);
-            forward_impl<T>(h, net, (const T*)params, (const T*)X, batch, (T*)out, Z, A, s);
+            forward_impl(h, net, (const T*)params, (const T*)X, batch, (T*)out, Z, A, s);
         };
         if (prec == PHOEBE_FP64)
             go((double*)nullptr);
@@ -166,10 +275,10 @@ phoebe_status phoebe_gpu_mlp_grad(void* handle, phoebe_precision prec, const voi
         HIPCHK(h, hipSetDevice(h->device));
         const Net net(n_in, width, depth);
         if (prec == PHOEBE_FP64)
-            grad_impl<double>(h, net, (const double*)params, (const double*)X, (const double*)target,
+            grad_impl(h, net, (const double*)params, (const double*)X, (const double*)target,
                               batch, (double*)grad, loss, s);
         else
-            grad_impl<float>(h, net, (const float*)params, (const float*)X, (const float*)target,
+            grad_impl(h, net, (const float*)params, (const float*)X, (const float*)target,
                              batch, (float*)grad, loss, s);
         HIPCHK(h, hipGetLastError());
     });
@@ -272,7 +381,6 @@ phoebe_status phoebe_gpu_propose_q(void* handle, const int32_t mesh[3], int32_t 
                 list = ar.take<int32_t>((size_t)nk * NR);
                 X = ar.take<float>((size_t)chunk * n_in);
                 for (size_t l = 0; l < net.shape.size(); ++l) {
-                    Z[l] = ar.take<float>((size_t)chunk * net.shape[l].first);
                     A[l] = ar.take<float>((size_t)chunk * net.shape[l].first);
                 }
                 y = ar.take<float>((size_t)chunk);
@@ -303,7 +411,7 @@ phoebe_status phoebe_gpu_propose_q(void* handle, const int32_t mesh[3], int32_t 
                 const int64_t nc = std::min<int64_t>(chunk, cnt - c0);
                 HIPCHK(h, launch_features_flat(kd, ek, list + c0, nc, NR, m, n_modes, n_harm, e0,
                                                escale, X, s));
-                forward_impl<float>(h, net, params, X, nc, y, Z, A, s);
+                forward_impl(h, net, params, X, nc, y, Z, A, s);
                 HIPCHK(h, launch_weight_list(dweights, list + c0, y, nc, E, s));
             }
             HIPCHK(h, launch_sum_modes(E, nk * N, n_modes, p, s));

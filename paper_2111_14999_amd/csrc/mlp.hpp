@@ -5,11 +5,35 @@
 
 namespace phx {
 
-// with act set, silu(C) is also written to act (same leading dimension)
-template <class T>
-hipError_t launch_mlp_gemm(bool ta, bool tb, const T* A, int64_t lda, const T* B, int64_t ldb, T* C,
-                           int64_t ldc, int64_t M, int64_t N, int64_t K, const T* bias, int acc,
-                           hipStream_t s, T* act = nullptr);
+// One BF16 product of the network (see mlp_tile): C [M, N] (leading dimension N).
+struct MlpJob {
+    const float *A, *B;
+    int64_t lda, ldb;
+    float* C;            // [nsplit, M, N]; may be NULL with act set
+    int64_t M, N, K;
+    const float* bias;   // [N] or NULL
+    float* act;          // [M, N] silu(C) or NULL
+    const float* zprev;  // [M, N] or NULL: C = (A B) silu'(zprev)
+    double* colsum;      // [nsplit, M] or NULL (weight gradients only)
+    int64_t kchunk;      // K range of a split (K where nsplit = 1), a multiple of 64 otherwise
+    int nsplit;
+};
+// Split partial sums of every layer's gradients; off: packed offset of W_l, then b_l.
+constexpr int kMlpLayers = 17;
+struct MlpGradParts {
+    int layers;
+    int64_t total, off[kMlpLayers];
+    int out[kMlpLayers], in[kMlpLayers], split[kMlpLayers];
+    const float* w[kMlpLayers];
+    const double* b[kMlpLayers];
+};
+int mlp_splits(int64_t M, int64_t N, int64_t K, int64_t* kchunk);
+hipError_t launch_mlp_forward(const MlpJob& g, hipStream_t s);
+hipError_t launch_mlp_backward(const MlpJob* da, const MlpJob& dw, hipStream_t s);
+hipError_t launch_mlp_grad_reduce(const MlpGradParts& t, float* grad, hipStream_t s);
+hipError_t launch_mlp_gemm_f64(bool ta, bool tb, const double* A, int64_t lda, const double* B,
+                               int64_t ldb, double* C, int64_t ldc, int64_t M, int64_t N, int64_t K,
+                               const double* bias, hipStream_t s);
 template <class T>
 hipError_t launch_silu_fwd(const T* z, T* a, int64_t n, hipStream_t s);
 template <class T>

@@ -364,3 +364,31 @@ def test_importance_sampling_unbiased_with_gain(lib):
     # what the smearing weights alone give
     assert np.median(var["learned"] / var["uniform"]) < 0.2
     assert np.median(var["learned"] / var["smearing"]) < 1.0
+
+
+@pytest.mark.parametrize("n_in,width,depth,B", [
+    (1, 1, 1, 1),        # every product a single element
+    (22, 64, 2, 64),     # full tiles, no K split
+    (23, 65, 2, 129),    # one past a tile; two K splits of unequal length
+    (7, 30, 3, 1000),    # narrow layers: many splits, unaligned rows
+    (22, 320, 1, 4096),  # 25 tiles per weight gradient
+])
+def test_bf16_gradient_tiles(lib, n_in, width, depth, B):
+    """Gradient at the edges of the 64 x 64 tiles and of the K splits, against the
+    backpropagation with every product's operands rounded to BF16 (bounds as above)."""
+    torch = torch_cuda()
+    theta, X, t = (a.astype(np.float32) for a in _net_case(3, n_in, width, depth, B))
+    loss_b, g_b = mlp.loss_and_grad(theta.astype(np.float64), X.astype(np.float64),
+                                    t.astype(np.float64), n_in, width, depth,
+                                    operand=mlp.round_bf16)
+    P = torch.from_numpy(theta).cuda()
+    g = torch.full_like(P, float("nan"))
+    y = torch.full((B,), float("nan"), device="cuda")
+    Xd = torch.from_numpy(X).cuda()
+    loss = lib.mlp_grad(P, Xd, torch.from_numpy(t).cuda(), g, n_in, width, depth, precision="bf16")
+    lib.mlp_forward(P, Xd, y, n_in, width, depth)
+    torch.cuda.synchronize()
+    gg, gmax = g.cpu().numpy().astype(np.float64), np.max(np.abs(g_b))
+    assert abs(loss - loss_b) < 1e-5 * loss_b
+    assert abs(np.mean((y.cpu().numpy().astype(np.float64) - t) ** 2) - loss_b) < 1e-5 * loss_b
+    assert np.all(np.abs(gg - g_b) <= 1e-3 * np.abs(g_b) + 3e-5 * gmax)
