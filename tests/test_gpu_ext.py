@@ -263,6 +263,20 @@ def test_velocities_match_oracle(lib):
     assert np.max(np.abs(E.cpu().numpy() - eps)) < 1e-12 * np.max(np.abs(eps))
 
 
+@pytest.mark.parametrize("nW", [1, 3, 16, 17, 32])
+def test_velocities_band_tiles(lib, nW):
+    """One and two 16-band passes, full and ragged, against the oracle."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(90 + nW, n_wannier=nW, n_atoms=1, r=1)
+    k = np.random.default_rng(nW).uniform(-1, 1, size=(7, 3))
+    _, v = velocity.group_velocities(k, s.rh, s.h_r)
+    V = torch.zeros((7, nW, 3), dtype=torch.float64, device="cuda")
+    lib.velocities(DeviceSystem.from_host(s, with_coupling=False), torch.from_numpy(k).cuda(), V)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(V.cpu().numpy() - v)) < V_BOUND * np.max(np.abs(v))
+
+
 def test_velocities_degenerate_pair(lib):
     """Two orbitals degenerate on the k_x = k_y plane: the 2x2 velocity block is
     diagonalised per direction (closed form, and the oracle)."""
