@@ -343,9 +343,9 @@ phoebe_status phoebe_gpu_batched_plan(void* handle, const phoebe_system* systems
             HIPCHK(h, hipStreamSynchronize(s));
             {
                 Arena b1(h->ws, h->ws_cap), b2(h->ws, h->ws_cap);
-                electron_bands_dev(h, b1, sys, p.rh, nullptr, nullptr, p.mesh, p.N, p.eps, p.U, s);
-                // the rate kernels read each eigenvector contiguously
-                HIPCHK(h, launch_transpose_batch(p.U, p.N, p.nW, s));
+                // (eigenvectors as rows: the rate kernels read each one contiguously)
+                electron_bands_dev(h, b1, sys, p.rh, nullptr, nullptr, p.mesh, p.N, p.eps, p.U, s,
+                                   true);
                 phonon_dev(h, b2, sys, p.rd, nullptr, nullptr, p.mesh, p.N, par->omega_min, par->kT,
                            p.omega, p.E, p.nb, nullptr, s);
             }

@@ -265,7 +265,7 @@ struct BandBufs {
 
 inline void electron_bands_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int32_t* rh_d,
                         const double* frac, const int32_t* idx, Mesh m, int64_t np, double* eps,
-                        cd* U, hipStream_t s) {
+                        cd* U, hipStream_t s, bool u_transposed = false) {
     const int nW = sys->n_wannier, nR = sys->n_rh;
     cd* P = ar.take<cd>((size_t)np * nR);
     cd* H = ar.take<cd>((size_t)np * nW * nW);
@@ -276,7 +276,7 @@ inline void electron_bands_dev(Handle* h, Arena& ar, const phoebe_system* sys, c
                            (int64_t)nW * nW, np, (int64_t)nW * nW, nR, s));
     t.done();
     Timer te(h, s, "eig_jacobi");
-    HIPCHK(h, launch_eig_herm(H, nW, np, eps, U, s));
+    HIPCHK(h, launch_eig_herm(H, nW, np, eps, U, u_transposed, s));
     te.done();
 }
 
@@ -294,7 +294,7 @@ inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int
     HIPCHK(h, launch_mass_weight(sys->phi_r, sys->mass, nR, nm, phic, s));
     HIPCHK(h, launch_zgemm_real_b(P, nR, phic, (int64_t)nm * nm, D, (int64_t)nm * nm, np,
                                   (int64_t)nm * nm, nR, s));
-    HIPCHK(h, launch_eig_herm(D, nm, np, lam, z, s));
+    HIPCHK(h, launch_eig_herm(D, nm, np, lam, z, false, s));
     HIPCHK(h, launch_phonon_post(lam, z, sys->mass, sys->n_atoms, np, omega_min, kT, omega, E, nb,
                                  s));
 }

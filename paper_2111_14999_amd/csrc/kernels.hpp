@@ -25,9 +25,11 @@ hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_
 hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int nm, double* out,
                               hipStream_t s);
 
-// In-place batched Hermitian eigensolver (cyclic Jacobi, FP64).  A [batch, n, n]
-// is destroyed; w [batch, n] ascending; V [batch, n, n] eigenvectors as columns.
-hipError_t launch_eig_herm(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s);
+// Batched Hermitian eigensolver (cyclic Jacobi, FP64), n <= 32.  A [batch, n, n];
+// w [batch, n] ascending; V [batch, n, n] eigenvectors as columns, or as rows with vt
+// (the rate path reads each eigenvector contiguously).
+hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, bool vt,
+                           hipStream_t s);
 
 // Phonon post-processing: omega = C_OMEGA sqrt(max(lam, 0)); e[q, sa, nu] =
 // z[q, sa, nu] l_{s, q nu} (0 when omega < omega_min); nb Bose occupation
@@ -53,8 +55,6 @@ hipError_t launch_band_extrema(const double* eps, int64_t nk, int nW, const doub
                                int64_t nq, int nm, double* bmin, double* bmax, double* wmax,
                                hipStream_t s);
 
-// In-place transpose of count n x n complex matrices.
-hipError_t launch_transpose_batch(cd* U, int64_t count, int n, hipStream_t s);
 
 // Stage-1 fold: F[st, r, sa*nW + b] = sum_a conj(U_k[a, n]) G[kb, r, sa, a, b]
 // for each state st = (kb, n); rows r >= n_rp and columns >= NC are zero.

@@ -248,32 +248,6 @@ hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_
 }
 
 // ---------------------------------------------------------------------------
-// In-place transpose of a batch of n x n matrices: the rate path keeps each
-// eigenvector contiguous (Ut[k, band, orbital] = U_k[orbital, band]), so a
-// band's column is one coalesced read.
-// ---------------------------------------------------------------------------
-__global__ void transpose_batch_kernel(cd* U, int64_t count, int n) {
-    const int64_t total = count * n * n;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int j = (int)(t % n);
-        const int i = (int)((t / n) % n);
-        if (i >= j) continue;
-        const int64_t base = (t / ((int64_t)n * n)) * n * n;
-        const cd a = U[base + (int64_t)i * n + j];
-        U[base + (int64_t)i * n + j] = U[base + (int64_t)j * n + i];
-        U[base + (int64_t)j * n + i] = a;
-    }
-}
-
-hipError_t launch_transpose_batch(cd* U, int64_t count, int n, hipStream_t s) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(transpose_batch_kernel, dim3(grid_for(count * n * n, 256)), dim3(256), 0, s,
-                       U, count, n);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
 // Mass weighting of the force constants: D-kernel entries Phi(R)/sqrt(M_s M_s')
 // ---------------------------------------------------------------------------
 __global__ void mass_weight_kernel(const double* phi, const double* mass, int nR, int nm,
@@ -294,353 +268,314 @@ hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Batched Hermitian eigensolver: cyclic Jacobi with the round-robin parallel
-// ordering, one wavefront per matrix, matrix and eigenvectors in LDS.
-// Rotation of pivot (p, q) with a = A_pp, d = A_qq, b = A_pq = |b| e^{i phi}:
-//   tau = (d - a) / (2|b|), t = sign(tau) / (|tau| + sqrt(1 + tau^2)),
-//   c = 1/sqrt(1 + t^2), s = t c,
-//   J_pp = J_qq = c, J_pq = s e^{i phi}, J_qp = -s e^{-i phi};  A <- J^H A J, V <- V J.
-// ---------------------------------------------------------------------------
-__device__ inline void rr_pair(int k, int round, int np, int& p, int& q) {
-    const int m = np - 1;
-    int a, b;
-    if (k == 0) {
-        a = m;
-        b = round;
-    } else {
-        a = (round + k) % m;
-        b = (round - k + m) % m;
-    }
-    p = a < b ? a : b;
-    q = a < b ? b : a;
-}
-
 __device__ inline double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
 
-// NT > 0 fixes the matrix order at compile time (index arithmetic without
-// integer division); NT = 0 takes it from the argument.
-template <int NT>
-__global__ __launch_bounds__(64) void eig_herm_kernel(cd* __restrict__ Aall, int n_arg,
-                                                      double* __restrict__ w_out,
-                                                      cd* __restrict__ V_out) {
-    const int n = NT > 0 ? NT : n_arg;
-    extern __shared__ char smem_raw[];
-    cd* A = reinterpret_cast<cd*>(smem_raw);
-    // odd row stride: 16 lanes walking down a column of 16-byte elements hit 16
-    // distinct 4-bank groups (an even stride such as 16 would serialise them)
-    const int ld = n | 1;
-    cd* V = A + n * ld;
-    double* rc = reinterpret_cast<double*>(V + n * ld);  // [n/2+1] c
-    double* rs = rc + (n / 2 + 1);                         // s
-    cd* re = reinterpret_cast<cd*>(rs + (n / 2 + 1));      // e^{i phi}
-    int* rp = reinterpret_cast<int*>(re + (n / 2 + 1));    // p
-    int* rq = rp + (n / 2 + 1);                            // q
-    const int64_t b = blockIdx.x;
-    const int lane = threadIdx.x;
-    cd* Ag = Aall + b * (int64_t)n * n;
-    for (int i = lane; i < n * n; i += 64) {
-        const int r = i / n, c = i % n;
-        A[r * ld + c] = Ag[i];
-        V[r * ld + c] = cd{r == c ? 1.0 : 0.0, 0.0};
-    }
-    __syncthreads();
-    const int np = n + (n & 1);
-    const int half = np / 2;
-    const double eps2 = 4.9e-32;  // (2.2e-16)^2
-    for (int sweep = 0; sweep < 40 && n > 1; ++sweep) {
-        int rotated = 0;
-        double off = 0.0, dia = 0.0;
-        for (int i = lane; i < n * n; i += 64) {
-            const int r = i / n, c = i % n;
-            const double v = cabs2(A[r * ld + c]);
-            if (r == c)
-                dia += v;
-            else
-                off += v;
-        }
-        off = wave_sum(off);
-        dia = wave_sum(dia);
-        if (!(off > 1e-32 * dia)) break;
-        // A pair is left alone once |A_pq|^2 is at the rounding level of its own diagonal
-        // entries or of the mean squared diagonal entry, whichever is larger: with the
-        // first test alone, pairs next to a zero eigenvalue keep rotating on rounding noise
-        // and the off-diagonal norm never falls below the stopping level above.
-        const double skip_abs = eps2 * dia / n;
-        for (int round = 0; round < np - 1; ++round) {
-            if (lane < half) {
-                int p, q;
-                rr_pair(lane, round, np, p, q);
-                double c = 1.0, s = 0.0;
-                cd e = {1.0, 0.0};
-                if (q < n) {
-                    const double a = A[p * ld + p].x, d = A[q * ld + q].x;
-                    const cd bpq = A[p * ld + q];
-                    const double bb2 = cabs2(bpq);
-                    if (bb2 > fmax(eps2 * fabs(a * d), skip_abs) && bb2 > 0.0) {
-                        rotated = 1;
-                        // (one reciprocal square root for 1/|b|, one for c: two
-                        // divisions and a square root fewer on the round's critical path)
-                        const double ib = rsqrt(bb2);
-                        const double tau = (d - a) * (0.5 * ib);
-                        const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(fma(tau, tau, 1.0)));
-                        c = rsqrt(fma(t, t, 1.0));
-                        s = t * c;
-                        e = cd{bpq.x * ib, bpq.y * ib};
-                    }
-                }
-                rc[lane] = c;
-                rs[lane] = s;
-                re[lane] = e;
-                rp[lane] = p;
-                rq[lane] = q < n ? q : -1;
-            }
-            __syncthreads();
-            // rows: A'_pj = c A_pj - s e A_qj ; A'_qj = s conj(e) A_pj + c A_qj
-            for (int it = lane; it < half * n; it += 64) {
-                const int k = it / n, j = it % n;
-                const int q = rq[k];
-                if (q < 0 || rs[k] == 0.0) continue;
-                const int p = rp[k];
-                const double c = rc[k], s = rs[k];
-                const cd e = re[k];
-                const cd apj = A[p * ld + j], aqj = A[q * ld + j];
-                const cd eq = cmul(e, aqj);
-                const cd ep = cmulc(e, apj);
-                A[p * ld + j] = cd{c * apj.x - s * eq.x, c * apj.y - s * eq.y};
-                A[q * ld + j] = cd{s * ep.x + c * aqj.x, s * ep.y + c * aqj.y};
-            }
-            __syncthreads();
-            // columns: A'_ip = c A_ip - s conj(e) A_iq ; A'_iq = s e A_ip + c A_iq ; same for V
-            for (int it = lane; it < 2 * half * n; it += 64) {
-                const int which = it / (half * n);
-                const int r = it % (half * n);
-                const int k = r / n, i = r % n;
-                const int q = rq[k];
-                if (q < 0 || rs[k] == 0.0) continue;
-                const int p = rp[k];
-                const double c = rc[k], s = rs[k];
-                const cd e = re[k];
-                cd* M = which ? V : A;
-                const cd aip = M[i * ld + p], aiq = M[i * ld + q];
-                const cd eq = cmulc(e, aiq);
-                const cd ep = cmul(e, aip);
-                M[i * ld + p] = cd{c * aip.x - s * eq.x, c * aip.y - s * eq.y};
-                M[i * ld + q] = cd{s * ep.x + c * aiq.x, s * ep.y + c * aiq.y};
-            }
-            __syncthreads();
-            if (lane < half) {
-                const int q = rq[lane];
-                if (q >= 0 && rs[lane] != 0.0) {
-                    const int p = rp[lane];
-                    A[p * ld + q] = cd{0.0, 0.0};
-                    A[q * ld + p] = cd{0.0, 0.0};
-                    A[p * ld + p].y = 0.0;
-                    A[q * ld + q].y = 0.0;
-                }
-            }
-            __syncthreads();
-        }
-        if (!__any(rotated)) break;  // a sweep with no rotation leaves A unchanged
-    }
-    // ascending order, ties by index
-    for (int i = lane; i < n; i += 64) {
-        const double wi = A[i * ld + i].x;
-        int rank = 0;
-        for (int j = 0; j < n; ++j) {
-            const double wj = A[j * ld + j].x;
-            rank += (wj < wi) || (wj == wi && j < i);
-        }
-        w_out[b * n + rank] = wi;
-        cd* Vg = V_out + b * (int64_t)n * n;
-        for (int r = 0; r < n; ++r) Vg[r * n + rank] = V[r * ld + i];
+// ---------------------------------------------------------------------------
+// Batched Hermitian eigensolver: cyclic Jacobi with the round-robin parallel
+// ordering, matrix and eigenvectors in LDS.  Round r of a sweep pairs the indices
+// (m, r), (r + k, r - k) mod m for k = 1 .. np/2 - 1, with np = n rounded up to even
+// and m = np - 1 (for odd n, m is a zero row and column that never rotates).
+// Rotation of pivot (f, g) with a = A_ff, d = A_gg, b = A_fg = |b| e^{i phi}:
+//   x = |d - a| / sqrt((d - a)^2 + 4 |b|^2),  c = sqrt((1 + x) / 2),
+//   s = sign(d - a) |b| / (c sqrt((d - a)^2 + 4 |b|^2))   (the smaller angle),
+//   J_ff = J_gg = c, J_fg = s e^{i phi}, J_gf = -s e^{-i phi};  A <- J^H A J, V <- V J
+// (two reciprocal square roots; the rotation of (g, f) is the same matrix).
+//
+// In a round the pairs partition the indices, so lane (I, J), I, J < H = np/2, owns the
+// 2 x 2 block of rows {f_I, g_I} and columns {f_J, g_J}; it rotates that block and V's
+// columns {f_J, g_J} on two of V's rows.  A wave holds as many matrices as fit (16 of
+// order 4, 2 of order 10, one of order 16) and a round then needs no barrier, only LDS
+// order; orders above 16 take H^2 threads and two barriers a round.
+//
+// The kernel is bound by LDS bandwidth, so the matrices are stored by slot: f_J at
+// position J, g_J at H + (J - 1 mod H), rows and columns alike.  From one round to the next
+// the indices move round the slots as on a conveyor (f_J -> f_{J-1}, f_1 -> g_0, g_J ->
+// g_{J+1}, g_{H-1} -> f_{H-1}, f_0 stays), so a lane always reads the same addresses and
+// writes its results where the next round expects them.  With this offset of the g slots
+// and a row stride of H modulo 8 (in 16-byte units), the eight lanes served in one LDS
+// cycle fall on distinct banks in reads and writes; stored by index they met 45 % of
+// extra cycles.  After a sweep every index is back at its first position.
+//
+// 64,000 matrices of order 16: 3.06 ms (parameters through LDS between two barriers,
+// sorted pairs stored by index) -> 2.89 ms (pairs per lane, no barriers) -> 2.72 ms (by
+// slot; LDS busy 0.8 of the time); 29,791 of order 20: 7.49 ms (row and column passes by
+// one wave) -> 3.25 ms; 9,384 of order 9: 325 -> 178 us; 301 of order 16: 108 -> 75 us.
+// ---------------------------------------------------------------------------
+// orders whose lanes fit a wave: no barrier, but the accesses keep their order
+template <int NW>
+__device__ inline void eig_sync() {
+    if constexpr (NW > 1) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 }
 
-// The same Jacobi method for n <= 16 with the work of a round split by 2 x 2
-// blocks: in a round the pairs partition the indices, so lane (I, J) (I, J <
-// n/2 rounded up) owns the block of rows {p_I, q_I} and columns {p_J, q_J}.
-// The two-sided rotation of that block reads only the block (rows by pair I,
-// then columns by pair J), and so does the column rotation of V on rows
-// {2I, 2I + 1}: every lane reads, rotates and writes its own elements, and a
-// round needs one barrier after the parameters and one after the update.
-// The pair order, the skip test and the stopping rule are those above.
-template <int NT>
-__global__ __launch_bounds__(64) void eig_herm_blk_kernel(cd* __restrict__ Aall, int n_arg,
-                                                          double* __restrict__ w_out,
-                                                          cd* __restrict__ V_out) {
-    const int n = NT > 0 ? NT : n_arg;
-    constexpr int LD = 17;  // odd row stride (see above)
-    __shared__ cd A[16 * LD], V[16 * LD];
-    __shared__ double prm[8][4];  // c, s, e of every pair of the round
-    const int64_t b = blockIdx.x;
-    const int lane = threadIdx.x;
-    const int I = lane >> 3, J = lane & 7;
-    const int np = n + (n & 1), half = np / 2;
-    const bool act = I < half && J < half;
-    const cd* Ag = Aall + b * (int64_t)n * n;
-    for (int i = lane; i < n * n; i += 64) {
-        const int r = i / n, c = i - r * n;
-        A[r * LD + c] = Ag[i];
-        V[r * LD + c] = cd{r == c ? 1.0 : 0.0, 0.0};
+struct JacobiRot {
+    double c, sx, sy;  // c and s e^{i phi}; (1, 0, 0) for a pair left alone
+};
+
+// 1 / sqrt(x) for x > 0: the hardware's estimate y (about 2^-23) and the series
+// y (1 - e)^{-1/2} = y (1 + e/2 + 3 e^2/8 + ...) in its error e = 1 - x y^2, whose next
+// term is below 2^-67
+__device__ inline double rsqrt_pos(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// a pair (f, g); `swapped`: f > g (where d == a the sign is that of the sorted pair)
+__device__ inline JacobiRot jacobi_rot(double a, double d, cd b, bool swapped, double eps2,
+                                       double skip_abs) {
+    const double bb2 = cabs2(b);
+    const double dl = d - a;
+    const double ir = rsqrt_pos(fma(dl, dl, 4.0 * bb2));
+    const double cc = fma(0.5 * fabs(dl), ir, 0.5);
+    const double ic = rsqrt_pos(cc);
+    double s = ir * ic;
+    if (dl < 0.0 || (dl == 0.0 && swapped)) s = -s;
+    // A pair is left alone once |b|^2 is at the rounding level of its own diagonal
+    // entries or of the mean squared diagonal entry, whichever is larger: with the first
+    // test alone, pairs next to a zero eigenvalue keep rotating on rounding noise and the
+    // off-diagonal norm never falls below the stopping level.
+    const bool rot = bb2 > fmax(eps2 * fabs(a * d), skip_abs) && bb2 > 0.0;
+    return rot ? JacobiRot{cc * ic, s * b.x, s * b.y} : JacobiRot{1.0, 0.0, 0.0};
+}
+
+template <int N>
+struct EigShape {
+    static constexpr int NP = N + (N & 1), H = NP / 2, L = H * H;  // lanes of a matrix
+    static constexpr int G = L <= 32 ? 64 / L : 1;                 // matrices of a work-group
+    static constexpr int NW = (L + 63) / 64;                       // waves of a work-group
+    static constexpr int LD = H <= 2 ? NP : NP + (8 - H % 8) % 8;  // = H modulo 8
+};
+
+template <int N>
+__global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd* __restrict__ Aall,
+                                                                        int64_t batch, int vt,
+                                                                        double* __restrict__ w_out,
+                                                                        cd* __restrict__ V_out) {
+    using S = EigShape<N>;
+    constexpr int NP = S::NP, H = S::H, L = S::L, G = S::G, NW = S::NW, LD = S::LD, m = NP - 1;
+    constexpr int VO = NP * LD;  // V after A
+    __shared__ cd sm[G][2 * VO];
+    __shared__ int srank[G][NP];
+    __shared__ double sred[2 * NW];
+    __shared__ double sprm[NW > 1 ? H : 1][4];
+    const int tid = threadIdx.x;
+    const int64_t b0 = (int64_t)blockIdx.x * G;
+    const int ng = batch - b0 < G ? (int)(batch - b0) : G;
+    const cd* Ag = Aall + b0 * N * N;
+    // position of index i at the start of a sweep
+    auto pos = [](int i) { return i == m ? 0 : (i == 0 ? NP - 1 : (i < H ? i : 3 * H - 2 - i)); };
+    for (int i = tid; i < G * NP * NP; i += 64 * NW) {  // (zeros in the padding)
+        const int g = i / (NP * NP), e = i - g * NP * NP, r = e / NP, c = e - r * NP;
+        const bool in = g < ng && r < N && c < N;
+        sm[g][pos(r) * LD + pos(c)] = in ? Ag[(int64_t)g * N * N + r * N + c] : cd{0.0, 0.0};
+        sm[g][VO + r * LD + pos(c)] = cd{r == c ? 1.0 : 0.0, 0.0};
     }
-    __syncthreads();
+    eig_sync<NW>();
+    const int g = G > 1 ? tid / L : 0;
+    const int l = tid - g * L;
+    const bool act = G > 1 ? g < ng : l < L;
+    const int base = g * L;  // first lane of the matrix (G > 1 or one wave)
+    const int I = act ? l / H : 0, J = act ? l - I * H : 0;
+    cd* const A = sm[act ? g : 0];
+    // slots f_k, g_k and where their contents go
+    auto pf = [](int k) { return k; };
+    auto pg = [](int k) { return H + (k + H - 1) % H; };
+    auto nf = [&](int k) { return k == 0 ? pf(0) : (k == 1 ? pg(0) : pf(k - 1)); };
+    auto ng_ = [&](int k) { return k == H - 1 ? (H == 1 ? pg(0) : pf(H - 1)) : pg(k + 1); };
+    const cd* const r00 = A + pf(I) * LD + pf(J);
+    const cd* const r01 = A + pf(I) * LD + pg(J);
+    const cd* const r10 = A + pg(I) * LD + pf(J);
+    const cd* const r11 = A + pg(I) * LD + pg(J);
+    cd* const w00 = A + nf(I) * LD + nf(J);
+    cd* const w01 = A + nf(I) * LD + ng_(J);
+    cd* const w10 = A + ng_(I) * LD + nf(J);
+    cd* const w11 = A + ng_(I) * LD + ng_(J);
+    // V's rows f_I and g_I (V's rows never move: any pairing of them will do)
+    cd* const v00 = A + VO + pf(I) * LD + nf(J);
+    cd* const v01 = A + VO + pf(I) * LD + ng_(J);
+    cd* const v10 = A + VO + pg(I) * LD + nf(J);
+    cd* const v11 = A + VO + pg(I) * LD + ng_(J);
     const double eps2 = 4.9e-32;  // (2.2e-16)^2
-    for (int sweep = 0; sweep < 40 && n > 1; ++sweep) {
-        double off = 0.0, dia = 0.0;
-        for (int i = lane; i < n * n; i += 64) {
-            const int r = i / n, c = i - r * n;
-            const double v = cabs2(A[r * LD + c]);
-            if (r == c)
-                dia += v;
-            else
-                off += v;
+    bool done = !act || N == 1;
+    for (int sweep = 0; sweep < 40; ++sweep) {
+        double off = 0.0, dia = 0.0, big = 0.0;  // big: the largest squared off-diagonal
+        if (act) {
+            const double a00 = cabs2(*r00), a01 = cabs2(*r01), a10 = cabs2(*r10), a11 = cabs2(*r11);
+            off = a01 + a10 + (I == J ? 0.0 : a00 + a11);
+            dia = I == J ? a00 + a11 : 0.0;
+            big = fmax(a01, a10);
+            if (I != J) big = fmax(big, fmax(a00, a11));
         }
-        off = wave_sum(off);
-        dia = wave_sum(dia);
-        if (!(off > 1e-32 * dia)) break;
-        const double skip_abs = eps2 * dia / n;
-        int rotated = 0;
-        for (int round = 0; round < np - 1; ++round) {
-            if (lane < half) {
-                int p, q;
-                rr_pair(lane, round, np, p, q);
-                double c = 1.0, s = 0.0;
-                cd e = {1.0, 0.0};
-                if (q < n) {
-                    const double a = A[p * LD + p].x, d = A[q * LD + q].x;
-                    const cd bpq = A[p * LD + q];
-                    const double bb2 = cabs2(bpq);
-                    if (bb2 > fmax(eps2 * fabs(a * d), skip_abs) && bb2 > 0.0) {
-                        rotated = 1;
-                        // (one reciprocal square root for 1/|b|, one for c: two
-                        // divisions and a square root fewer on the round's critical path)
-                        const double ib = rsqrt(bb2);
-                        const double tau = (d - a) * (0.5 * ib);
-                        const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(fma(tau, tau, 1.0)));
-                        c = rsqrt(fma(t, t, 1.0));
-                        s = t * c;
-                        e = cd{bpq.x * ib, bpq.y * ib};
-                    }
-                }
-                prm[lane][0] = c;
-                prm[lane][1] = s;
-                prm[lane][2] = e.x;
-                prm[lane][3] = e.y;
-            }
-            __syncthreads();
-            if (act) {
-                int pI, qI, pJ, qJ;
-                rr_pair(I, round, np, pI, qI);
-                rr_pair(J, round, np, pJ, qJ);
-                const double cI = prm[I][0], sI = prm[I][1], cJ = prm[J][0], sJ = prm[J][1];
-                const cd eI = {prm[I][2], prm[I][3]}, eJ = {prm[J][2], prm[J][3]};
-                const bool qIok = qI < n, qJok = qJ < n;
-                if (sI != 0.0 || sJ != 0.0) {
-                    const cd z = {0.0, 0.0};
-                    cd x00 = A[pI * LD + pJ];
-                    cd x01 = qJok ? A[pI * LD + qJ] : z;
-                    cd x10 = qIok ? A[qI * LD + pJ] : z;
-                    cd x11 = qIok && qJok ? A[qI * LD + qJ] : z;
-                    if (sI != 0.0) {  // rows: A'_p = c A_p - s e A_q ; A'_q = s conj(e) A_p + c A_q
-                        const cd e0 = cmul(eI, x10), e1 = cmul(eI, x11);
-                        const cd f0 = cmulc(eI, x00), f1 = cmulc(eI, x01);
-                        x00 = cd{cI * x00.x - sI * e0.x, cI * x00.y - sI * e0.y};
-                        x01 = cd{cI * x01.x - sI * e1.x, cI * x01.y - sI * e1.y};
-                        x10 = cd{sI * f0.x + cI * x10.x, sI * f0.y + cI * x10.y};
-                        x11 = cd{sI * f1.x + cI * x11.x, sI * f1.y + cI * x11.y};
-                    }
-                    if (sJ != 0.0) {  // columns: A'_ip = c A_ip - s conj(e) A_iq ; A'_iq = s e A_ip + c A_iq
-                        const cd e0 = cmulc(eJ, x01), e1 = cmulc(eJ, x11);
-                        const cd f0 = cmul(eJ, x00), f1 = cmul(eJ, x10);
-                        x00 = cd{cJ * x00.x - sJ * e0.x, cJ * x00.y - sJ * e0.y};
-                        x10 = cd{cJ * x10.x - sJ * e1.x, cJ * x10.y - sJ * e1.y};
-                        x01 = cd{sJ * f0.x + cJ * x01.x, sJ * f0.y + cJ * x01.y};
-                        x11 = cd{sJ * f1.x + cJ * x11.x, sJ * f1.y + cJ * x11.y};
-                    }
-                    if (I == J && sI != 0.0) {  // the rotated pair: exact zero off the diagonal
-                        x01 = z;
-                        x10 = z;
-                        x00.y = 0.0;
-                        x11.y = 0.0;
-                    }
-                    A[pI * LD + pJ] = x00;
-                    if (qJok) A[pI * LD + qJ] = x01;
-                    if (qIok) A[qI * LD + pJ] = x10;
-                    if (qIok && qJok) A[qI * LD + qJ] = x11;
-                }
-                if (sJ != 0.0) {  // V columns p_J, q_J on rows 2I, 2I + 1
+        if constexpr (G > 1) {
+            double o = 0.0, d = 0.0;
+            const int bl = act ? base : 0;
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int r = 2 * I + h;
-                        if (r < n) {
-                            const cd vp = V[r * LD + pJ];
-                            const cd vq = qJok ? V[r * LD + qJ] : cd{0.0, 0.0};
-                            const cd eq = cmulc(eJ, vq), ep = cmul(eJ, vp);
-                            V[r * LD + pJ] = cd{cJ * vp.x - sJ * eq.x, cJ * vp.y - sJ * eq.y};
-                            if (qJok) V[r * LD + qJ] = cd{sJ * ep.x + cJ * vq.x, sJ * ep.y + cJ * vq.y};
-                        }
-                    }
+            for (int t = 0; t < L; ++t) {
+                o += __shfl(off, bl + t, 64);
+                d += __shfl(dia, bl + t, 64);
+            }
+            off = o;
+            dia = d;
+        } else {
+            off = wave_sum(off);
+            dia = wave_sum(dia);
+            if constexpr (NW > 1) {
+                if ((tid & 63) == 0) {
+                    sred[tid >> 6] = off;
+                    sred[NW + (tid >> 6)] = dia;
+                }
+                __syncthreads();
+                off = dia = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    off += sred[w];
+                    dia += sred[NW + w];
                 }
             }
-            __syncthreads();
         }
-        if (!__any(rotated)) break;  // a sweep with no rotation leaves A unchanged
+        const double skip_abs = eps2 * dia / N;
+        // converged, or a sweep in which every pair would be left alone
+        const bool more = off > 1e-32 * dia && big > skip_abs;
+        if constexpr (NW > 1) {
+            if (!__syncthreads_or(more)) break;
+        } else if constexpr (G > 1) {
+            const uint64_t mine = ((1ull << L) - 1ull) << base;
+            done = done || !(__ballot(more) & mine);
+            if (__all(done)) break;
+        } else {
+            if (!__any(more)) break;
+        }
+        // (a finished matrix sharing the wave rotates no more)
+        const double skip = done ? __builtin_huge_val() : skip_abs;
+        bool rotated = false;
+        int fi = I == 0 ? m : I, gi = I == 0 ? 0 : m - I;  // the indices in slots f_I and g_I
+        for (int round = 0; round < m; ++round) {
+            cd x00 = *r00, x01 = *r01, x10 = *r10, x11 = *r11;
+            const cd vf0 = r00[VO], vg0 = r01[VO], vf1 = r10[VO], vg1 = r11[VO];
+            // in lane (I, I) the block is the pair's own
+            const JacobiRot rd = jacobi_rot(x00.x, x11.x, x01, fi > gi, eps2, skip);
+            JacobiRot ri, rj;
+            if constexpr (NW == 1) {
+                const int si = base + I * (H + 1), sj = base + J * (H + 1);
+                ri = JacobiRot{__shfl(rd.c, si, 64), __shfl(rd.sx, si, 64), __shfl(rd.sy, si, 64)};
+                rj = JacobiRot{__shfl(rd.c, sj, 64), __shfl(rd.sx, sj, 64), __shfl(rd.sy, sj, 64)};
+            } else {
+                if (act && I == J) {
+                    sprm[I][0] = rd.c;
+                    sprm[I][1] = rd.sx;
+                    sprm[I][2] = rd.sy;
+                }
+                __syncthreads();  // (and every block has been read)
+                ri = JacobiRot{sprm[I][0], sprm[I][1], sprm[I][2]};
+                rj = JacobiRot{sprm[J][0], sprm[J][1], sprm[J][2]};
+            }
+            const bool any = ri.sx != 0.0 || ri.sy != 0.0;
+            rotated = rotated || any;
+            // rows: A'_f = c A_f - s e A_g ; A'_g = s conj(e) A_f + c A_g
+            auto rot_f = [](double c, double sx, double sy, cd u, cd w) {  // c u - s w
+                return cd{fma(c, u.x, fma(sy, w.y, -sx * w.x)), fma(c, u.y, -fma(sx, w.y, sy * w.x))};
+            };
+            auto rot_g = [](double c, double sx, double sy, cd u, cd w) {  // conj(s) u + c w
+                return cd{fma(c, w.x, fma(sx, u.x, sy * u.y)), fma(c, w.y, fma(sx, u.y, -sy * u.x))};
+            };
+            const cd y00 = rot_f(ri.c, ri.sx, ri.sy, x00, x10), y01 = rot_f(ri.c, ri.sx, ri.sy, x01, x11);
+            const cd y10 = rot_g(ri.c, ri.sx, ri.sy, x00, x10), y11 = rot_g(ri.c, ri.sx, ri.sy, x01, x11);
+            // columns: A'_f = c A_f - s conj(e) A_g ; A'_g = s e A_f + c A_g ; V the same
+            x00 = rot_f(rj.c, rj.sx, -rj.sy, y00, y01);
+            x01 = rot_g(rj.c, rj.sx, -rj.sy, y00, y01);
+            x10 = rot_f(rj.c, rj.sx, -rj.sy, y10, y11);
+            x11 = rot_g(rj.c, rj.sx, -rj.sy, y10, y11);
+            if (I == J && any) {  // the rotated pair: exact zero off the diagonal
+                x01 = x10 = cd{0.0, 0.0};
+                x00.y = x11.y = 0.0;
+            }
+            const cd z00 = rot_f(rj.c, rj.sx, -rj.sy, vf0, vg0), z01 = rot_g(rj.c, rj.sx, -rj.sy, vf0, vg0);
+            const cd z10 = rot_f(rj.c, rj.sx, -rj.sy, vf1, vg1), z11 = rot_g(rj.c, rj.sx, -rj.sy, vf1, vg1);
+            if constexpr (NW == 1) eig_sync<1>();  // (reads before writes)
+            if (act) {
+                *w00 = x00;
+                *w01 = x01;
+                *w10 = x10;
+                *w11 = x11;
+                *v00 = z00;
+                *v01 = z01;
+                *v10 = z10;
+                *v11 = z11;
+            }
+            eig_sync<NW>();
+            // the next round's pairs
+            if (I > 0 && ++fi == m) fi = 0;
+            if (++gi == m) gi = 0;
+        }
+        // a sweep with no rotation leaves the matrix unchanged
+        if constexpr (NW > 1) {
+            if (!__syncthreads_or(rotated)) break;
+        } else if constexpr (G > 1) {
+            const uint64_t mine = ((1ull << L) - 1ull) << base;
+            done = done || !(__ballot(rotated) & mine);
+        } else {
+            if (!__any(rotated)) break;
+        }
     }
     // ascending order, ties by index
-    for (int i = lane; i < n; i += 64) {
-        const double wi = A[i * LD + i].x;
-        int rank = 0;
-        for (int j = 0; j < n; ++j) {
-            const double wj = A[j * LD + j].x;
-            rank += (wj < wi) || (wj == wi && j < i);
+    if (act) {
+        for (int i = l; i < N; i += L) {
+            const double wi = A[pos(i) * (LD + 1)].x;
+            int rank = 0;
+            for (int j = 0; j < N; ++j) {
+                const double wj = A[pos(j) * (LD + 1)].x;
+                rank += (wj < wi) || (wj == wi && j < i);
+            }
+            srank[g][i] = rank;
+            w_out[(b0 + g) * N + rank] = wi;
         }
-        w_out[b * n + rank] = wi;
-        cd* Vg = V_out + b * (int64_t)n * n;
-        for (int r = 0; r < n; ++r) Vg[r * n + rank] = V[r * LD + i];
+    }
+    eig_sync<NW>();
+    cd* Vg = V_out + b0 * N * N;
+    for (int i = tid; i < ng * N * N; i += 64 * NW) {
+        const int q = i / (N * N), e = i - q * N * N, r = e / N, c = e - r * N;
+        const int rank = srank[q][c];
+        Vg[(int64_t)q * N * N + (vt ? rank * N + r : r * N + rank)] = sm[q][VO + r * LD + pos(c)];
     }
 }
 
-hipError_t launch_eig_herm(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s) {
-    if (batch <= 0) return hipSuccess;
-    const int h = n / 2 + 1;
-    const size_t shm = (size_t)2 * n * (n + 1) * sizeof(cd) + 2 * h * sizeof(double) +
-                       h * sizeof(cd) + 2 * h * sizeof(int);
-    for (int64_t b0 = 0; b0 < batch; b0 += 2000000000LL) {
-        const int64_t nb = batch - b0 < 2000000000LL ? batch - b0 : 2000000000LL;
-        cd* Ab = A + b0 * n * n;
-        double* wb = w + b0 * n;
-        cd* Vb = V + b0 * n * n;
-        switch (n) {
-#define PHX_EIG(NV)                                                                             \
-    case NV:                                                                                    \
-        hipLaunchKernelGGL(eig_herm_kernel<NV>, dim3((unsigned)nb), dim3(64), shm, s, Ab, n, wb, \
-                           Vb);                                                                 \
-        break;
-#define PHX_EIGB(NV)                                                                            \
-    case NV:                                                                                    \
-        hipLaunchKernelGGL(eig_herm_blk_kernel<NV>, dim3((unsigned)nb), dim3(64), 0, s, Ab, n,  \
-                           wb, Vb);                                                             \
-        break;
-            PHX_EIGB(3) PHX_EIGB(4) PHX_EIGB(5) PHX_EIGB(6) PHX_EIGB(7) PHX_EIGB(8) PHX_EIGB(9)
-            PHX_EIGB(10) PHX_EIGB(12) PHX_EIGB(14) PHX_EIGB(15) PHX_EIGB(16)
-            PHX_EIG(18) PHX_EIG(20) PHX_EIG(21) PHX_EIG(24) PHX_EIG(27) PHX_EIG(30)
-            case 1: case 2: case 11: case 13:
-                hipLaunchKernelGGL(eig_herm_blk_kernel<0>, dim3((unsigned)nb), dim3(64), 0, s, Ab,
-                                   n, wb, Vb);
-                break;
-#undef PHX_EIG
-#undef PHX_EIGB
-            default:
-                hipLaunchKernelGGL(eig_herm_kernel<0>, dim3((unsigned)nb), dim3(64), shm, s, Ab, n,
-                                   wb, Vb);
-        }
+template <int N>
+static hipError_t go_eig(const cd* A, int64_t batch, bool vt, double* w, cd* V, hipStream_t s) {
+    constexpr int G = EigShape<N>::G;
+    const int64_t chunk = 1000000000LL / G * G;
+    for (int64_t b = 0; b < batch; b += chunk) {
+        const int64_t nb = batch - b < chunk ? batch - b : chunk;
+        hipLaunchKernelGGL(eig_herm_kernel<N>, dim3((unsigned)((nb + G - 1) / G)),
+                           dim3(64 * EigShape<N>::NW), 0, s, A + b * N * N, nb, vt ? 1 : 0, w + b * N,
+                           V + b * N * N);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, bool vt,
+                           hipStream_t s) {
+    if (batch <= 0) return hipSuccess;
+    switch (n) {
+#define PHX_EIG(NV) \
+    case NV: return go_eig<NV>(A, batch, vt, w, V, s);
+        PHX_EIG(1) PHX_EIG(2) PHX_EIG(3) PHX_EIG(4) PHX_EIG(5) PHX_EIG(6) PHX_EIG(7) PHX_EIG(8)
+        PHX_EIG(9) PHX_EIG(10) PHX_EIG(11) PHX_EIG(12) PHX_EIG(13) PHX_EIG(14) PHX_EIG(15)
+        PHX_EIG(16) PHX_EIG(17) PHX_EIG(18) PHX_EIG(19) PHX_EIG(20) PHX_EIG(21) PHX_EIG(22)
+        PHX_EIG(23) PHX_EIG(24) PHX_EIG(25) PHX_EIG(26) PHX_EIG(27) PHX_EIG(28) PHX_EIG(29)
+        PHX_EIG(30) PHX_EIG(31) PHX_EIG(32)
+#undef PHX_EIG
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -80,3 +80,27 @@ def test_degenerate_spectrum(lib):
     torch.cuda.synchronize()
     ref = np.sort([0.5, -1.0, 0.5, 2.0, -1.0, 0.5])
     assert np.max(np.abs(eps.cpu().numpy() - ref[None])) < 1e-15
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 7, 8, 9, 10, 11, 13, 16, 17, 19, 22, 23, 27, 31, 32])
+def test_eigensolver_orders(lib, n):
+    """Every layout of the eigensolver: matrices per wave (64 at order 1 down to one), waves per
+    matrix, odd orders, a ragged last work-group, and equal diagonal entries (the sign of
+    the first rotations)."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(70, n_wannier=n, n_atoms=1, r=1)
+    s.h_r[13] -= np.diag(np.diag(s.h_r[13])) - 0.25 * np.eye(n)
+    ds = DeviceSystem.from_host(s, with_coupling=False)
+    k = np.random.default_rng(n).uniform(-1, 1, size=(67, 3))
+    eps = torch.empty((67, n), dtype=torch.float64, device="cuda")
+    U = torch.empty((67, n, n), dtype=torch.complex128, device="cuda")
+    lib.electron_bands(ds, torch.from_numpy(k).cuda(), eps, U)
+    torch.cuda.synchronize()
+    eps, U = eps.cpu().numpy(), U.cpu().numpy()
+    H = bands.hamiltonian_k(k, s.rh, s.h_r)
+    ref = np.linalg.eigvalsh(H)
+    scale = np.max(np.abs(ref))
+    assert np.max(np.abs(eps - ref)) < 1e-13 * scale
+    assert np.max(np.abs(H @ U - U * eps[:, None, :])) < 1e-13 * scale
+    assert np.max(np.abs(np.conj(np.swapaxes(U, 1, 2)) @ U - np.eye(n))) < 1e-13
