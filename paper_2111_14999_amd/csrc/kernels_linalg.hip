@@ -213,6 +213,14 @@ static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* 
     if (K <= 0) return hipErrorInvalidValue;
     auto go = [&](auto kernel, int tm, int tn) {
         dim3 grid((unsigned)((N + 64 * tn - 1) / (64 * tn)), (unsigned)((M + 16 * tm - 1) / (16 * tm)));
+        // A real B of few rows (dynamical matrices, 27 vectors) gains nothing from a split
+        // and keeps the order of its sum (see EigShape::SORTED); one tile a wave instead.
+        if (sizeof(BT) == 8 && K <= 64 && (int64_t)grid.x * grid.y < 1024 && M <= 16 * 65535) {
+            grid = dim3((unsigned)((N + 63) / 64), (unsigned)((M + 15) / 16));
+            hipLaunchKernelGGL((zgemm_kernel<1, 1, 4, BT>), grid, dim3(256), 0, s, A, lda, B, ldb, C,
+                               ldc, M, N, K);
+            return hipGetLastError();
+        }
         // Under four work-groups (one wave per SIMD each) per CU the tiles wait on their
         // loads: 13,824 points x 256 x 343, 864 work-groups, 243 us against 187 us with K
         // split; 301 points, 20 work-groups, 47 against 12 us.  (Also rows too long for
@@ -348,11 +356,38 @@ __device__ inline JacobiRot jacobi_rot(double a, double d, cd b, bool swapped, d
     return rot ? JacobiRot{cc * ic, s * b.x, s * b.y} : JacobiRot{1.0, 0.0, 0.0};
 }
 
+// The rotation of a sorted pair p < q in the form c, s = t c, e = e^{i phi} with
+// t = sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (A_qq - A_pp) / (2 |A_pq|)
+struct SortedRot {
+    double c, s;
+    cd e;
+};
+__device__ inline SortedRot sorted_rot(double a, double d, cd bpq, double eps2, double skip_abs) {
+    const double bb2 = cabs2(bpq);
+    if (!(bb2 > fmax(eps2 * fabs(a * d), skip_abs) && bb2 > 0.0)) return SortedRot{1.0, 0.0, {1.0, 0.0}};
+    const double ib = rsqrt(bb2);
+    const double tau = (d - a) * (0.5 * ib);
+    const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(fma(tau, tau, 1.0)));
+    const double c = rsqrt(fma(t, t, 1.0));
+    return SortedRot{c, t * c, cd{bpq.x * ib, bpq.y * ib}};
+}
+__device__ inline void swap_if(bool sw, cd& a, cd& b) {
+    // (by value: selecting between the two lvalues would put both in scratch memory)
+    const double ax = a.x, ay = a.y, bx = b.x, by = b.y;
+    a = cd{sw ? bx : ax, sw ? by : ay};
+    b = cd{sw ? ax : bx, sw ? ay : by};
+}
+
 template <int N>
 struct EigShape {
     static constexpr int NP = N + (N & 1), H = NP / 2, L = H * H;  // lanes of a matrix
     static constexpr int G = L <= 32 ? 64 / L : 1;                 // matrices of a work-group
     static constexpr int NW = (L + 63) / 64;                       // waves of a work-group
+    // Where pivots are equal by the crystal's structure (CsCl: order 6), the direction of
+    // a rotation, and with it the phases of the eigenvectors, hangs on the last bit.
+    // Orders up to 8, which have the cycles to spare, therefore rotate each pair in
+    // index order, operation for operation as before.
+    static constexpr bool SORTED = N <= 8;
     static constexpr int LD = H <= 2 ? NP : NP + (8 - H % 8) % 8;  // = H modulo 8
 };
 
@@ -459,9 +494,63 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
         const double skip = done ? __builtin_huge_val() : skip_abs;
         bool rotated = false;
         int fi = I == 0 ? m : I, gi = I == 0 ? 0 : m - I;  // the indices in slots f_I and g_I
+        int fj = J == 0 ? m : J, gj = J == 0 ? 0 : m - J;
         for (int round = 0; round < m; ++round) {
             cd x00 = *r00, x01 = *r01, x10 = *r10, x11 = *r11;
-            const cd vf0 = r00[VO], vg0 = r01[VO], vf1 = r10[VO], vg1 = r11[VO];
+            cd vf0 = r00[VO], vg0 = r01[VO], vf1 = r10[VO], vg1 = r11[VO];
+            cd z00, z01, z10, z11;
+            if constexpr (S::SORTED) {
+                const bool swi = fi > gi, swj = fj > gj;
+                swap_if(swi, x00, x10);
+                swap_if(swi, x01, x11);
+                swap_if(swj, x00, x01);
+                swap_if(swj, x10, x11);
+                swap_if(swj, vf0, vg0);
+                swap_if(swj, vf1, vg1);
+                const SortedRot rd = sorted_rot(x00.x, x11.x, x01, eps2, skip);
+                const int si = base + I * (H + 1), sj = base + J * (H + 1);
+                const double cI = __shfl(rd.c, si, 64), sI = __shfl(rd.s, si, 64);
+                const double cJ = __shfl(rd.c, sj, 64), sJ = __shfl(rd.s, sj, 64);
+                const cd eI = {__shfl(rd.e.x, si, 64), __shfl(rd.e.y, si, 64)};
+                const cd eJ = {__shfl(rd.e.x, sj, 64), __shfl(rd.e.y, sj, 64)};
+                rotated = rotated || sI != 0.0;
+                if (sI != 0.0) {
+                    const cd e0 = cmul(eI, x10), e1 = cmul(eI, x11);
+                    const cd f0 = cmulc(eI, x00), f1 = cmulc(eI, x01);
+                    x00 = cd{cI * x00.x - sI * e0.x, cI * x00.y - sI * e0.y};
+                    x01 = cd{cI * x01.x - sI * e1.x, cI * x01.y - sI * e1.y};
+                    x10 = cd{sI * f0.x + cI * x10.x, sI * f0.y + cI * x10.y};
+                    x11 = cd{sI * f1.x + cI * x11.x, sI * f1.y + cI * x11.y};
+                }
+                z00 = vf0;
+                z01 = vg0;
+                z10 = vf1;
+                z11 = vg1;
+                if (sJ != 0.0) {
+                    const cd e0 = cmulc(eJ, x01), e1 = cmulc(eJ, x11);
+                    const cd f0 = cmul(eJ, x00), f1 = cmul(eJ, x10);
+                    x00 = cd{cJ * x00.x - sJ * e0.x, cJ * x00.y - sJ * e0.y};
+                    x10 = cd{cJ * x10.x - sJ * e1.x, cJ * x10.y - sJ * e1.y};
+                    x01 = cd{sJ * f0.x + cJ * x01.x, sJ * f0.y + cJ * x01.y};
+                    x11 = cd{sJ * f1.x + cJ * x11.x, sJ * f1.y + cJ * x11.y};
+                    const cd q0 = cmulc(eJ, vg0), p0 = cmul(eJ, vf0);
+                    const cd q1 = cmulc(eJ, vg1), p1 = cmul(eJ, vf1);
+                    z00 = cd{cJ * vf0.x - sJ * q0.x, cJ * vf0.y - sJ * q0.y};
+                    z01 = cd{sJ * p0.x + cJ * vg0.x, sJ * p0.y + cJ * vg0.y};
+                    z10 = cd{cJ * vf1.x - sJ * q1.x, cJ * vf1.y - sJ * q1.y};
+                    z11 = cd{sJ * p1.x + cJ * vg1.x, sJ * p1.y + cJ * vg1.y};
+                }
+                if (I == J && sI != 0.0) {  // the rotated pair: exact zero off the diagonal
+                    x01 = x10 = cd{0.0, 0.0};
+                    x00.y = x11.y = 0.0;
+                }
+                swap_if(swj, x00, x01);
+                swap_if(swj, x10, x11);
+                swap_if(swi, x00, x10);
+                swap_if(swi, x01, x11);
+                swap_if(swj, z00, z01);
+                swap_if(swj, z10, z11);
+            } else {
             // in lane (I, I) the block is the pair's own
             const JacobiRot rd = jacobi_rot(x00.x, x11.x, x01, fi > gi, eps2, skip);
             JacobiRot ri, rj;
@@ -486,7 +575,7 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
                 return cd{fma(c, u.x, fma(sy, w.y, -sx * w.x)), fma(c, u.y, -fma(sx, w.y, sy * w.x))};
             };
             auto rot_g = [](double c, double sx, double sy, cd u, cd w) {  // conj(s) u + c w
-                return cd{fma(c, w.x, fma(sx, u.x, sy * u.y)), fma(c, w.y, fma(sx, u.y, -sy * u.x))};
+                return cd{fma(c, w.x, fma(sy, u.y, sx * u.x)), fma(c, w.y, fma(sx, u.y, -sy * u.x))};
             };
             const cd y00 = rot_f(ri.c, ri.sx, ri.sy, x00, x10), y01 = rot_f(ri.c, ri.sx, ri.sy, x01, x11);
             const cd y10 = rot_g(ri.c, ri.sx, ri.sy, x00, x10), y11 = rot_g(ri.c, ri.sx, ri.sy, x01, x11);
@@ -499,8 +588,11 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
                 x01 = x10 = cd{0.0, 0.0};
                 x00.y = x11.y = 0.0;
             }
-            const cd z00 = rot_f(rj.c, rj.sx, -rj.sy, vf0, vg0), z01 = rot_g(rj.c, rj.sx, -rj.sy, vf0, vg0);
-            const cd z10 = rot_f(rj.c, rj.sx, -rj.sy, vf1, vg1), z11 = rot_g(rj.c, rj.sx, -rj.sy, vf1, vg1);
+            z00 = rot_f(rj.c, rj.sx, -rj.sy, vf0, vg0);
+            z01 = rot_g(rj.c, rj.sx, -rj.sy, vf0, vg0);
+            z10 = rot_f(rj.c, rj.sx, -rj.sy, vf1, vg1);
+            z11 = rot_g(rj.c, rj.sx, -rj.sy, vf1, vg1);
+            }
             if constexpr (NW == 1) eig_sync<1>();  // (reads before writes)
             if (act) {
                 *w00 = x00;
@@ -516,6 +608,10 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
             // the next round's pairs
             if (I > 0 && ++fi == m) fi = 0;
             if (++gi == m) gi = 0;
+            if constexpr (S::SORTED) {
+                if (J > 0 && ++fj == m) fj = 0;
+                if (++gj == m) gj = 0;
+            }
         }
         // a sweep with no rotation leaves the matrix unchanged
         if constexpr (NW > 1) {
