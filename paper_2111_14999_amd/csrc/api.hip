@@ -498,6 +498,61 @@ phoebe_status phoebe_gpu_interp_g_mesh(void* handle, const phoebe_system* sys,
 
 }  // extern "C"
 
+// Lists of one batch for launch_re_reg, appended to rbh with their offsets in rbo:
+// (chunks, -, offsets of pair_k1, ent, chunks).  kmesh: the rows' mesh indices;
+// row_end[i]: states before row i; prs: the distinct (k0, k1) = k0 n1 + k1, ascending.  A
+// chunk holds pairs of one k0 and at most the kernel's numbers of pairs and k; a pair
+// with more k continues in the next chunk.
+static void append_reg_batch(const int32_t* kmesh, int rows, const int32_t* row_end,
+                             const std::vector<int32_t>& prs, const Mesh& mesh, int rmax_e,
+                             std::vector<int32_t>& rbh, std::vector<std::array<int64_t, 11>>& rbo) {
+    int max_pairs = 0, max_ks = 0;
+    re_reg_limits(rmax_e, &max_pairs, &max_ks);
+    const int np = (int)prs.size();
+    std::vector<int32_t> row_pair(rows), off(np + 1, 0), order(rows);
+    for (int i = 0, last = -1; i < rows; ++i) {
+        const int32_t pr = kmesh[i] / mesh.n2;
+        if (last < 0 || prs[last] != pr)
+            last = (int)(std::lower_bound(prs.begin(), prs.end(), pr) - prs.begin());
+        row_pair[i] = last;
+        ++off[last + 1];
+    }
+    for (int p = 0; p < np; ++p) off[p + 1] += off[p];
+    {
+        std::vector<int32_t> at(off.begin(), off.end() - 1);
+        for (int i = 0; i < rows; ++i) order[at[row_pair[i]]++] = i;
+    }
+    std::vector<int32_t> chunks, ent;
+    int32_t* cur = nullptr;  // chunk being filled: k0, first pair, pairs, first entry, entries
+    for (int p = 0; p < np; ++p)
+        for (int i = off[p]; i < off[p + 1];) {
+            const int32_t k0 = prs[p] / mesh.n1;
+            if (!cur || cur[0] != k0 || cur[4] == max_ks || (p - cur[1] == max_pairs)) {
+                const int32_t c[8] = {k0, p, 0, i, 0, 0, 0, 0};
+                chunks.insert(chunks.end(), c, c + 8);
+                cur = chunks.data() + chunks.size() - 8;
+            }
+            cur[2] = p - cur[1] + 1;
+            for (; i < off[p + 1] && cur[4] < max_ks; ++i, ++cur[4]) {
+                const int32_t row = order[i];
+                ent.insert(ent.end(), {row_end[row] - row_end[0], row_end[row + 1] - row_end[0],
+                                       (p - cur[1]) | (kmesh[row] % mesh.n2) << 8, row});
+            }
+        }
+    ent.insert(ent.end(), 12, 0);  // read ahead of, never used
+    std::array<int64_t, 11> o{};
+    o[0] = (int64_t)chunks.size() / 8;
+    o[2] = (int64_t)rbh.size();
+    for (int32_t pr : prs) rbh.push_back(pr % mesh.n1);
+    rbh.insert(rbh.end(), 8, 0);  // (read ahead of, as the entries)
+    while (rbh.size() % 4) rbh.push_back(0);
+    o[3] = (int64_t)rbh.size();
+    rbh.insert(rbh.end(), ent.begin(), ent.end());
+    o[4] = (int64_t)rbh.size();
+    rbh.insert(rbh.end(), chunks.begin(), chunks.end());
+    rbo.push_back(o);
+}
+
 // Rate path; with `terms` (FP64, full q mesh only) it also writes each kept
 // state's per-(q, mode) terms and the state list.
 static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
@@ -632,12 +687,17 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                              re_axes_lds(rmax_e, lowp) <= 160 * 1024 &&
                              (h->mesh_sum == PHOEBE_MESH_SUM_FACTORED || 2 * We <= n_re);
         constexpr int kD0Max = 8, kD01Max = 256;
+        // boxes up to 7 wide: the whole sum in one pass over g, with no T0
+        const bool re_reg = re_fact && re_reg_supported(rmax_e, NC2);
         // nW = 16: the pair and k steps of stage 1 apply the U_k fold themselves and
         // write F; G (nW times larger) never reaches HBM
         const bool fold_fused = re_fact && nW == 16 && cw == 16;
         int BK = re_fact ? 256 : 64;
+        // G and F of a batch: 8 GB each, or a sixteenth of the workspace budget (a pass of
+        // re_reg reads g once per batch, so its batches are as large as F allows)
+        const double gf_cap = re_reg && !h->fixed_ws ? std::min(8e9, (double)h->budget / 16) : 8e9;
         while (BK > 16 && ((double)BK * NC2 * g_elem > 8e9 ||
-                           (double)BK * nW * rp_pad * nc_pad * f_elem > 8e9))
+                           (double)BK * nW * rp_pad * nc_pad * f_elem > gf_cap))
             BK /= 2;
         const int BQ = 16 * tq;
         // states per factorised sub-batch: T1 + T2 of a sub-batch stay under 16 GB or a
@@ -687,7 +747,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             cd *U, *E;
             uint8_t* mask;
             int32_t *flag, *kept, *cnt, *rowflag, *ids;
-            int32_t *st_row, *st_band, *st_kmesh, *st_mlo, *st_mhi;
+            int32_t *st_row, *st_band, *st_kmesh, *st_mlo, *st_mhi, *st_urow;
             int32_t *box_rp, *box_re;
             cd *Pax, *Pre;
             cd* Lpol;            // polar factor [N, nm]
@@ -723,6 +783,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             T.st_kmesh = ar.take<int32_t>((size_t)rows_cap * nW);
             T.st_mlo = ar.take<int32_t>((size_t)rows_cap * nW);
             T.st_mhi = ar.take<int32_t>((size_t)rows_cap * nW);
+            T.st_urow = ar.take<int32_t>((size_t)rows_cap * nW);
             if (factored) {
                 T.box_rp = ar.take<int32_t>((size_t)Wbox * Wbox * Wbox);
                 T.Pax = ar.take<cd>((size_t)(mesh.n0 + mesh.n1 + mesh.n2) * Wbox);
@@ -775,16 +836,18 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                                                    2 * (size_t)(rows_cap * nW + rows_cap + 1) *
                                                        sizeof(uint32_t) + 512
                                              : 0) +
-                                   (re_fact ? (size_t)rows_cap * 176 * sizeof(int32_t) + 1024
+                                   (re_fact ? (size_t)rows_cap * (re_reg ? 40 : 176) * sizeof(int32_t) +
+                                                  1024
                                             : 0) +
+                                   (re_reg && fold_fused ? (size_t)(rows_cap + 4) * 256 + 512 : 0) +
                                    (lw_out ? (factored ? (size_t)nsb * NL * n0_line
                                                        : (size_t)max_states * N) *
                                                      nm * sizeof(double) + 256
                                            : 0);
         const bool all_planes =
-            re_fact && tables_end + std::max(scratch_bands, batch_bytes + planes_cap * plane_bytes) +
+            re_fact && !re_reg && tables_end + std::max(scratch_bands, batch_bytes + planes_cap * plane_bytes) +
                                256 <= h->budget;
-        const size_t t0_bytes = re_fact ? (all_planes ? planes_cap : kD0Max) * plane_bytes : 0;
+        const size_t t0_bytes = re_fact && !re_reg ? (all_planes ? planes_cap : kD0Max) * plane_bytes : 0;
         ensure_ws(h, tables_end + std::max(scratch_bands, batch_bytes + t0_bytes) + 256);
         Arena ar(h->ws, h->ws_cap);
         plan_tables(ar);
@@ -823,7 +886,10 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 }
                 HIPCHK(h, hipMemcpyAsync(T.box_re, box_e.data(), sizeof(int32_t) * box_e.size(),
                                          hipMemcpyHostToDevice, s));
-                HIPCHK(h, launch_axis_phases(mesh, rmax_e, T.Pre, s));
+                if (re_reg && lowp)
+                    HIPCHK(h, launch_axis_phases_f32(mesh, rmax_e, reinterpret_cast<cf*>(T.Pre), s));
+                else
+                    HIPCHK(h, launch_axis_phases(mesh, rmax_e, T.Pre, s));
             }
             // the host vector must outlive the copy
             HIPCHK(h, hipStreamSynchronize(s));
@@ -977,7 +1043,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         }
         const double cut = 27.5 * sigma_bound;  // exp(-27.5^2) underflows to 0 in FP64
         HIPCHK(h, launch_build_states(T.ids, nst, nW, kept, T.eps, T.bmin, T.bmax, T.wmax, cut,
-                                      T.st_row, T.st_band, T.st_kmesh, T.st_mlo, T.st_mhi, s));
+                                      T.st_row, T.st_band, T.st_kmesh, T.st_mlo, T.st_mhi,
+                                      T.st_urow, s));
         if (dweights)
             HIPCHK(h, launch_delta_weights(nst, N, mesh, T.st_kmesh, T.st_band, T.st_mlo, T.st_mhi,
                                            T.eps, T.focc, T.omega, T.nb, nW, nm, par->sigma,
@@ -1003,7 +1070,9 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         // ---- phase B: batches of kept-k rows ----
         // Direct stage 1: BK rows each.  Factorised stage 1: consecutive rows
         // while the batch holds at most BK rows, kD0Max distinct k0 and kD01Max
-        // distinct (k0, k1), with the grouping lists the axis kernels use.
+        // distinct (k0, k1), with the grouping lists the axis kernels use.  The one-pass
+        // form has no such limits: BK rows of G, or with the fold as many rows as F has
+        // states for.
         std::vector<std::pair<int64_t, int64_t>> batches;
         std::vector<int32_t> rbh;          // grouping lists of every batch, one array
         std::vector<std::array<int64_t, 11>> rbo;  // per batch: d0, d01, offsets of the 8 lists
@@ -1021,16 +1090,28 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 planes.erase(std::unique(planes.begin(), planes.end()), planes.end());
             }
             int64_t r = 0;
+            // states of the rows: strow is ascending
+            std::vector<int32_t> row_end(rows + 1);
+            {
+                int32_t st = 0;
+                for (int64_t i = 0; i < rows; ++i) {
+                    while (st < nst && strow[st] <= i) ++st;
+                    row_end[i + 1] = st;
+                }
+            }
+            auto seen = [](const std::vector<int32_t>& v, int32_t x) {  // (usually the last)
+                return !v.empty() && (v.back() == x || std::find(v.begin(), v.end(), x) != v.end());
+            };
             while (r < rows) {
                 std::vector<int32_t> k0s, prs;  // distinct k0 and pair ids k0 n1 + k1
                 int64_t e = r;
-                while (e < rows && e - r < BK) {
+                while (e < rows && (fold_fused && re_reg ? row_end[e + 1] - row_end[r] <= max_states
+                                                         : e - r < BK)) {
                     const int32_t k0 = (int32_t)(kh[e] / n12);
                     const int32_t pr = (int32_t)(kh[e] / mesh.n2);
-                    const bool n0 = std::find(k0s.begin(), k0s.end(), k0) == k0s.end();
-                    const bool n01 = std::find(prs.begin(), prs.end(), pr) == prs.end();
-                    if ((!all_planes && (int)k0s.size() + n0 > kD0Max) ||
-                        (int)prs.size() + n01 > kD01Max)
+                    const bool n0 = !seen(k0s, k0), n01 = !seen(prs, pr);
+                    if (!re_reg && ((!all_planes && (int)k0s.size() + n0 > kD0Max) ||
+                                    (int)prs.size() + n01 > kD01Max))
                         break;
                     if (n0) k0s.push_back(k0);
                     if (n01) prs.push_back(pr);
@@ -1038,6 +1119,13 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 }
                 std::sort(k0s.begin(), k0s.end());
                 std::sort(prs.begin(), prs.end());
+                if (re_reg) {
+                    append_reg_batch(kh.data() + r, (int)(e - r), row_end.data() + r, prs, mesh,
+                                     rmax_e, rbh, rbo);
+                    batches.push_back({r, e - r});
+                    r = e;
+                    continue;
+                }
                 const int d0 = (int)k0s.size(), d01 = (int)prs.size();
                 const int64_t nb = e - r;
                 std::array<int64_t, 11> o{};
@@ -1088,14 +1176,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 // row_st: first state (batch-local) of every batch row, and the end
                 o[9] = (int64_t)rbh.size();
                 std::vector<int32_t> rst(nb + 1);
-                {
-                    const int64_t s0 = std::lower_bound(strow.begin(), strow.end(), (int32_t)r) -
-                                       strow.begin();
-                    for (int64_t i = r; i <= e; ++i)
-                        rst[i - r] = (int32_t)(std::lower_bound(strow.begin(), strow.end(),
-                                                                (int32_t)i) - strow.begin() - s0);
-                    rbh.insert(rbh.end(), rst.begin(), rst.end());
-                }
+                for (int64_t i = r; i <= e; ++i) rst[i - r] = row_end[i] - row_end[r];
+                rbh.insert(rbh.end(), rst.begin(), rst.end());
                 // k_ent: per entry of k_row, (k2, first state, end of states, 0), 16-byte aligned
                 while (rbh.size() % 4) rbh.push_back(0);
                 o[10] = (int64_t)rbh.size();
@@ -1114,13 +1196,16 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 rbo.push_back({(int64_t)planes.size(), 0, (int64_t)rbh.size(), 0, 0, 0, 0, 0, 0, 0, 0});
                 rbh.insert(rbh.end(), planes.begin(), planes.end());
             }
-            REQUIRE(h, rbh.size() <= (size_t)rows_cap * 176, "stage-1 grouping lists too long");
+            REQUIRE(h, rbh.size() <= (size_t)rows_cap * (re_reg ? 40 : 176),
+                    "stage-1 grouping lists too long");
         }
         int32_t* rbd = re_fact ? ar.take<int32_t>(std::max<size_t>(rbh.size(), 1)) : nullptr;
         if (re_fact)
             HIPCHK(h, hipMemcpyAsync(rbd, rbh.data(), sizeof(int32_t) * rbh.size(),
                                      hipMemcpyHostToDevice, s));
-        char* T0re = re_fact ? ar.take<char>(t0_bytes) : nullptr;
+        char* T0re = t0_bytes ? ar.take<char>(t0_bytes) : nullptr;
+        // U_k rows of a batch's k
+        cd* ue = re_reg && fold_fused ? ar.take<cd>((size_t)(rows + 4) * 16) : nullptr;
         cd* P1 = ar.take<cd>((size_t)BK * n_re);
         char* Gbuf = fold_fused ? nullptr : ar.take<char>((size_t)BK * NC2 * g_elem);
         char* Fbuf = ar.take<char>((size_t)max_states * rp_pad * nc_pad * f_elem);
@@ -1153,7 +1238,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         const double inv_sqrtpi_sigma = 1.0 / (std::sqrt(kPi) * (adaptive ? 1.0 : par->sigma));
         const double scale = 2.0 * kPi * inv_sqrtpi_sigma * (q_off ? 1.0 : 1.0 / (double)N);
         if (fold_fused)  // F's padding (rows >= n_rp, columns of no mode) is never written
-            HIPCHK(h, launch_zero_fpad(Fbuf, max_states, rp_pad, nc_pad, n_rp, 16 * nm, (int)f_elem,
+            HIPCHK(h, launch_zero_fpad(Fbuf, std::min(max_states, nst), rp_pad, nc_pad, n_rp, 16 * nm, (int)f_elem,
                                        s));
         if (all_planes) {
             // T0 of every k0 plane of the call: g(Re,Rp) read once, the planes written once
@@ -1178,17 +1263,30 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             if (ns == 0) continue;
             if (re_fact) {
                 const auto& o = rbo[bi];
+                ReRegBatch rr{(int)o[0], (int)nb, rbd + o[2], rbd + o[3], rbd + o[4], ue};
                 ReBatch rb{(int)o[0], (int)o[1], rbd + o[2], rbd + o[3], rbd + o[4],
                            rbd + o[5], rbd + o[6], rbd + o[7], all_planes ? rbd + o[8] : nullptr,
                            rbd + o[10]};
-                FoldOut fo{rbd + o[9], T.st_kmesh + sbeg, T.st_band + sbeg, T.U,
+                FoldOut fo{rbd + o[9], T.st_kmesh + sbeg, T.st_band + sbeg, T.st_urow + sbeg, T.U,
                            nW, nm, n_rp, rp_pad, nc_pad, Fbuf};
                 const FoldOut* fop = fold_fused ? &fo : nullptr;
                 // written once: G, or F when the fold is applied here
                 const double out_bytes = fold_fused ? (double)ns * n_rp * nm * nW * f_elem
                                                     : (double)nb * NC2 * g_elem;
-                Timer t1(h, s, "stage1_axes");
-                if (all_planes) {
+                // (a pass that takes every k0 plane of the call reads g once per call)
+                Timer t1(h, s, re_reg && batches.size() == 1 ? "stage1_planes" : "stage1_axes");
+                if (re_reg) {
+                    if (lowp)
+                        HIPCHK(h, launch_re_reg_f32(reinterpret_cast<const cd*>(sys->g_rr), NC2,
+                                                    T.box_re, rmax_e, mesh,
+                                                    reinterpret_cast<const cf*>(T.Pre), rr, fop,
+                                                    reinterpret_cast<cf*>(Gbuf), NC2, s));
+                    else
+                        HIPCHK(h, launch_re_reg(reinterpret_cast<const cd*>(sys->g_rr), NC2, T.box_re,
+                                                rmax_e, mesh, T.Pre, rr, fop,
+                                                reinterpret_cast<cd*>(Gbuf), NC2, s));
+                    t1.done((double)NC2 * 16.0 * n_re + out_bytes);
+                } else if (all_planes) {
                     if (lowp)
                         HIPCHK(h, launch_re_pairs_f32(reinterpret_cast<const cf*>(T0re), NC2, rmax_e,
                                                       mesh, T.Pre, rb, fop,

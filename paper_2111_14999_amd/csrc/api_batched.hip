@@ -369,7 +369,7 @@ phoebe_status phoebe_gpu_batched_plan(void* handle, const phoebe_system* systems
             if (p.states == 0) continue;
             HIPCHK(h, launch_build_states(p.ids, p.states, p.nW, p.kept, p.eps, p.bmin, p.bmax,
                                           p.wmax, 27.5 * par->sigma, p.st_row, p.st_band, p.st_kmesh,
-                                          p.st_mlo, p.st_mhi, s));
+                                          p.st_mlo, p.st_mhi, nullptr, s));
             HIPCHK(h, launch_phase_table(nullptr, p.kept, p.mesh, p.rows, p.re, p.n_re, p.P1, p.n_re, s));
             p.strow.resize(p.states);
             HIPCHK(h, hipMemcpyAsync(p.strow.data(), p.st_row, 4 * (size_t)p.states,

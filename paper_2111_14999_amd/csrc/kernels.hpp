@@ -117,6 +117,7 @@ hipError_t launch_stage2_rates(const RateArgs& a, int nst, hipStream_t s);
 
 // Per-axis phase tables P[d][n, r] = e^{i2pi (n (r - rmax) mod N_d)/N_d}, [N0+N1+N2, W].
 hipError_t launch_axis_phases(Mesh m, int rmax, cd* P, hipStream_t s);
+hipError_t launch_axis_phases_f32(Mesh m, int rmax, cf* P, hipStream_t s);  // rounded to FP32
 // T1 (axis 2) and T2 (axis 1) of the factorised full-mesh sum over Rp.
 // line_any (nullable): [nst, N1*N2]; T2 of a line whose entry is 0 is not formed.
 hipError_t launch_axis_transforms(const cd* F, int rp_pad, int nc_pad, const int32_t* box_rp,
@@ -159,10 +160,30 @@ struct FoldOut {
     const int32_t* row_st;    // [rows of the batch + 1] first state of each batch row
     const int32_t* st_kmesh;  // [states of the batch] mesh index of the state's k
     const int32_t* st_band;   // [states of the batch]
+    const int32_t* st_urow;   // [states of the batch] st_kmesh * nW + st_band (one-pass form)
     const cd* U;              // [Nk, nW, nW] eigenvectors, transposed: U[k, band, orbital]
     int nW, nm, n_rp, rp_pad, nc_pad;
     void* F;                  // cd (FP64) or cf (FP32 form)
 };
+// The whole sum in one pass, no T0 (boxes up to 7 wide); P is the phase table in the
+// working type (launch_axis_phases, _f32).  Device lists: pair_k1 [pairs + 8] of the distinct
+// (k0, k1); ent [nent + 3][4] (16-byte aligned), the k grouped by pair: first state, end of
+// its states, pair within its chunk + 256 k2, batch row; chunks [nchunk][8] k0, first pair,
+// pairs, first entry, entries, -, -, - (limits: re_reg_limits).  The entries past the
+// ends are read ahead of and hold zeros.  ue: scratch [nent + 4, 16] with a fold.
+struct ReRegBatch {
+    int nchunk, nent;
+    const int32_t *pair_k1, *ent, *chunks;
+    cd* ue;
+};
+bool re_reg_supported(int rmax, int64_t NC);
+void re_reg_limits(int rmax, int* pairs, int* ks);
+hipError_t launch_re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
+                         const cd* P, const ReRegBatch& b, const FoldOut* fo, cd* G, int64_t ldg,
+                         hipStream_t s);
+hipError_t launch_re_reg_f32(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
+                             const cf* P, const ReRegBatch& b, const FoldOut* fo, cf* G, int64_t ldg,
+                             hipStream_t s);
 hipError_t launch_re_axes(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
                           const cd* P, const ReBatch& b, const FoldOut* fo, cd* T0, cd* G,
                           int64_t ldg, hipStream_t s);
@@ -219,7 +240,7 @@ hipError_t launch_gather_rows(const uint8_t* mask, const int32_t* kept, int64_t 
 hipError_t launch_build_states(const int32_t* ids, int nst, int nW, const int32_t* kept,
                                const double* eps, const double* bmin, const double* bmax,
                                const double* wmax, double cut, int32_t* st_row, int32_t* st_band,
-                               int32_t* st_kmesh, int32_t* st_mlo, int32_t* st_mhi,
+                               int32_t* st_kmesh, int32_t* st_mlo, int32_t* st_mhi, int32_t* st_urow,
                                hipStream_t s);
 int stage2_config(int nm, int nW, int* tq_out, int* tn_out);
 

@@ -28,8 +28,10 @@ static inline int gridm(int64_t n, int block) {
     return (int)g;
 }
 
-// P[d][n, r] for the three axes, stored one after another ([N0 + N1 + N2, W])
-__global__ void axis_phase_kernel(Mesh m, int rmax, cd* P) {
+// P[d][n, r] for the three axes, stored one after another ([N0 + N1 + N2, W]); C = cf:
+// formed in FP64 and rounded once
+template <class C>
+__global__ void axis_phase_kernel(Mesh m, int rmax, C* P) {
     const int W = 2 * rmax + 1;
     const int total = (m.n0 + m.n1 + m.n2) * W;
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < total; t += gridDim.x * blockDim.x) {
@@ -46,15 +48,22 @@ __global__ void axis_phase_kernel(Mesh m, int rmax, cd* P) {
         }
         int a = (int)(((int64_t)n * r) % N);
         if (a < 0) a += N;
-        P[t] = expi2pi((double)a / N);
+        P[t] = to_c<C>(expi2pi((double)a / N));
     }
 }
 
-hipError_t launch_axis_phases(Mesh m, int rmax, cd* P, hipStream_t s) {
+template <class C>
+static hipError_t axis_phases(Mesh m, int rmax, C* P, hipStream_t s) {
     const int W = 2 * rmax + 1;
-    hipLaunchKernelGGL(axis_phase_kernel, dim3(gridm((int64_t)(m.n0 + m.n1 + m.n2) * W, 256)),
+    hipLaunchKernelGGL(axis_phase_kernel<C>, dim3(gridm((int64_t)(m.n0 + m.n1 + m.n2) * W, 256)),
                        dim3(256), 0, s, m, rmax, P);
     return hipGetLastError();
+}
+hipError_t launch_axis_phases(Mesh m, int rmax, cd* P, hipStream_t s) {
+    return axis_phases<cd>(m, rmax, P, s);
+}
+hipError_t launch_axis_phases_f32(Mesh m, int rmax, cf* P, hipStream_t s) {
+    return axis_phases<cf>(m, rmax, P, s);
 }
 
 constexpr int kMaxW = 32;
@@ -774,6 +783,334 @@ __global__ __launch_bounds__(64 * kFoldWaves, fold_waves_per_simd<WT>()) void re
     }
 }
 
+// All three Re axes in one pass over g, for boxes of at most kRegW: nothing between g
+// and F (or G) reaches memory.  A work-group takes 64 columns; wave w (w < WT) holds
+// g[R0, R1, R2 = w] of its columns in registers (49 complex values at WT = 7) and goes
+// through the chunks of the call, each some pairs (k0, k1) of one plane k0 and some of
+// their k:
+//   T0[R1] = sum_R0 P0[k0, R0] g[R0, R1, w]      registers
+//   T1[p]  = sum_R1 P1[k1_p, R1] T0[R1]          registers -> LDS [pair][R2 = w][column]
+// and after a barrier the waves share the chunk's k in equal contiguous ranges:
+//   G[k]   = sum_R2 P2[k2, R2] T1[p(k), R2]      then the U_k fold (FOLD) or G itself.
+// g is read once per launch, so a launch covers as many k as F (or G) has rows for.
+//
+// g of 64 columns takes 351 of the 512 KB of registers of a CU at WT = 7, so there are two
+// waves per SIMD and latency is hidden by order, not by other waves: the next pair's or
+// k's phases are issued after the first product of the current one (scalar loads return
+// out of order, so a wait is for all of them) from the small per-axis tables, which
+// stay in the scalar cache (rows copied out in the order of use did not, and were
+// slower), and the chunk's eigenvector rows go from memory to LDS during the pair sums: a
+// vector load inside the k loop would wait for every F store before it.
+//
+// Against T0 in HBM (one plane per distinct k0, at 40 planes 5 times the size of g)
+// this takes out its write and its read, and the pair sums read no LDS.  nW = 16, 15
+// modes, 343 x 343 vectors, 1,964 k of a 40^3 mesh: 9.8 + 17.4 ms (planes, then pairs and
+// k) -> 15.6 ms, of which the k and fold 6.3; 454 k of a 24^3 mesh: 6.1 + 7.2 -> 6.4 ms.
+// Without the folded axes (RegAxis) 20.3 and 8.3 ms.  What bounds it is the scalar
+// phase loads (three pairs at a time instead of two is no faster) and FP64 VALU.
+//
+// FOLD: the 64 columns are b = 4 qb + g, a = i of one (Rp, mode) for lane (g, i), read from
+// g as 64-byte pieces; the four qb of a group run on one XCD, next to one another,
+// so that every line of g comes from HBM once.
+constexpr int kRegW = 7;
+constexpr int kRegK = 8;  // k of a wave in a chunk
+constexpr int reg_waves(int W) { return W == 7 ? 8 : (W == 1 ? 4 : W); }
+constexpr int reg_pairs(int W) { return W == 7 ? 16 : 12; }  // pairs of a chunk: its T1 in LDS
+template <int WT, class C>
+constexpr int reg_wps() { return WT == 7 ? 2 : (WT == 5 && sizeof(C) == 16 ? 3 : 4); }
+
+// Values of g that a lane keeps in LDS, not in registers: at WT = 7 in FP64 all 49 (196
+// VGPRs) beside the 28 of T0 or T1 spilled, and a spill's reload waits for every F store.
+template <int WT, class C>
+constexpr int reg_stash() { return WT == 7 && sizeof(C) == 16 ? 4 : 0; }
+// pairs whose phases are in scalar registers at a time (and as many of the next)
+template <int WT, class C>
+constexpr int reg_group() { return sizeof(C) == 16 ? 2 : 1; }
+
+void re_reg_limits(int rmax, int* pairs, int* ks) {
+    const int W = 2 * rmax + 1;
+    *pairs = reg_pairs(W);
+    *ks = kRegK * reg_waves(W);
+}
+
+// U_k of the first state of every entry, in the order re_reg_kernel uses them
+__global__ void re_urows_kernel(const int4* ent, int nent, const int32_t* st_urow, const cd* U, cd* ue) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= nent * 16) return;
+    const int4 e = ent[t >> 4];
+    ue[t] = e.x < e.y ? U[(int64_t)st_urow[e.x] * 16 + (t & 15)] : cd{0.0, 0.0};
+}
+
+// One axis sum sum_R P[n, R] v[R].  FP64 folds the axis: P[n, -r] = conj(P[n, r]) and
+// P[n, 0] = 1, so with s_r = v[r] + v[-r] and d_r = v[r] - v[-r] (formed once per v,
+// used for every n)
+//   sum_R P[n, R] v[R] = v[0] + sum_{r > 0} (cos_r s_r + i sin_r d_r):
+// 4 products per r instead of 8 and none at r = 0 (12 instead of 28 FMAs at W = 7), and 3
+// of a row's 7 phases are read.  FP32 keeps the sum of the per-axis kernels, whose
+// rounding shows in the results.
+template <int W, class C>
+struct RegAxis {
+    static constexpr bool SYM = sizeof(C) == 16;
+    static constexpr int H = W / 2, NP = SYM ? (H > 0 ? H : 1) : W;
+    struct Row {
+        C p[NP];
+    };
+    static __device__ inline void load(Row& q, const C* P, int row) {
+        const C* src = P + (int64_t)row * W + (SYM && H > 0 ? H + 1 : 0);
+#pragma unroll
+        for (int r = 0; r < NP; ++r) q.p[r] = src[r];
+    }
+    static __device__ inline void pair_up(C& lo, C& hi) {  // v[-r], v[r] -> d_r, s_r
+        const C a = hi, b = lo;
+        hi = C{a.x + b.x, a.y + b.y};
+        lo = C{a.x - b.x, a.y - b.y};
+    }
+    static __device__ inline void prepare(C (&v)[W]) {
+        if constexpr (SYM)
+#pragma unroll
+            for (int r = 1; r <= H; ++r) pair_up(v[H - r], v[H + r]);
+    }
+    // the terms of v[H - r] and v[H + r] (r >= 1), FP64
+    static __device__ inline void add_pair(C& acc, const C& p, const C& d, const C& s) {
+        acc.x = fma(p.x, s.x, fma(-p.y, d.y, acc.x));
+        acc.y = fma(p.x, s.y, fma(p.y, d.x, acc.y));
+    }
+    static __device__ inline C first(const Row& q, const C (&v)[W]) {  // the first terms
+        if constexpr (SYM) {
+            C acc = v[H];
+            if constexpr (H > 0) add_pair(acc, q.p[0], v[H - 1], v[H + 1]);
+            return acc;
+        } else {
+            return cfma(q.p[0], v[0], C{0, 0});
+        }
+    }
+    static __device__ inline void rest(C& acc, const Row& q, const C (&v)[W]) {
+        if constexpr (SYM) {
+#pragma unroll
+            for (int r = 2; r <= H; ++r) add_pair(acc, q.p[r - 1], v[H - r], v[H + r]);
+        } else {
+#pragma unroll
+            for (int r = 1; r < W; ++r) acc = cfma(q.p[r], v[r], acc);
+        }
+    }
+};
+
+template <int WT, class C, bool FOLD>
+__global__ __launch_bounds__(64 * reg_waves(WT), (reg_wps<WT, C>())) void re_reg_kernel(
+    const cd* __restrict__ gmat, int64_t NC, const int32_t* __restrict__ box_re,
+    const C* __restrict__ P0, const C* __restrict__ P1, const C* __restrict__ P2,
+    const int32_t* __restrict__ pair_k1, const cd* __restrict__ ue, const int32_t* __restrict__ chunks, int nchunk,
+    const int4* __restrict__ ent, int64_t ncb, FoldOut fo, C* __restrict__ G, int64_t ldg) {
+    using R = decltype(C::x);
+    using X = RegAxis<WT, C>;
+    using Row = typename X::Row;
+    constexpr int NWV = reg_waves(WT), PC = reg_pairs(WT), NS = reg_stash<WT, C>();
+    constexpr int GP = reg_group<WT, C>();
+    static_assert(PC % (2 * GP) == 0, "pairs are taken GP at a time, twice a pass");
+    extern __shared__ char smem_raw[];
+    C* sT = reinterpret_cast<C*>(smem_raw);             // [PC][WT][64]
+    C* sG = sT + PC * WT * 64;                          // [WT][NS][64]
+    cd* sU = reinterpret_cast<cd*>(sG + WT * NS * 64);  // FOLD: [NWV][kRegK][16]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, lg = lane >> 4;
+    int64_t cb;
+    if constexpr (FOLD) {
+        const int64_t id = blockIdx.x;
+        const int64_t grp = (id >> 5) * 8 + (id & 7);
+        cb = grp * 4 + ((id >> 3) & 3);
+        if (cb >= ncb) return;
+    } else {
+        cb = blockIdx.x;
+    }
+    const int64_t c = cb * 64 + lane;
+    const int64_t cg = FOLD ? (cb >> 2) * 256 + li * 16 + 4 * (int)(cb & 3) + lg : (c < NC ? c : NC - 1);
+    const uint32_t cgb = (uint32_t)cg * 16u;  // (a row of g is below 4 GB, checked at launch)
+    C g[WT][WT];
+    C* const gs = sG + wave * NS * 64 + lane;  // the last NS values (see reg_stash)
+    if (wave < WT) {
+        auto value = [&](int r0, int r1) {
+            const int row = box_re[(r0 * WT + r1) * WT + wave];
+            C v = {0, 0};
+            if (row >= 0)  // (wave-uniform: the row's address is scalar, the column 32-bit)
+                v = to_c<C>(ld_vec(reinterpret_cast<const cd*>(
+                    reinterpret_cast<const char*>(gmat + (int64_t)row * NC) + cgb)));
+            return v;
+        };
+        constexpr int H = WT / 2;
+#pragma unroll
+        for (int r1 = 0; r1 < WT; ++r1) g[H][r1] = value(H, r1);
+#pragma unroll
+        for (int r = 1; r <= H; ++r)
+#pragma unroll
+            for (int r1 = 0; r1 < WT; ++r1) {
+                C lo = value(H - r, r1), hi = value(H + r, r1);
+                if constexpr (X::SYM) X::pair_up(lo, hi);
+                g[H - r][r1] = lo;
+                const int e = (H + r) * WT + r1 - (WT * WT - NS);
+                if (e < 0)
+                    g[H + r][r1] = hi;
+                else
+                    st_vec(gs + e * 64, hi);
+            }
+    }
+    // F columns of this block: Rp row r, mode sa, b = 4 qb + lg
+    C* Fo = nullptr;
+    int64_t fst = 0;
+    if constexpr (FOLD) {
+        const int64_t grp = cb >> 2;
+        const int r = (int)(grp / fo.nm), sa = (int)(grp - (int64_t)r * fo.nm);
+        Fo = reinterpret_cast<C*>(fo.F) + (int64_t)r * fo.nc_pad + sa * 16 + 4 * (int)(cb & 3) + lg;
+        fst = (int64_t)fo.rp_pad * fo.nc_pad;
+    }
+    // small grids: the chunks are shared over grid.y
+    const int ch0 = (int)((int64_t)nchunk * blockIdx.y / gridDim.y);
+    const int ch1 = (int)((int64_t)nchunk * (blockIdx.y + 1) / gridDim.y);
+    if (ch0 >= ch1) return;
+    int4 rec = *reinterpret_cast<const int4*>(chunks + 8 * ch0);  // k0, first pair, pairs, first entry
+    int ne = chunks[8 * ch0 + 4];                                 // entries
+    for (int ch = ch0; ch < ch1; ++ch) {
+        const int p0 = rec.y, np = rec.z, e0 = rec.w;
+        const int ibeg = e0 + ne * wave / NWV, iend = e0 + ne * (wave + 1) / NWV;
+        Row p0r, pha[GP], phb[GP];
+        X::load(p0r, P0, rec.x);
+        int k1n[GP];
+#pragma unroll
+        for (int j = 0; j < GP; ++j) X::load(pha[j], P1, pair_k1[p0 + j]);
+#pragma unroll
+        for (int j = 0; j < GP; ++j) k1n[j] = pair_k1[p0 + GP + j];
+        if constexpr (FOLD) {  // this wave's eigenvector rows, four per load, straight to LDS
+            cd* dst = sU + wave * kRegK * 16;
+            for (int i = ibeg; i < iend; i += 4)
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void*)(ue + (int64_t)i * 16 + lane),
+                    (__attribute__((address_space(3))) void*)(dst + (i - ibeg) * 16), 16, 0, 0);
+        }
+        if (wave < WT) {
+            C t0[WT];
+            constexpr int H = WT / 2;
+            auto gv = [&](int r0, int r1) {
+                const int e = r0 * WT + r1 - (WT * WT - NS);
+                return e < 0 ? g[r0][r1] : ld_vec(gs + e * 64);
+            };
+#pragma unroll
+            for (int r1 = 0; r1 < WT; ++r1) {
+                if constexpr (X::SYM) {
+                    t0[r1] = g[H][r1];
+#pragma unroll
+                    for (int r = 1; r <= H; ++r)
+                        X::add_pair(t0[r1], p0r.p[r - 1], gv(H - r, r1), gv(H + r, r1));
+                } else {
+                    t0[r1] = C{0, 0};
+#pragma unroll
+                    for (int r0 = 0; r0 < WT; ++r0) t0[r1] = cfma(p0r.p[r0], gv(r0, r1), t0[r1]);
+                }
+            }
+            X::prepare(t0);
+            // GP pairs at a time, the next ones' phases issued after the first terms of these;
+            // the last group may end past the chunk's pairs, in unused slots
+            auto group = [&](int p, const Row (&ph)[GP], Row (&nx)[GP]) {
+                C acc[GP];
+#pragma unroll
+                for (int j = 0; j < GP; ++j) acc[j] = X::first(ph[j], t0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < GP; ++j) X::load(nx[j], P1, k1n[j]);
+#pragma unroll
+                for (int j = 0; j < GP; ++j) k1n[j] = pair_k1[p0 + p + 2 * GP + j];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < GP; ++j) {
+                    X::rest(acc[j], ph[j], t0);
+                    st_vec(sT + ((p + j) * WT + wave) * 64 + lane, acc[j]);
+                }
+            };
+            for (int p = 0; p < np; p += 2 * GP) {
+                group(p, pha, phb);
+                group(p + GP, phb, pha);
+            }
+        }
+        // the first k's phases and record, ahead of the barrier
+        // (entry: first state, end of its states, pair of the chunk + 256 k2, batch row)
+        int4 en = ent[ibeg], en1 = ent[ibeg + 1];
+        X::load(pha[0], P2, en.z >> 8);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FOLD) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): sU
+        __syncthreads();
+        if (ibeg < iend) {  // (wave-uniform)
+            int cur = -1;
+            C t1[WT];
+            auto one = [&](int i, const Row& ph, Row& nx) {
+                if ((en.z & 255) != cur) {
+                    cur = en.z & 255;
+#pragma unroll
+                    for (int r2 = 0; r2 < WT; ++r2) t1[r2] = ld_vec(sT + (cur * WT + r2) * 64 + lane);
+                    X::prepare(t1);
+                }
+                C u = {0, 0};
+                if constexpr (FOLD) u = to_c<C>(ld_vec(sU + (wave * kRegK + i - ibeg) * 16 + li));
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): nothing but the prefetch below
+                __builtin_amdgcn_sched_barrier(0);
+                const int4 ec = en;
+                en = en1;
+                X::load(nx, P2, en.z >> 8);
+                en1 = ent[i + 2];
+                __builtin_amdgcn_sched_barrier(0);
+                C acc = X::first(ph, t1);
+                X::rest(acc, ph, t1);
+                if constexpr (FOLD) {
+                    // sum over the 16 lanes of a row: conj(U_k[a, n]) G
+                    auto fold = [&](const C& v, int st) {
+                        const R f = row16_sum2(v.x * acc.x + v.y * acc.y, v.x * acc.y - v.y * acc.x,
+                                               li & 1);
+                        if (li < 2) reinterpret_cast<R*>(Fo + st * fst)[li] = f;
+                    };
+                    if (ec.x < ec.y) fold(u, ec.x);
+                    for (int st = ec.x + 1; st < ec.y; ++st)
+                        fold(to_c<C>(fo.U[(int64_t)fo.st_urow[st] * 16 + li]), st);
+                } else if (c < NC) {
+                    G[(int64_t)ec.w * ldg + c] = acc;
+                }
+            };
+            for (int i = ibeg; i < iend; i += 2) {
+                one(i, pha[0], phb[0]);
+                if (i + 1 < iend) one(i + 1, phb[0], pha[0]);
+            }
+        }
+        if (ch + 1 < ch1) {  // the next chunk's record, ahead of the barrier
+            rec = *reinterpret_cast<const int4*>(chunks + 8 * (ch + 1));
+            ne = chunks[8 * (ch + 1) + 4];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+    }
+}
+
+template <int WT, class C, bool FOLD>
+static hipError_t go_re_reg(const cd* g, int64_t NC, const int32_t* box_re, Mesh m, const C* P,
+                            const ReRegBatch& b, const FoldOut& fo, C* G, int64_t ldg, hipStream_t s) {
+    const C* P1 = P + (int64_t)m.n0 * WT;
+    const C* P2 = P1 + (int64_t)m.n1 * WT;
+    const int4* ent = reinterpret_cast<const int4*>(b.ent);
+    if (FOLD)
+        hipLaunchKernelGGL(re_urows_kernel, dim3((unsigned)((b.nent + 15) / 16)), dim3(256), 0, s, ent,
+                           b.nent, fo.st_urow, fo.U, b.ue);
+    const size_t shm = (size_t)(reg_pairs(WT) + reg_stash<WT, C>()) * WT * 64 * sizeof(C) +
+                       (FOLD ? (size_t)reg_waves(WT) * kRegK * 16 * sizeof(cd) : 0);
+    hipError_t e = hipFuncSetAttribute((const void*)re_reg_kernel<WT, C, FOLD>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+    if (e != hipSuccess) return e;
+    const int64_t ncb = (NC + 63) / 64;
+    const int64_t groups = FOLD ? (ncb + 31) / 32 * 32 : ncb;  // FOLD: ids 32 j + 8 qb + xcd
+    if (groups > 2147483647LL) return hipErrorInvalidValue;
+    // few column blocks: each taken by several work-groups, a share of the chunks each
+    // (they read the block of g again, from L2)
+    const int split = (int)std::min<int64_t>(b.nchunk, std::max<int64_t>(1, 1024 / groups));
+    hipLaunchKernelGGL((re_reg_kernel<WT, C, FOLD>), dim3((unsigned)groups, split),
+                       dim3(64 * reg_waves(WT)), shm, s, g, NC, box_re, P, P1, P2, b.pair_k1, b.ue,
+                       b.chunks, b.nchunk, ent, ncb, fo, G, ldg);
+    return hipGetLastError();
+}
+
 template <int WT, class C>
 static hipError_t go_re_axis0(const cd* g, int64_t NC, const int32_t* box_re, int W, const cd* P,
                               const int32_t* k0_list, int n, bool tr, C* T0, hipStream_t s) {
@@ -872,6 +1209,40 @@ static hipError_t re_pairs(const C* T0, int64_t NC, int rmax, Mesh m, const cd* 
     return with_box_width(W, [&](auto wt) {
         return go_re_axis12<decltype(wt)::value, C>(T0, NC, W, m, P, b, fo, G, ldg, s);
     });
+}
+
+bool re_reg_supported(int rmax, int64_t NC) {
+    return 2 * rmax + 1 <= kRegW && NC < ((int64_t)1 << 28);  // (32-bit byte offsets in a row)
+}
+
+template <class C>
+static hipError_t re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
+                         const C* P, const ReRegBatch& b, const FoldOut* fo, C* G, int64_t ldg,
+                         hipStream_t s) {
+    if (!re_reg_supported(rmax, NC) || b.nchunk <= 0 || b.nent <= 0 || m.n2 >= (1 << 23) ||
+        !fold_ok(fo, NC) || ((reinterpret_cast<uintptr_t>(b.ent) | reinterpret_cast<uintptr_t>(b.ue)) & 15))
+        return hipErrorInvalidValue;
+    auto go = [&](auto wt) {
+        constexpr int WT = decltype(wt)::value;
+        return fo ? go_re_reg<WT, C, true>(g, NC, box_re, m, P, b, *fo, G, ldg, s)
+                  : go_re_reg<WT, C, false>(g, NC, box_re, m, P, b, FoldOut{}, G, ldg, s);
+    };
+    switch (rmax) {
+        case 0: return go(std::integral_constant<int, 1>{});
+        case 1: return go(std::integral_constant<int, 3>{});
+        case 2: return go(std::integral_constant<int, 5>{});
+        default: return go(std::integral_constant<int, 7>{});
+    }
+}
+hipError_t launch_re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
+                         const cd* P, const ReRegBatch& b, const FoldOut* fo, cd* G, int64_t ldg,
+                         hipStream_t s) {
+    return re_reg<cd>(g, NC, box_re, rmax, m, P, b, fo, G, ldg, s);
+}
+hipError_t launch_re_reg_f32(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
+                             const cf* P, const ReRegBatch& b, const FoldOut* fo, cf* G, int64_t ldg,
+                             hipStream_t s) {
+    return re_reg<cf>(g, NC, box_re, rmax, m, P, b, fo, G, ldg, s);
 }
 
 hipError_t launch_re_axes(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,

@@ -486,7 +486,7 @@ __global__ void build_states_kernel(const int32_t* ids, int nst, int nW, const i
                                     const double* eps, const double* bmin, const double* bmax,
                                     const double* wmax, double cut, int32_t* st_row,
                                     int32_t* st_band, int32_t* st_kmesh, int32_t* st_mlo,
-                                    int32_t* st_mhi) {
+                                    int32_t* st_mhi, int32_t* st_urow) {
     const int st = blockIdx.x * blockDim.x + threadIdx.x;
     if (st >= nst) return;
     const int id = ids[st];
@@ -506,16 +506,18 @@ __global__ void build_states_kernel(const int32_t* ids, int nst, int nW, const i
     st_kmesh[st] = km;
     st_mlo[st] = mlo;
     st_mhi[st] = mhi;
+    if (st_urow) st_urow[st] = km * nW + band;
 }
 
 hipError_t launch_build_states(const int32_t* ids, int nst, int nW, const int32_t* kept,
                                const double* eps, const double* bmin, const double* bmax,
                                const double* wmax, double cut, int32_t* st_row, int32_t* st_band,
                                int32_t* st_kmesh, int32_t* st_mlo, int32_t* st_mhi,
-                               hipStream_t s) {
+                               int32_t* st_urow, hipStream_t s) {
     if (nst <= 0) return hipSuccess;
     hipLaunchKernelGGL(build_states_kernel, dim3((nst + 127) / 128), dim3(128), 0, s, ids, nst, nW,
-                       kept, eps, bmin, bmax, wmax, cut, st_row, st_band, st_kmesh, st_mlo, st_mhi);
+                       kept, eps, bmin, bmax, wmax, cut, st_row, st_band, st_kmesh, st_mlo, st_mhi,
+                       st_urow);
     return hipGetLastError();
 }
 

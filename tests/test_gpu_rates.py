@@ -394,3 +394,50 @@ def test_two_tile_modes_fp32_factored(lib, nW, nat, mesh):
     mx, med, _ = rel_err(gamma.cpu().numpy()[:n], ref["gamma"])
     print(f"nW {nW}: FP32 factorised Gamma rel err max {mx:.2e} median {med:.2e}")
     assert mx < 1e-6
+
+
+@pytest.mark.parametrize("r_e,nW,mesh,order", [
+    (1, 5, (3, 20, 6), "all"),        # 20 pairs a plane: two chunks; G written
+    (2, 16, (2, 17, 5), "shuffled"),  # fold; rows out of order and repeated
+    (3, 16, (3, 20, 6), "all"),       # fold, 16 states a k, more k a plane than one chunk's
+    (3, 5, (4, 3, 7), "shuffled"),
+    (3, 16, (1, 1, 5), "all"),        # one pair, one chunk
+])
+def test_one_pass_stage1(lib, r_e, nW, mesh, order):
+    """The one-pass Re sum against the direct contraction, FP64 and FP32; and under a budget
+    that splits its batches, where the results are the same bits."""
+    torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem, Library
+    rng = np.random.default_rng(100 * r_e + nW)
+    s = synth.small_system(94 + r_e, n_wannier=nW, n_atoms=1, r=1)
+    box = synth.box_vectors(r_e)
+    inner = box[rng.choice(len(box), size=min(len(box), 40), replace=False)]
+    s.re = np.ascontiguousarray(np.unique(np.concatenate([inner, [[-r_e, 0, r_e]]]), axis=0),
+                                dtype=np.int32)
+    shape = (len(s.re), 27, 3, nW, nW)
+    s.g_rr = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    N = int(np.prod(mesh))
+    mu = float(np.median(rates.mesh_tables(s, mesh)["eps"]))
+    par = dict(mu=mu, kT=constants.kT_of(300.0), sigma=0.1, win_lo=-1e30, win_hi=1e30,
+               omega_min=1e-4)
+    k_idx = None if order == "all" else rng.integers(0, N, size=min(N, 50))
+    ds = DeviceSystem.from_host(s)
+    small = Library(0, workspace_budget=100 * 10**6)
+    try:
+        lib.set_mesh_sum("direct")
+        _, ref, _, _ = _gpu_rates(lib, s, mesh, par, k_idx=k_idx, ds=ds)
+        lib.set_mesh_sum("factored")
+        small.set_mesh_sum("factored")
+        _, got, _, _ = _gpu_rates(lib, s, mesh, par, k_idx=k_idx, ds=ds)
+        _, split, _, _ = _gpu_rates(small, s, mesh, par, k_idx=k_idx, ds=ds)
+        torch = torch_cuda()
+        kd = None if k_idx is None else torch.from_numpy(k_idx.astype(np.int32)).cuda()
+        g32 = torch.zeros((len(ref), nW), dtype=torch.float64, device="cuda")
+        lib.scatter_rates(ds, mesh, par, g32, k_idx=kd, precision="fp32")
+        torch.cuda.synchronize()
+    finally:
+        lib.set_mesh_sum("auto")
+        small.close()
+    assert rel_err(got, ref)[0] < 1e-11
+    assert np.array_equal(got, split)
+    assert rel_err(g32.cpu().numpy(), ref)[0] < 1e-5
