@@ -117,6 +117,8 @@ hipError_t launch_stage2_rates(const RateArgs& a, int nst, hipStream_t s);
 
 // Per-axis phase tables P[d][n, r] = e^{i2pi (n (r - rmax) mod N_d)/N_d}, [N0+N1+N2, W].
 hipError_t launch_axis_phases(Mesh m, int rmax, cd* P, hipStream_t s);
+// Rows of a lattice list (device [n, 3], no vector twice) by position in its box.
+hipError_t launch_box_rows(const int32_t* R, int n, int rmax, int32_t* box, hipStream_t s);
 hipError_t launch_axis_phases_f32(Mesh m, int rmax, cf* P, hipStream_t s);  // rounded to FP32
 // T1 (axis 2) and T2 (axis 1) of the factorised full-mesh sum over Rp.
 // line_any (nullable): [nst, N1*N2]; T2 of a line whose entry is 0 is not formed.

@@ -66,6 +66,21 @@ hipError_t launch_axis_phases_f32(Mesh m, int rmax, cf* P, hipStream_t s) {
     return axis_phases<cf>(m, rmax, P, s);
 }
 
+// box position ((R0 + r) W + R1 + r) W + R2 + r -> row of a lattice list (-1: not listed);
+// one work-group, the list holding no vector twice
+__global__ __launch_bounds__(1024) void box_rows_kernel(const int32_t* R, int n, int rmax, int32_t* box) {
+    const int W = 2 * rmax + 1;
+    for (int i = threadIdx.x; i < W * W * W; i += 1024) box[i] = -1;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += 1024)
+        box[((R[3 * i] + rmax) * W + R[3 * i + 1] + rmax) * W + R[3 * i + 2] + rmax] = i;
+}
+
+hipError_t launch_box_rows(const int32_t* R, int n, int rmax, int32_t* box, hipStream_t s) {
+    hipLaunchKernelGGL(box_rows_kernel, dim3(1), dim3(1024), 0, s, R, n, rmax, box);
+    return hipGetLastError();
+}
+
 constexpr int kMaxW = 32;
 
 // T1[st, p, q2, c] = sum_r P2[q2, r] F[st, box_rp[p W + r], c]   (p = (R0, R1))

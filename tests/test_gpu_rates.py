@@ -441,3 +441,30 @@ def test_one_pass_stage1(lib, r_e, nW, mesh, order):
     assert rel_err(got, ref)[0] < 1e-11
     assert np.array_equal(got, split)
     assert rel_err(g32.cpu().numpy(), ref)[0] < 1e-5
+
+
+@pytest.mark.parametrize("nW,r,mesh", [
+    (3, 2, (24, 24, 24)),    # box 5 wide
+    (5, 3, (16, 17, 15)),    # box 7 wide, odd axes
+    (2, 4, (1, 3, 600)),     # box 9 wide, a short and a single-plane axis
+])
+def test_mesh_bands_by_axes(lib, nW, r, mesh):
+    """H(k) over a mesh axis by axis against the phase table and GEMM, which a list that
+    holds a vector twice (half of H(R) in each) still takes: the same rates."""
+    torch_cuda()
+    import dataclasses
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(140 + nW, n_wannier=nW, n_atoms=1, r=r)
+    rows = np.flatnonzero(np.any(s.rh != 0, axis=1))[-1:]
+    h2 = np.concatenate([s.h_r, 0.5 * s.h_r[rows]])
+    h2[rows] *= 0.5
+    twice = dataclasses.replace(s, rh=np.ascontiguousarray(np.concatenate([s.rh, s.rh[rows]])),
+                                h_r=np.ascontiguousarray(h2))
+    assert len(s.rh) * int(np.prod(mesh)) >= 1 << 20 and 2 * (2 * r + 1) <= len(s.rh)
+    k_idx = np.arange(0, int(np.prod(mesh)), max(1, int(np.prod(mesh)) // 7))[:7]
+    par = dict(mu=0.0, kT=constants.kT_of(300.0), sigma=0.1, win_lo=-1e30, win_hi=1e30,
+               omega_min=1e-4)
+    _, got, _, _ = _gpu_rates(lib, s, mesh, par, k_idx=k_idx, ds=DeviceSystem.from_host(s))
+    _, ref, _, _ = _gpu_rates(lib, twice, mesh, par, k_idx=k_idx, ds=DeviceSystem.from_host(twice))
+    assert np.max(np.abs(ref)) > 0
+    assert rel_err(got, ref)[0] < 1e-10
