@@ -351,7 +351,7 @@ phoebe_status interp_g_impl(Handle* h, const phoebe_system* sys, const double* k
             if (polar) {
                 HIPCHK(h, hipMemcpyAsync(born, sys->polar->born, sizeof(double) * 9 * sys->n_atoms,
                                          hipMemcpyHostToDevice, s));
-                HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, nm, polar_dev(sys, born),
+                HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, true, nm, polar_dev(sys, born),
                                               Lq, s));
             }
             if (fact) {
@@ -931,7 +931,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 // (eigenvectors as rows: the rate kernels read each one contiguously)
                 electron_bands_dev(h, b1, sys, T.rh, nullptr, nullptr, mesh, N, T.eps, T.U, s, true);
                 phonon_dev(h, b2, sys, T.rd, nullptr, nullptr, mesh, N, par->omega_min, par->kT,
-                           T.omega, T.E, T.nb, nullptr, s);
+                           T.omega, T.E, T.nb, nullptr, s, false);
                 if (use_cache) {
                     tc.valid = false;
                     if (tc.bytes < tc_bytes) {
@@ -978,7 +978,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         if (polar) {
             HIPCHK(h, hipMemcpyAsync(T.born, sys->polar->born, sizeof(double) * 9 * sys->n_atoms,
                                      hipMemcpyHostToDevice, s));
-            HIPCHK(h, launch_polar_factor(nullptr, mesh, N, T.E, nm, polar_dev(sys, T.born), T.Lpol, s));
+            HIPCHK(h, launch_polar_factor(nullptr, mesh, N, T.E, false, nm, polar_dev(sys, T.born), T.Lpol, s));
         }
         // adaptive smearing: velocities on the mesh; the widest width any transition
         // can take bounds the final-band pruning
@@ -1612,7 +1612,7 @@ phoebe_status phoebe_gpu_polar_factor(void* handle, const phoebe_system* sys, co
             if (!ar.base) return;
             HIPCHK(h, hipMemcpyAsync(born, sys->polar->born, sizeof(double) * 9 * sys->n_atoms,
                                      hipMemcpyHostToDevice, s));
-            HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, nm, polar_dev(sys, born),
+            HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, true, nm, polar_dev(sys, born),
                                           reinterpret_cast<cd*>(l_out), s));
         };
         Arena dry(nullptr);

@@ -36,7 +36,7 @@ hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, 
 // (0 when inactive or kT <= 0).
 hipError_t launch_phonon_post(const double* lam, const cd* z, const double* mass, int nat,
                               int64_t nq, double omega_min, double kT, double* omega, cd* e,
-                              double* nb, hipStream_t s);
+                              bool by_mode, double* nb, hipStream_t s);
 
 // Fermi occupations of a band table.
 hipError_t launch_fermi(const double* eps, int64_t n, double mu, double kT, double* f,
@@ -87,7 +87,7 @@ struct RateArgs {
     const cd* U;               // [Nk, nW, nW] transposed: U[k, band, orbital]
     const double* omega;       // [Nq, nm]
     const double* nb;          // [Nq, nm]
-    const cd* E;               // [Nq, nm, nm]: E[q, nu, sa] = z[q][sa][nu] l_{sa,nu}
+    const cd* E;               // [Nq, nm, nm]: E[q, sa, nu] = z[q][sa][nu] l_{sa,nu}
     int nW, nm;
     double sigma;
     double* partial;           // [nst, n_qtiles]

@@ -18,10 +18,20 @@ static inline unsigned grid_n(int64_t n, int block) {
 // ---------------------------------------------------------------------------
 // Polar long-range factor (Electron Properties, long-range coupling)
 // ---------------------------------------------------------------------------
-__global__ void polar_factor_kernel(const double* frac, Mesh m, int64_t np, const cd* E, int nm,
-                                    PolarDev pd, double pref, cd* L) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < np;
-         p += (int64_t)gridDim.x * blockDim.x) {
+//
+// D is linear in K: the sum over G leaves only S = sum_G w(G) K(G), and D = Z^T S.  A point
+// has kPolarLanes lanes, which share the G and then the modes; a thread per point, with a
+// D of its own to add to for each G, left most of the chip idle (9,384 points, 343 G,
+// 3 atoms: 335 us; PFNEW us so, bound by the exponentials and divisions).
+constexpr int kPolarLanes = 16;
+
+__global__ __launch_bounds__(256) void polar_factor_kernel(const double* frac, Mesh m, int64_t np,
+                                                           const cd* __restrict__ E, bool by_mode, int nm,
+                                                           PolarDev pd, double pref, cd* __restrict__ L) {
+    const int lane = threadIdx.x % kPolarLanes;
+    constexpr int G = 256 / kPolarLanes;
+    for (int64_t p = blockIdx.x * (int64_t)G + threadIdx.x / kPolarLanes; p < np;
+         p += (int64_t)gridDim.x * G) {
         double q[3];
         if (frac) {
             q[0] = frac[3 * p];
@@ -34,47 +44,52 @@ __global__ void polar_factor_kernel(const double* frac, Mesh m, int64_t np, cons
             q[1] = (double)i1 / m.n1;
             q[2] = (double)i2 / m.n2;
         }
-        double D[30];
-        for (int i = 0; i < 3 * pd.nat; ++i) D[i] = 0.0;
-        const int gm = pd.g_max;
-        for (int g0 = -gm; g0 <= gm; ++g0)
-            for (int g1 = -gm; g1 <= gm; ++g1)
-                for (int g2 = -gm; g2 <= gm; ++g2) {
-                    const double K0 = 2.0 * kPi * (q[0] + g0), K1 = 2.0 * kPi * (q[1] + g1),
-                                 K2 = 2.0 * kPi * (q[2] + g2);
-                    if (sqrt(K0 * K0 + K1 * K1 + K2 * K2) <= 1e-12) continue;  // q + G = 0
-                    const double* e = pd.eps;
-                    const double den = K0 * (e[0] * K0 + e[1] * K1 + e[2] * K2) +
-                                       K1 * (e[3] * K0 + e[4] * K1 + e[5] * K2) +
-                                       K2 * (e[6] * K0 + e[7] * K1 + e[8] * K2);
-                    const double w = exp(-den / (4.0 * pd.alpha)) / den;
-                    for (int s = 0; s < pd.nat; ++s) {
-                        const double* Z = pd.born + 9 * s;
-                        for (int b = 0; b < 3; ++b)
-                            D[3 * s + b] += w * (K0 * Z[b] + K1 * Z[3 + b] + K2 * Z[6 + b]);
-                    }
-                }
+        const int gm = pd.g_max, gw = 2 * gm + 1;
+        double S0 = 0.0, S1 = 0.0, S2 = 0.0;
+        for (int g = lane; g < gw * gw * gw; g += kPolarLanes) {
+            const int g0 = g / (gw * gw) - gm, g1 = g / gw % gw - gm, g2 = g % gw - gm;
+            const double K0 = 2.0 * kPi * (q[0] + g0), K1 = 2.0 * kPi * (q[1] + g1),
+                         K2 = 2.0 * kPi * (q[2] + g2);
+            if (sqrt(K0 * K0 + K1 * K1 + K2 * K2) <= 1e-12) continue;  // q + G = 0
+            const double* e = pd.eps;
+            const double den = K0 * (e[0] * K0 + e[1] * K1 + e[2] * K2) +
+                               K1 * (e[3] * K0 + e[4] * K1 + e[5] * K2) +
+                               K2 * (e[6] * K0 + e[7] * K1 + e[8] * K2);
+            const double w = exp(-den / (4.0 * pd.alpha)) / den;
+            S0 += w * K0;
+            S1 += w * K1;
+            S2 += w * K2;
+        }
+#pragma unroll
+        for (int o = kPolarLanes / 2; o > 0; o >>= 1) {
+            S0 += __shfl_xor(S0, o, 64);
+            S1 += __shfl_xor(S1, o, 64);
+            S2 += __shfl_xor(S2, o, 64);
+        }
         const cd* Ep = E + p * nm * nm;
-        for (int nu = 0; nu < nm; ++nu) {
+        const int sn = by_mode ? nm : 1, ss = by_mode ? 1 : nm;
+        for (int nu = lane; nu < nm; nu += kPolarLanes) {
             cd acc = {0.0, 0.0};
             for (int sa = 0; sa < nm; ++sa) {
-                const cd e = Ep[nu * nm + sa];
-                acc.x += D[sa] * e.x;
-                acc.y += D[sa] * e.y;
+                const double* Z = pd.born + 9 * (sa / 3) + sa % 3;
+                const double D = S0 * Z[0] + S1 * Z[3] + S2 * Z[6];
+                const cd e = Ep[nu * sn + sa * ss];
+                acc.x += D * e.x;
+                acc.y += D * e.y;
             }
             L[p * nm + nu] = cd{pref * acc.x, pref * acc.y};
         }
     }
 }
 
-hipError_t launch_polar_factor(const double* frac, Mesh m, int64_t np, const cd* E, int nm,
-                               const PolarDev& pd, cd* L, hipStream_t s) {
+hipError_t launch_polar_factor(const double* frac, Mesh m, int64_t np, const cd* E, bool by_mode,
+                               int nm, const PolarDev& pd, cd* L, hipStream_t s) {
     if (np <= 0) return hipSuccess;
     if (pd.nat > 10 || nm != 3 * pd.nat) return hipErrorInvalidValue;
     // 4 pi (e^2 / (4 pi eps0)) in eV A^2 for V = 1 A^3 (CODATA 2018: e / (4 pi eps0 A))
     const double e2 = 1.602176634e-19 / (4.0 * kPi * 8.8541878128e-12 * 1.0e-10);
-    hipLaunchKernelGGL(polar_factor_kernel, dim3(grid_n(np, 128)), dim3(128), 0, s, frac, m, np, E,
-                       nm, pd, 4.0 * kPi * e2, L);
+    hipLaunchKernelGGL(polar_factor_kernel, dim3(grid_n(np, 256 / kPolarLanes)), dim3(256), 0, s, frac,
+                       m, np, E, by_mode, nm, pd, 4.0 * kPi * e2, L);
     return hipGetLastError();
 }
 

@@ -679,7 +679,7 @@ hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, 
 // ---------------------------------------------------------------------------
 __global__ void phonon_post_kernel(const double* lam, const cd* z, const double* mass, int nat,
                                    int64_t nq, double omega_min, double kT, double c_om,
-                                   double c_ph, double* omega, cd* e, double* nb) {
+                                   double c_ph, double* omega, cd* e, bool by_mode, double* nb) {
     const int nm = 3 * nat;
     const int64_t total = nq * nm;
     for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
@@ -692,10 +692,10 @@ __global__ void phonon_post_kernel(const double* lam, const cd* z, const double*
         if (omega) omega[t] = w;
         if (nb) nb[t] = (act && kT > 0.0) ? 1.0 / expm1(w / kT) : 0.0;
         if (e) {
-            // E[q, nu, sa] = z[q][sa][nu] l_{sa,nu}: one mode's column contiguous
+            // z[q][sa][nu] l_{sa,nu} as E[q, nu, sa] (by_mode) or E[q, sa, nu]
             for (int sa = 0; sa < nm; ++sa) {
                 const int64_t o = (q * nm + sa) * nm + nu;
-                const int64_t oe = (q * nm + nu) * nm + sa;
+                const int64_t oe = by_mode ? (q * nm + nu) * nm + sa : o;
                 if (act) {
                     const double ls = sqrt(c_ph / (2.0 * mass[sa / 3] * w));
                     e[oe] = cd{z[o].x * ls, z[o].y * ls};
@@ -709,10 +709,10 @@ __global__ void phonon_post_kernel(const double* lam, const cd* z, const double*
 
 hipError_t launch_phonon_post(const double* lam, const cd* z, const double* mass, int nat,
                               int64_t nq, double omega_min, double kT, double* omega, cd* e,
-                              double* nb, hipStream_t s) {
+                              bool by_mode, double* nb, hipStream_t s) {
     if (nq <= 0) return hipSuccess;
     hipLaunchKernelGGL(phonon_post_kernel, dim3(grid_for(nq * 3 * nat, 256)), dim3(256), 0, s, lam,
-                       z, mass, nat, nq, omega_min, kT, c_omega(), kCPh, omega, e, nb);
+                       z, mass, nat, nq, omega_min, kT, c_omega(), kCPh, omega, e, by_mode, nb);
     return hipGetLastError();
 }
 

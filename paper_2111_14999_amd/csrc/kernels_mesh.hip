@@ -1359,8 +1359,8 @@ __device__ inline R rows4_reduce_scatter(R u0, R u1, R u2, R u3) {
 // masks of one line are contiguous, so the line kernel reads them as one
 // block.  The thread also leaves
 // the union of its line's bands in line_bands and counts (one atomic per wave)
-// n_live[0] the lines with a live band and n_live[1] the units of 16 points the
-// line kernel will take (per band, its live points / 16 rounded up), and writes
+// n_live[0] the lines with a live band and n_live[1] the units of 16 points of its bands
+// (per band, its live points / 16 rounded up), and writes
 // the zero partial sum of every pair without a live band.
 __global__ __launch_bounds__(256, 8) void line_live_kernel(RateArgs a, uint32_t* __restrict__ live,
                                  uint32_t* __restrict__ line_bands, uint32_t* __restrict__ n_live) {
@@ -1491,8 +1491,24 @@ constexpr int kTP = 2;  // column tiles per MFMA pass
 // extension terms, and the FP64 form with two tiles per mode (its U_{k+q} values
 // of both halves), need more registers, and at four waves they would spill.
 constexpr int kLineLW = 1, kLinePol = 2, kLineVel = 4;
-template <int FEAT, int H, bool F64, int NWV = 4>
+
+// MB: bands a work-group takes together, sharing the list of points and with it the MFMA
+// part of a unit, the E_q loads and, per band and point, the width and its divisions.  The
+// adaptive widths leave about four live bands at a point (24^3 mesh, 16 bands: 52,900 live
+// (q, band) against 13,800 live q a state), where one list per band computes X four times;
+// the plain Gaussian at the band edge leaves one, and there the registers of the further
+// bands only cost occupancy.  Adaptive rates of that mesh, 543 states, ms in this kernel:
+// MB 1 25.1; MB 2, 3, 4, 6 16.9, 16.5, 18.0, 18.1 (three waves per SIMD up to MB 3, two
+// above); four waves of MB 4 18.5.  What is left is the terms' FP64 arithmetic (the two
+// exponentials; 5 ms), the MFMA part (4 ms), Y (2 ms) and the waits between them.
+template <int FEAT, int H>
+constexpr int line_bands_at_once() {
+    return FEAT & kLineVel ? (H == 2 ? 2 : 3) : 1;
+}
+
+template <int FEAT, int H, bool F64, int NWV = 4, int MB = 1>
 constexpr int line_waves_per_simd() {
+    if (MB > 1) return FEAT == kLineVel ? 3 : 2;  // (every extension at once would spill at three)
     if (NWV == 2) return FEAT & kLinePol ? 2 : 3;  // two waves per work-group: twice the tiles per wave
     if (H == 2 && F64) return FEAT == 0 || FEAT == kLineLW ? 3 : 2;
     return FEAT == 0 || FEAT == kLineLW ? 4 : 3;
@@ -1506,15 +1522,15 @@ constexpr int line_waves_per_simd() {
 // launch against 2.68 ms; one wave of sixteen tiles, 2.47 ms; two waves loading
 // T2 per K step, 2.73 ms).  The plain rates of two and three tiles per wave take the
 // two-wave form as well (the batched plan of 32 systems: 137.9 -> 133.9 ms), and so do
-// the linewidth and adaptive-width variants (163 VGPRs; phonon linewidth 107 -> 101.5 ms,
-// adaptive rates 541 -> 478 ms per step) and, at two waves per SIMD (181 VGPRs; four
+// the linewidth and adaptive-width variants (phonon linewidth 107 -> 101.5 ms, adaptive
+// rates 541 -> 478 ms per step) and, at two waves per SIMD (181 VGPRs; four
 // pairs per CU against three), the polar one (3.29 -> 3.16 ms per launch); with two
 // tiles per mode (16 < nW <= 32) the plain rates of one and two modes per wave, the
 // latter in FP32 (batched plan 133.4 -> 132.1 ms); and the plain rates of six and eight
 // tiles per wave, whose T2 is read per K step (12 and 16 tiles in two waves: 132.1 ->
 // 129.9 ms), with one or two tiles per mode (-> 128.6 ms).
-template <int TN, int KS, class C, int FEAT, int H = 1, int NWV = 4>
-__global__ __launch_bounds__(64 * NWV, (line_waves_per_simd<FEAT, H, sizeof(C) == sizeof(cd), NWV>())) void
+template <int TN, int KS, class C, int FEAT, int H = 1, int NWV = 4, int MB = 1>
+__global__ __launch_bounds__(64 * NWV, (line_waves_per_simd<FEAT, H, sizeof(C) == sizeof(cd), NWV, MB>())) void
 line_rates_kernel(RateArgs a) {
     constexpr int BT = 64 * NWV;  // threads of the work-group
     static_assert(H == 1 || (H == 2 && TN % 2 == 0 && kTP == 2),
@@ -1534,14 +1550,18 @@ line_rates_kernel(RateArgs a) {
     // start on different LDS banks (Wp apart, every other row would share banks)
     const int Ws = Wp + 1;
     C* sP = reinterpret_cast<C*>(smem_raw);                    // [N0 + 1][Ws], row N0 zero
-    C* sY = sP + (N0 + 1) * Ws;                                // [16][nm]
-    uint32_t* sPm = reinterpret_cast<uint32_t*>(sY + 16 * nm);  // [N0] live bands per point
+    C* sY = sP + (N0 + 1) * Ws;                                // [MB][16][nm]
+    uint32_t* sPm = reinterpret_cast<uint32_t*>(sY + MB * 16 * nm);  // [N0] live bands per point
     int* sList = reinterpret_cast<int*>(sPm + N0);             // [N0] live points of a band
     // LW: [N0][nm] linewidth partials of the work-group (8-byte aligned: N0 ints above)
     double* sLW = reinterpret_cast<double*>(sList + N0 + (N0 & 1));
     __shared__ double sRed[NWV];
     __shared__ int sCount;
-    __shared__ cd sO[16];  // POL: overlap [U_k^dagger U_{k+q}]_{n m} at the unit's points
+    struct BandPoint {
+        double x, f, is2, wt, cut;
+    };
+    __shared__ BandPoint sB[MB > 1 ? MB * 16 : 1];  // [MB][16], see band_point
+    __shared__ cd sO[MB * 16];  // POL: overlap [U_k^dagger U_{k+q}]_{n m} at the unit's points
 
     // XCD-aware order: work-groups are dealt to the 8 XCDs round-robin, so
     // with id = 8 j + x every state of a line lands on XCD x, one after
@@ -1554,7 +1574,7 @@ line_rates_kernel(RateArgs a) {
     const int line = (int)((j / nst) * 8 + xcd);
     const int st = (int)(j % nst);
     if (line >= NL) return;
-    uint32_t bands = a.line_bands[(int64_t)st * NL + line];
+    uint32_t bands = __builtin_amdgcn_readfirstlane(a.line_bands[(int64_t)st * NL + line]);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (!bands) return;  // its partial sum is 0 (written with the masks)
     const int q1 = line / mesh.n2, q2 = line - q1 * mesh.n2;
@@ -1639,24 +1659,28 @@ line_rates_kernel(RateArgs a) {
     // at k+q and omega and n of (q, nu).  Items beyond the first of a thread
     // (nm > 16) read theirs in place.
     struct Unit {
-        C u[4 * H];  // U_{k+q}[b, m] at b = 16 h + 4 lg + v, entry 4 h + v
+        C u[MB][4 * H];  // U_{k+q}[b, m] at b = 16 h + 4 lg + v, entry 4 h + v
         double em, fm, om, nbq;
     };
     const bool has_item = tid < 16 * nm;
     const int ic = tid / nm, inu = tid - ic * nm;
     auto kq_of = [&](int q0) { return (int64_t)((k0i + q0) % N0) * NL + kq12; };
-    auto load_unit = [&](int pl, int pc, int m, Unit& d) {
+    auto load_unit = [&](int pl, int pc, int m, int nb, const int (&mj)[MB], Unit& d) {
         // pl: this lane's point (-1: padding); pc: this thread's item point
         const int64_t kql = pl >= 0 ? kq_of(pl) : 0;
-        const cd* Ur = a.U + (kql * nW + m) * nW + 4 * lg;
 #pragma unroll
-        for (int h = 0; h < H; ++h)
+        for (int j = 0; j < MB; ++j) {
+            const cd* Ur = a.U + (kql * nW + mj[j]) * nW + 4 * lg;
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                d.u[4 * h + v] =
-                    (pl >= 0 && 16 * h + 4 * lg + v < nW) ? to_c<C>(Ur[16 * h + v]) : C{0, 0};
+            for (int h = 0; h < H; ++h)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    d.u[j][4 * h + v] = (j < nb && pl >= 0 && 16 * h + 4 * lg + v < nW)
+                                            ? to_c<C>(Ur[16 * h + v])
+                                            : C{0, 0};
+        }
         d.em = d.fm = d.om = d.nbq = 0.0;
-        if (has_item && pc >= 0) {
+        if (MB == 1 && has_item && pc >= 0) {
             const int64_t q = (int64_t)pc * NL + q12;
             const int64_t kq = kq_of(pc);
             d.em = a.eps[kq * nW + m];
@@ -1670,29 +1694,13 @@ line_rates_kernel(RateArgs a) {
     auto item_term = [&](int q0, int c, int nu, double em, double fm, double w, double nbq, int m) {
         const double x = eps_n - em;
         const double y1 = x - w, y2 = x + w;
-        double is2 = inv_s2, cutv = cut, wt = 1.0;
-        if constexpr (VEL) {
-            if (a.vel) {  // adaptive width of the transition (k n) -> (k+q m)
-                const double* vm = a.vel + (kq_of(q0) * nW + m) * 3;
-                double s2 = 0.0;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const double t = a.ad_c[d] * (vn[d] - vm[d]);
-                    s2 += t * t;
-                }
-                const double sg = fmax(a.sigma, sqrt(s2));
-                is2 = 1.0 / (sg * sg);
-                cutv = 27.5 * sg;
-                wt = 1.0 / sg;
-            }
-        }
         // both Gaussians underflow to exactly 0: the term is 0
-        if (fabs(y1) > cutv && fabs(y2) > cutv) return;
+        if (fabs(y1) > cut && fabs(y2) > cut) return;
         const int64_t q = (int64_t)q0 * NL + q12;
         const C* Yr = sY + c * nm;
-        const cd* Eq = a.E + (q * nm + nu) * nm;
+        const cd* Eq = a.E + q * nm * nm + nu;
         C z = {0, 0};
-        for (int sa = 0; sa < nm; ++sa) z = cfma(to_c<C>(Eq[sa]), Yr[sa], z);
+        for (int sa = 0; sa < nm; ++sa) z = cfma(to_c<C>(Eq[sa * nm]), Yr[sa], z);
         if constexpr (POL) {
             if (a.Lpol) {  // + i L(q, nu) O_nm
                 const cd l = a.Lpol[q * nm + nu];
@@ -1701,7 +1709,7 @@ line_rates_kernel(RateArgs a) {
                 z.y += l.x * o.x - l.y * o.y;
             }
         }
-        const double g1 = wt * exp(-y1 * y1 * is2), g2 = wt * exp(-y2 * y2 * is2);
+        const double g1 = exp(-y1 * y1 * inv_s2), g2 = exp(-y2 * y2 * inv_s2);
         const double z2 = cabs2(z);
         const double term = z2 * ((nbq + 1.0 - fm) * g1 + (nbq + fm) * g2);
         gacc += term;
@@ -1712,16 +1720,122 @@ line_rates_kernel(RateArgs a) {
         }
     };
 
+    // what the terms of a band and point share: x = eps_n - eps_m, f_m, 1 / width^2, the
+    // weight 1 / width (adaptive) and the Gaussian's reach
+    auto band_point = [&](int q0, int m) {
+        const int64_t row = kq_of(q0) * nW + m;
+        BandPoint t{eps_n - a.eps[row], a.focc[row], inv_s2, 1.0, cut};
+        if (VEL && a.vel) {  // adaptive width of the transition (k n) -> (k+q m)
+            const double* vm = a.vel + row * 3;
+            double s2 = 0.0;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const double v = a.ad_c[d] * (vn[d] - vm[d]);
+                s2 += v * v;
+            }
+            const double sg = fmax(a.sigma, sqrt(s2));
+            t.is2 = 1.0 / (sg * sg);
+            t.wt = 1.0 / sg;
+            t.cut = 27.5 * sg;
+        }
+        return t;
+    };
+    // rate terms of one item for the bands of a group: E_q is read once for all of them
+    auto item_terms = [&](int q0, int c, int nu, int nb, const int (&mj)[MB]) {
+        const int64_t q = (int64_t)q0 * NL + q12;
+        const uint32_t pm = sPm[q0];
+        const double w = a.omega[q * nm + nu], nbq = a.nb[q * nm + nu];
+        bool on[MB], any = false;
+        C z[MB];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            z[j] = C{0, 0};
+            const BandPoint& t = sB[j * 16 + c];
+            // both Gaussians underflow to exactly 0: the term is 0
+            on[j] = j < nb && ((pm >> mj[j]) & 1u) && !(fabs(t.x - w) > t.cut && fabs(t.x + w) > t.cut);
+            any |= on[j];
+        }
+        if (!any) return;
+        const cd* Eq = a.E + q * nm * nm + nu;
+#pragma unroll 4
+        for (int sa = 0; sa < nm; ++sa) {
+            const C ev = to_c<C>(Eq[sa * nm]);
+#pragma unroll
+            for (int j = 0; j < MB; ++j)
+                if (j < nb) z[j] = cfma(ev, sY[(j * 16 + c) * nm + sa], z[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            if (!on[j]) continue;
+            if constexpr (POL) {
+                if (a.Lpol) {  // + i L(q, nu) O_nm
+                    const cd l = a.Lpol[q * nm + nu];
+                    const cd o = sO[j * 16 + c];
+                    z[j].x -= l.x * o.y + l.y * o.x;
+                    z[j].y += l.x * o.x - l.y * o.y;
+                }
+            }
+            const BandPoint t = sB[j * 16 + c];
+            const double y1 = t.x - w, y2 = t.x + w;
+            const double g1 = t.wt * exp(-y1 * y1 * t.is2), g2 = t.wt * exp(-y2 * y2 * t.is2);
+            const double z2 = cabs2(z[j]);
+            const double term = z2 * ((nbq + 1.0 - t.f) * g1 + (nbq + t.f) * g2);
+            gacc += term;
+            if (a.terms)
+                atomicAdd(&a.terms[((int64_t)st * a.nq_mesh + q) * nm + nu], a.terms_scale * term);
+            if constexpr (LW) {
+                if (a.lw) sLW[q0 * nm + nu] += mdf * z2 * g1;  // one thread per (q0, nu) per unit
+            }
+        }
+    };
+
     __syncthreads();  // sPm, sP
+    auto units_of = [&](uint32_t mask) {
+        int n = 0;
+        for (int w0 = 0; w0 < N0; w0 += 64) {
+            const int p = w0 + lane;
+            n += __popcll(__ballot(p < N0 && (sPm[min(p, N0 - 1)] & mask)));
+        }
+        return (n + 15) >> 4;
+    };
     while (bands) {
         const int m = __builtin_ctz(bands);
-        bands &= bands - 1;
-        // live points of band m, ascending
+        // the group: bands from m on, as long as one list for all of them is cheaper than a
+        // list for the next band by itself (the MFMA part of a unit counts 2, each band's
+        // contraction and terms 1)
+        uint32_t gm = bands & (0u - bands);
+        int nb = 1;
+        int mj[MB];
+        mj[0] = m;
+#pragma unroll
+        for (int j = 1; j < MB; ++j) mj[j] = m;
+        if constexpr (MB > 1) {
+            int ug = units_of(gm);
+            bool open = true;
+#pragma unroll
+            for (int j = 1; j < MB; ++j) {
+                const uint32_t rest = bands & ~gm;
+                if (open && rest) {
+                    const uint32_t b1 = rest & (0u - rest);
+                    const int u1 = units_of(gm | b1);
+                    if (u1 * (3 + nb) <= ug * (2 + nb) + 3 * units_of(b1)) {
+                        gm |= b1;
+                        ug = u1;
+                        mj[j] = __builtin_ctz(b1);
+                        ++nb;
+                    } else {
+                        open = false;
+                    }
+                }
+            }
+        }
+        bands &= ~gm;
+        // live points of the group, ascending
         if (wave == 0) {
             int base = 0;
             for (int w0 = 0; w0 < N0; w0 += 64) {
                 const int p = w0 + lane;
-                const bool bit = p < N0 && ((sPm[p] >> m) & 1u);
+                const bool bit = p < N0 && (sPm[p] & gm);
                 const uint64_t bal = __ballot(bit);
                 if (bit) sList[base + __popcll(bal & ((1ull << lane) - 1ull))] = p;
                 base += __popcll(bal);
@@ -1735,7 +1849,16 @@ line_rates_kernel(RateArgs a) {
             const int pl = g + li < cnt ? sList[g + li] : -1;
             const int pc = has_item && g + ic < cnt ? sList[g + ic] : -1;
             Unit d;
-            load_unit(pl, pc, m, d);
+            load_unit(pl, pc, m, nb, mj, d);
+            if constexpr (MB > 1) {
+                for (int i = tid; i < MB * 16; i += BT) {
+                    const int j = i >> 4, c = i & 15;
+                    int mm = m;
+#pragma unroll
+                    for (int jj = 1; jj < MB; ++jj) mm = j == jj ? mj[jj] : mm;
+                    if (j < nb && g + c < cnt) sB[i] = band_point(sList[g + c], mm);
+                }
+            }
             const int prow = (pl >= 0 ? pl : N0) * Ws;
             // X^T tiles of the unit's points and Y, two column tiles at a time
 #pragma unroll
@@ -1781,60 +1904,72 @@ line_rates_kernel(RateArgs a) {
                 // Y[slot li, sa] = sum_b X[slot li, sa, b] U_{k+q}[b, m]: products over
                 // the lane's four b, then the sum over the four rows; rows 0/1 receive
                 // Re Y of tiles t/t+1, rows 2/3 Im Y of tiles t/t+1.
-                R pr[P], pi[P];
 #pragma unroll
-                for (int t = 0; t < P; ++t) {
-                    const C* uu = d.u + (H == 2 ? 4 * t : 0);  // H = 2: tile t is half t
-                    R xr = 0, xi = 0;
+                for (int j = 0; j < MB; ++j) {
+                    if (j >= nb) break;
+                    C* sYj = sY + j * 16 * nm;
+                    R pr[P], pi[P];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        xr += cr[t][v] * uu[v].x - ci[t][v] * uu[v].y;
-                        xi += cr[t][v] * uu[v].y + ci[t][v] * uu[v].x;
+                    for (int t = 0; t < P; ++t) {
+                        const C* uu = d.u[j] + (H == 2 ? 4 * t : 0);  // H = 2: tile t is half t
+                        R xr = 0, xi = 0;
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            xr += cr[t][v] * uu[v].x - ci[t][v] * uu[v].y;
+                            xi += cr[t][v] * uu[v].y + ci[t][v] * uu[v].x;
+                        }
+                        pr[t] = xr;
+                        pi[t] = xi;
                     }
-                    pr[t] = xr;
-                    pi[t] = xi;
-                }
-                if constexpr (H == 1) {
+                    if constexpr (H == 1) {
 #pragma unroll
-                    for (int t = 0; t < P; t += 2) {
-                        const R y = rows4_reduce_scatter(pr[t], t + 1 < P ? pr[t + 1] : R(0), pi[t],
-                                                         t + 1 < P ? pi[t + 1] : R(0));
-                        const int tt = t0 + t + (lg & 1);
-                        const int sa = wave * TN + tt;
-                        if (t + (lg & 1) < P && tt < TN && sa < nm)
-                            reinterpret_cast<R*>(sY + li * nm + sa)[lg >> 1] = y;
+                        for (int t = 0; t < P; t += 2) {
+                            const R y = rows4_reduce_scatter(pr[t], t + 1 < P ? pr[t + 1] : R(0), pi[t],
+                                                             t + 1 < P ? pi[t + 1] : R(0));
+                            const int tt = t0 + t + (lg & 1);
+                            const int sa = wave * TN + tt;
+                            if (t + (lg & 1) < P && tt < TN && sa < nm)
+                                reinterpret_cast<R*>(sYj + li * nm + sa)[lg >> 1] = y;
+                        }
+                    } else {
+                        // both halves of mode sa: Y is their sum; rows 0 and 2 receive Re and Im
+                        const R y = rows4_reduce_scatter(pr[0] + pr[1], R(0), pi[0] + pi[1], R(0));
+                        const int sa = (wave * TN + t0) >> 1;
+                        if (!(lg & 1) && sa < nm) reinterpret_cast<R*>(sYj + li * nm + sa)[lg >> 1] = y;
                     }
-                } else {
-                    // both halves of mode sa: Y is their sum; rows 0 and 2 receive Re and Im
-                    const R y = rows4_reduce_scatter(pr[0] + pr[1], R(0), pi[0] + pi[1], R(0));
-                    const int sa = (wave * TN + t0) >> 1;
-                    if (!(lg & 1) && sa < nm) reinterpret_cast<R*>(sY + li * nm + sa)[lg >> 1] = y;
                 }
             }
             if constexpr (POL) {
                 if (a.Lpol) {  // O at point li: sum over the lane's four b, then over the rows
-                    cd o = {0.0, 0.0};
 #pragma unroll
-                    for (int v = 0; v < 4 * H; ++v)
-                        o = cfmac(ukn[v], cd{(double)d.u[v].x, (double)d.u[v].y}, o);
-                    o.x += __shfl_xor(o.x, 16, 64);
-                    o.y += __shfl_xor(o.y, 16, 64);
-                    o.x += __shfl_xor(o.x, 32, 64);
-                    o.y += __shfl_xor(o.y, 32, 64);
-                    if (wave == 0 && lg == 0) sO[li] = o;
+                    for (int j = 0; j < MB; ++j) {
+                        cd o = {0.0, 0.0};
+#pragma unroll
+                        for (int v = 0; v < 4 * H; ++v)
+                            o = cfmac(ukn[v], cd{(double)d.u[j][v].x, (double)d.u[j][v].y}, o);
+                        o.x += __shfl_xor(o.x, 16, 64);
+                        o.y += __shfl_xor(o.y, 16, 64);
+                        o.x += __shfl_xor(o.x, 32, 64);
+                        o.y += __shfl_xor(o.y, 32, 64);
+                        if (wave == 0 && lg == 0) sO[j * 16 + li] = o;
+                    }
                 }
             }
             __syncthreads();
             // Z[c, nu] = sum_sa E_q[sa, nu] Y[c, sa] and the rate terms
-            if (pc >= 0) item_term(pc, ic, inu, d.em, d.fm, d.om, d.nbq, m);
-            for (int it = tid + BT; it < 16 * nm; it += BT) {
+            if (MB == 1 && pc >= 0) item_term(pc, ic, inu, d.em, d.fm, d.om, d.nbq, m);
+            for (int it = MB == 1 ? tid + BT : tid; it < 16 * nm; it += BT) {
                 const int c = it / nm, nu = it - c * nm;
                 if (g + c >= cnt) continue;
                 const int q0 = sList[g + c];
-                const int64_t q = (int64_t)q0 * NL + q12;
-                const int64_t kq = kq_of(q0);
-                item_term(q0, c, nu, a.eps[kq * nW + m], a.focc[kq * nW + m], a.omega[q * nm + nu],
-                          a.nb[q * nm + nu], m);
+                if constexpr (MB > 1) {
+                    item_terms(q0, c, nu, nb, mj);
+                } else {
+                    const int64_t q = (int64_t)q0 * NL + q12;
+                    const int64_t kq = kq_of(q0);
+                    item_term(q0, c, nu, a.eps[kq * nW + m], a.focc[kq * nW + m], a.omega[q * nm + nu],
+                              a.nb[q * nm + nu], m);
+                }
             }
             __syncthreads();  // sY (and the list, after a band's last unit) are rewritten
         }
@@ -1861,11 +1996,15 @@ line_rates_kernel(RateArgs a) {
     }
 }
 
-size_t line_rates_lds(int W, int N0, int nm, bool f32, bool lw) {
+static size_t line_lds(int W, int N0, int nm, bool f32, bool lw, int mb) {
     const int Wp = (W + 3) & ~3;
-    return ((size_t)(N0 + 1) * (Wp + 1) + 16 * (size_t)nm) * (f32 ? sizeof(cf) : sizeof(cd)) +
+    return ((size_t)(N0 + 1) * (Wp + 1) + 16 * (size_t)nm * mb) * (f32 ? sizeof(cf) : sizeof(cd)) +
            2 * (size_t)N0 * sizeof(uint32_t) +
            (lw ? sizeof(uint32_t) * (size_t)(N0 & 1) + (size_t)N0 * nm * sizeof(double) : 0);
+}
+
+size_t line_rates_lds(int W, int N0, int nm, bool f32, bool lw) {
+    return line_lds(W, N0, nm, f32, lw, 1);
 }
 
 // Columns of the factorised form, 4 waves x TN tiles of 16 (or 2 x 2 TN): one tile per mode index
@@ -1882,9 +2021,12 @@ int line_rates_ncpad(int nm, int nW) {
 
 template <int TN, int KS, class C, int FEAT, int H = 1, int NWV = 4>
 static hipError_t go_line(const RateArgs& a, int nst, hipStream_t s) {
-    const size_t shm = line_rates_lds(a.W, a.mesh.n0, a.nm, sizeof(C) == sizeof(cf), a.lw != nullptr);
-    if (shm > 64 * 1024) return hipErrorInvalidValue;
-    hipError_t e = hipFuncSetAttribute((const void*)line_rates_kernel<TN, KS, C, FEAT, H, NWV>,
+    if (line_rates_lds(a.W, a.mesh.n0, a.nm, sizeof(C) == sizeof(cf), a.lw != nullptr) > 64 * 1024)
+        return hipErrorInvalidValue;
+    constexpr int MB = line_bands_at_once<FEAT, H>();
+    // (the further bands' Y: up to 16 KB above that limit, within a CU's 160 KB)
+    const size_t shm = line_lds(a.W, a.mesh.n0, a.nm, sizeof(C) == sizeof(cf), a.lw != nullptr, MB);
+    hipError_t e = hipFuncSetAttribute((const void*)line_rates_kernel<TN, KS, C, FEAT, H, NWV, MB>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
     const int64_t NL = (int64_t)a.mesh.n1 * a.mesh.n2;
@@ -1905,7 +2047,7 @@ static hipError_t go_line(const RateArgs& a, int nst, hipStream_t s) {
         b.line_bands = a.line_bands + (int64_t)s0 * NL;
         if (a.lw) b.lw = a.lw + (int64_t)s0 * NL * a.mesh.n0 * a.nm;
         b.n_states = ns;
-        hipLaunchKernelGGL((line_rates_kernel<TN, KS, C, FEAT, H, NWV>),
+        hipLaunchKernelGGL((line_rates_kernel<TN, KS, C, FEAT, H, NWV, MB>),
                            dim3((unsigned)(groups * 8 * ns)), dim3(64 * NWV), shm, s, b);
     }
     return hipGetLastError();

@@ -345,6 +345,40 @@ def test_adaptive_rates_and_linewidth_match_oracle(lib, form, nW, nat):
     assert mx < P_BOUND and mp < P_BOUND
 
 
+@pytest.mark.parametrize("nW,nat,mesh,scale,smin", [
+    (6, 2, (70, 2, 3), 1.0, 0.01),   # more points a line than a wave has lanes
+    (16, 5, (18, 3, 2), 0.5, 1e-4),  # two waves; groups that close before they are full
+    (16, 5, (5, 2, 2), 8.0, 0.5),    # every band live everywhere: full groups and a remainder
+    (20, 4, (17, 2, 3), 1.0, 0.01),  # two tiles a mode, pairs of bands
+    (3, 1, (1, 4, 3), 1.0, 0.01),
+])
+def test_adaptive_band_groups(lib, nW, nat, mesh, scale, smin):
+    """Several final bands on one list of points against the direct sum, which takes them
+    by themselves: rates and linewidths."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(97 + nW, n_wannier=nW, n_atoms=nat, r=1)
+    s.h_r *= 0.3
+    t, par = _params(s, mesh, sigma=smin)
+    par = dict(par, smearing="adaptive", adaptive_scale=scale)
+    ds = DeviceSystem.from_host(s)
+    N = int(np.prod(mesh))
+    out = {}
+    try:
+        for form in ("direct", "factored"):
+            lib.set_mesh_sum(form)
+            gam = torch.zeros((N, nW), dtype=torch.float64, device="cuda")
+            P = torch.zeros((N, s.n_modes), dtype=torch.float64, device="cuda")
+            lib.scatter_rates(ds, mesh, par, gam)
+            lib.phonon_linewidth(ds, mesh, par, P)
+            out[form] = gam.cpu().numpy(), P.cpu().numpy()
+    finally:
+        lib.set_mesh_sum("auto")
+    assert np.max(out["direct"][0]) > 0
+    for a, b in zip(out["factored"], out["direct"]):
+        assert rel_err(a, b)[0] < 1e-10
+
+
 # ---------------------------------------------------------------------------
 # 3-phonon coupling
 # ---------------------------------------------------------------------------
