@@ -327,6 +327,7 @@ __device__ inline void eig_sync() {
 
 struct JacobiRot {
     double c, sx, sy;  // c and s e^{i phi}; (1, 0, 0) for a pair left alone
+    double dlt;        // A'_ff = A_ff - dlt, A'_gg = A_gg + dlt
 };
 
 // 1 / sqrt(x) for x > 0: the hardware's estimate y (about 2^-23) and the series
@@ -353,7 +354,7 @@ __device__ inline JacobiRot jacobi_rot(double a, double d, cd b, bool swapped, d
     // test alone, pairs next to a zero eigenvalue keep rotating on rounding noise and the
     // off-diagonal norm never falls below the stopping level.
     const bool rot = bb2 > fmax(eps2 * fabs(a * d), skip_abs) && bb2 > 0.0;
-    return rot ? JacobiRot{cc * ic, s * b.x, s * b.y} : JacobiRot{1.0, 0.0, 0.0};
+    return rot ? JacobiRot{cc * ic, s * b.x, s * b.y, bb2 * (s * ic)} : JacobiRot{1.0, 0.0, 0.0, 0.0};
 }
 
 // The rotation of a sorted pair p < q in the form c, s = t c, e = e^{i phi} with
@@ -556,8 +557,8 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
             JacobiRot ri, rj;
             if constexpr (NW == 1) {
                 const int si = base + I * (H + 1), sj = base + J * (H + 1);
-                ri = JacobiRot{__shfl(rd.c, si, 64), __shfl(rd.sx, si, 64), __shfl(rd.sy, si, 64)};
-                rj = JacobiRot{__shfl(rd.c, sj, 64), __shfl(rd.sx, sj, 64), __shfl(rd.sy, sj, 64)};
+                ri = JacobiRot{__shfl(rd.c, si, 64), __shfl(rd.sx, si, 64), __shfl(rd.sy, si, 64), 0.0};
+                rj = JacobiRot{__shfl(rd.c, sj, 64), __shfl(rd.sx, sj, 64), __shfl(rd.sy, sj, 64), 0.0};
             } else {
                 if (act && I == J) {
                     sprm[I][0] = rd.c;
@@ -565,8 +566,8 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
                     sprm[I][2] = rd.sy;
                 }
                 __syncthreads();  // (and every block has been read)
-                ri = JacobiRot{sprm[I][0], sprm[I][1], sprm[I][2]};
-                rj = JacobiRot{sprm[J][0], sprm[J][1], sprm[J][2]};
+                ri = JacobiRot{sprm[I][0], sprm[I][1], sprm[I][2], 0.0};
+                rj = JacobiRot{sprm[J][0], sprm[J][1], sprm[J][2], 0.0};
             }
             const bool any = ri.sx != 0.0 || ri.sy != 0.0;
             rotated = rotated || any;
@@ -577,6 +578,7 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
             auto rot_g = [](double c, double sx, double sy, cd u, cd w) {  // conj(s) u + c w
                 return cd{fma(c, w.x, fma(sy, u.y, sx * u.x)), fma(c, w.y, fma(sx, u.y, -sy * u.x))};
             };
+            const double af = x00.x - rd.dlt, ag = x11.x + rd.dlt;
             const cd y00 = rot_f(ri.c, ri.sx, ri.sy, x00, x10), y01 = rot_f(ri.c, ri.sx, ri.sy, x01, x11);
             const cd y10 = rot_g(ri.c, ri.sx, ri.sy, x00, x10), y11 = rot_g(ri.c, ri.sx, ri.sy, x01, x11);
             // columns: A'_f = c A_f - s conj(e) A_g ; A'_g = s e A_f + c A_g ; V the same
@@ -584,9 +586,12 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
             x01 = rot_g(rj.c, rj.sx, -rj.sy, y00, y01);
             x10 = rot_f(rj.c, rj.sx, -rj.sy, y10, y11);
             x11 = rot_g(rj.c, rj.sx, -rj.sy, y10, y11);
-            if (I == J && any) {  // the rotated pair: exact zero off the diagonal
+            // the rotated pair: exact zero off the diagonal, and a diagonal changed by t |A_fg|
+            // only: multiplied by c^2 and s^2 it would gather their rounding at every rotation
+            if (I == J && any) {
                 x01 = x10 = cd{0.0, 0.0};
-                x00.y = x11.y = 0.0;
+                x00 = cd{af, 0.0};
+                x11 = cd{ag, 0.0};
             }
             z00 = rot_f(rj.c, rj.sx, -rj.sy, vf0, vg0);
             z01 = rot_g(rj.c, rj.sx, -rj.sy, vf0, vg0);
