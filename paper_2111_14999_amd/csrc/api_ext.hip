@@ -61,7 +61,6 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
             cd* S = ar.take<cd>((size_t)qb * n2 * m3);
             cd* T = ar.take<cd>((size_t)qb * n2 * m3);
             cd* X = ar.take<cd>((size_t)nqp * m3);
-            cd* Y = ar.take<cd>((size_t)nqp * m3);
             {
                 Arena a1 = ar, a2 = ar, a3 = ar;
                 phonon_dev(h, a1, &ph, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, omega_min, 0.0, w1, E1,
@@ -91,9 +90,8 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
                     Timer t2(h, s, "v3_stage2");
                     HIPCHK(h, launch_zgemm(P2, n2, T + i * n2 * m3, m3, X, m3, nqp, m3, n2, s));
                     t2.done();
-                    HIPCHK(h, launch_v3_rot1(X, nqp, nm, E2, Y, s));
-                    HIPCHK(h, launch_v3_rot2(Y, nqp, nm, E3 + iq * nqp * nm * nm,
-                                             reinterpret_cast<cd*>(v3_out) + iq * nqp * m3, s));
+                    HIPCHK(h, launch_v3_rot(X, nqp, nm, E2, E3 + iq * nqp * nm * nm,
+                                            reinterpret_cast<cd*>(v3_out) + iq * nqp * m3, s));
                 }
             }
         };

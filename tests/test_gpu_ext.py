@@ -407,6 +407,28 @@ def test_v3_matches_oracle(lib, nat):
     assert werr < 1e-10
 
 
+@pytest.mark.parametrize("nat", [3, 4, 5, 6, 7, 8, 9, 10])
+def test_v3_rotation_tiles(lib, nat):
+    """Every mode count of the rotation kernel (whole and split over nu) against the oracle."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem3
+    s = synth.small_system(50 + nat, n_wannier=1, n_atoms=nat, r=1)
+    r, phi3 = synth.third_order_constants(50 + nat, nat)
+    keep = np.flatnonzero(np.abs(r).sum(axis=1) <= 1)[:3]  # (three vectors: the oracle's size)
+    r = np.ascontiguousarray(r[keep])
+    phi3 = np.ascontiguousarray(phi3[np.ix_(keep, keep)])
+    s.r1, s.r2, s.phi3 = r, r, phi3
+    g = np.random.default_rng(nat)
+    q, qp = g.uniform(-1, 1, size=(2, 3)), g.uniform(-1, 1, size=(3, 3))
+    ref = np.abs(phonon3.interp_v3(q, qp, s)["v3"])
+    nm = 3 * nat
+    V = torch.zeros((2, 3, nm, nm, nm), dtype=torch.complex128, device="cuda")
+    lib.interp_v3(DeviceSystem3.from_host(s, r, phi3), torch.from_numpy(q).cuda(),
+                  torch.from_numpy(qp).cuda(), V)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(np.abs(V.cpu().numpy()) - ref)) < V3_BOUND * np.max(ref)
+
+
 # ---------------------------------------------------------------------------
 # Philox streams, initialisation, training set, gather
 # ---------------------------------------------------------------------------
