@@ -1409,17 +1409,18 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                     rb.line_bands = lineany;
                     // live bands of every (state, line, chunk) first: T2 is formed for live lines only
                     HIPCHK(h, launch_line_live(rb, nn, livebuf, lineany, nl, s));
+                    const AxisCols acols{nW <= 16 ? 16 : 32, nW, nm};  // F's columns in use
                     Timer ta(h, s, "axis_transforms");
                     if (lowp)
                         HIPCHK(h, launch_axis_transforms_f32(
                                       reinterpret_cast<const cf*>(Fbuf) + (int64_t)sb * rp_pad * nc_pad,
                                       rp_pad, nc_pad, T.box_rp, rmax_p, mesh, T.Pax, nn, lineany,
-                                      reinterpret_cast<cf*>(T1buf), reinterpret_cast<cf*>(T2buf), s));
+                                      reinterpret_cast<cf*>(T1buf), reinterpret_cast<cf*>(T2buf), s, acols));
                     else
                         HIPCHK(h, launch_axis_transforms(
                                       reinterpret_cast<const cd*>(Fbuf) + (int64_t)sb * rp_pad * nc_pad,
                                       rp_pad, nc_pad, T.box_rp, rmax_p, mesh, T.Pax, nn, lineany,
-                                      reinterpret_cast<cd*>(T1buf), reinterpret_cast<cd*>(T2buf), s));
+                                      reinterpret_cast<cd*>(T1buf), reinterpret_cast<cd*>(T2buf), s, acols));
                     // F read once, T2 written for the live lines; T1 written and read once
                     // unless both axes ran in one pass
                     const double ab = (double)g_elem * nm * nW;

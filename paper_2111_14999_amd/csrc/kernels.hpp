@@ -122,16 +122,22 @@ hipError_t launch_box_rows(const int32_t* R, int n, int rmax, int32_t* box, hipS
 hipError_t launch_axis_phases_f32(Mesh m, int rmax, cf* P, hipStream_t s);  // rounded to FP32
 // T1 (axis 2) and T2 (axis 1) of the factorised full-mesh sum over Rp.
 // line_any (nullable): [nst, N1*N2]; T2 of a line whose entry is 0 is not formed.
+// Columns in use: rows x live, live of every per columns (per = 0: all).  The one-pass
+// form neither reads nor writes the others.
+struct AxisCols {
+    int per = 0, live = 0, rows = 0;
+};
 hipError_t launch_axis_transforms(const cd* F, int rp_pad, int nc_pad, const int32_t* box_rp,
                                   int rmax, Mesh m, const cd* P, int nst, const uint32_t* line_any,
-                                  cd* T1, cd* T2, hipStream_t s);
+                                  cd* T1, cd* T2, hipStream_t s, AxisCols cols = {});
 // With line_any set, a box of width 1, 3, 5, 7 or 9 whose F slab (W^2 x 64 columns)
 // fits 64 KB of LDS and nc_pad % 64 == 0, both axes run in one pass and T1 is not
 // used (T1 may then be null); this tells which route a call takes.
 bool axis_transforms_fused(int rmax, int nc_pad, bool f32);
 hipError_t launch_axis_transforms_f32(const cf* F, int rp_pad, int nc_pad, const int32_t* box_rp,
                                       int rmax, Mesh m, const cd* P, int nst,
-                                      const uint32_t* line_any, cf* T1, cf* T2, hipStream_t s);
+                                      const uint32_t* line_any, cf* T1, cf* T2, hipStream_t s,
+                                      AxisCols cols = {});
 // The last axis written out for q0 in [q0a, q0b) of one T2 [W, N1*N2, nc_pad]:
 // X [(q0 - q0a) N1 N2 + line, c] (rows ldx apart, c < nc); P as for the transforms.
 hipError_t launch_axis0_out(const cd* T2, Mesh m, int nc_pad, int nc, int rmax, const cd* P,

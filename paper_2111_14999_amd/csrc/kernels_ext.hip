@@ -22,7 +22,7 @@ static inline unsigned grid_n(int64_t n, int block) {
 // D is linear in K: the sum over G leaves only S = sum_G w(G) K(G), and D = Z^T S.  A point
 // has kPolarLanes lanes, which share the G and then the modes; a thread per point, with a
 // D of its own to add to for each G, left most of the chip idle (9,384 points, 343 G,
-// 3 atoms: 335 us; PFNEW us so, bound by the exponentials and divisions).
+// 3 atoms: 335 us; 26 us so, bound by the exponentials and divisions).
 constexpr int kPolarLanes = 16;
 
 __global__ __launch_bounds__(256) void polar_factor_kernel(const double* frac, Mesh m, int64_t np,
@@ -737,7 +737,7 @@ hipError_t launch_v3_fold(const cd* S, int64_t nq, int nr, int nm, const cd* E1,
 // the work-group's, so they come through the scalar cache and take no LDS reads); Y is
 // turned in LDS, and thread (nu, nu') does the same over c.  Memory sees X once and V
 // once: 15 modes, 1,024 j, 110 MB and 0.8 GFLOP, a kernel per rotation with a thread per
-// element 132 us, V3ROTNEW us so.
+// element 132 us, 50 us so.
 template <int NM>
 struct V3Rot {
     static constexpr int LD = NM | 1;  // odd: rows of 16-byte elements start on different banks

@@ -166,7 +166,9 @@ __global__ __launch_bounds__(256) void axis_mid_kernel(const C* __restrict__ in,
 // live lines.  The sums run in the same order as axis2 then axis_mid, so the two
 // routes agree bit for bit; T1 never goes through HBM.  Wave g of the work-group
 // (64 lanes, one column each) takes q2 = g, g + kAxisWaves, ...  Eight waves
-// share one slab and the kernel is compiled for six waves per SIMD (80 VGPRs), so
+// share one slab, of 64 columns that are used (the padding of F's layout, a sixteenth of
+// it for 15 modes of 16 bands and more than half for 9 of 9, is left out: its T2 is never
+// written), and the kernel is compiled for six waves per SIMD (80 VGPRs), so
 // that three work-groups (three FP64 slabs of a box 7 wide) fill a CU.
 constexpr int kAxisWaves = 8;
 
@@ -176,11 +178,12 @@ __global__ __launch_bounds__(64 * kAxisWaves, 6) void axis_fused_kernel(const C*
                                                          Mesh m, const cd* __restrict__ P1,
                                                          const cd* __restrict__ P2,
                                                          const uint32_t* __restrict__ line_any,
-                                                         int qsplit, C* __restrict__ T2) {
+                                                         int qsplit, AxisCols cols,
+                                                         C* __restrict__ T2) {
     constexpr int W = WT;
     extern __shared__ char smem_raw[];
     C* sF = reinterpret_cast<C*>(smem_raw);  // [W * W][64]
-    const int ncb = nc_pad / 64;
+    const int nlive = cols.rows * cols.live, ncb = (nlive + 63) / 64;
     int64_t b = blockIdx.x;
     const int qs = (int)(b % qsplit);  // this work-group's share of the q2 values
     b /= qsplit;
@@ -189,7 +192,9 @@ __global__ __launch_bounds__(64 * kAxisWaves, 6) void axis_fused_kernel(const C*
     const int r0 = (int)(b % W);
     const int st = (int)(b / W);
     const int tid = threadIdx.x, cc = tid & 63, g = tid >> 6;
-    const int c = cb * 64 + cc;
+    const int cl = cb * 64 + cc;  // this lane's column among those that are used
+    const bool in = cl < nlive;
+    const int c = in ? cl / cols.live * cols.per + cl % cols.live : 0;
     const C* Fs = F + (int64_t)st * rp_pad * nc_pad + c;
     for (int i = g; i < W * W; i += kAxisWaves) {
         const int row = box_rp[r0 * W * W + i];
@@ -219,7 +224,7 @@ __global__ __launch_bounds__(64 * kAxisWaves, 6) void axis_fused_kernel(const C*
             C acc = {0, 0};
 #pragma unroll
             for (int r1 = 0; r1 < W; ++r1) acc = cfma(to_c<C>(Pn[r1]), t1[r1], acc);
-            st_vec(out + (int64_t)line * nc_pad, acc);
+            if (in) st_vec(out + (int64_t)line * nc_pad, acc);
         }
     }
 }
@@ -227,7 +232,7 @@ __global__ __launch_bounds__(64 * kAxisWaves, 6) void axis_fused_kernel(const C*
 template <int WT, class C>
 static hipError_t go_axes(const C* F, int rp_pad, int nc_pad, const int32_t* box_rp, int W,
                           Mesh m, const cd* P1, const cd* P2, int nst, const uint32_t* line_any,
-                          C* T1, C* T2, hipStream_t s) {
+                          C* T1, C* T2, hipStream_t s, AxisCols cols) {
     // one pass where the box is a compile-time width, the F slab fits 64 KB of LDS
     // and the columns come in 64-wide blocks
     if constexpr (WT > 0) {
@@ -238,7 +243,7 @@ static hipError_t go_axes(const C* F, int rp_pad, int nc_pad, const int32_t* box
             if (e != hipSuccess) return e;
             // a few states make few work-groups: split the q2 values of a slab over up to
             // ceil(N2 / waves) work-groups (each reloads the slab) until the grid fills the chip
-            const int64_t base = (int64_t)nst * WT * (nc_pad / 64);
+            const int64_t base = (int64_t)nst * WT * ((cols.rows * cols.live + 63) / 64);
             const int qmax = (m.n2 + kAxisWaves - 1) / kAxisWaves;
             int qsplit = 1;
             while (qsplit < qmax && base * qsplit < 2048) ++qsplit;
@@ -246,7 +251,7 @@ static hipError_t go_axes(const C* F, int rp_pad, int nc_pad, const int32_t* box
             if (groups > 2147483647LL) return hipErrorInvalidValue;
             hipLaunchKernelGGL((axis_fused_kernel<WT, C>), dim3((unsigned)groups), dim3(64 * kAxisWaves),
                                shm, s,
-                               F, rp_pad, nc_pad, box_rp, m, P1, P2, line_any, qsplit, T2);
+                               F, rp_pad, nc_pad, box_rp, m, P1, P2, line_any, qsplit, cols, T2);
             return hipGetLastError();
         }
     }
@@ -264,19 +269,22 @@ static hipError_t go_axes(const C* F, int rp_pad, int nc_pad, const int32_t* box
 template <class C>
 static hipError_t axis_transforms(const C* F, int rp_pad, int nc_pad, const int32_t* box_rp,
                                   int rmax, Mesh m, const cd* P, int nst, const uint32_t* line_any,
-                                  C* T1, C* T2, hipStream_t s) {
+                                  C* T1, C* T2, hipStream_t s, AxisCols cols) {
     const int W = 2 * rmax + 1;
-    if (W > kMaxW) return hipErrorInvalidValue;
+    if (cols.per == 0) cols = AxisCols{nc_pad, nc_pad, 1};
+    if (W > kMaxW || cols.live < 1 || cols.live > cols.per || cols.rows < 1 ||
+        (int64_t)cols.rows * cols.per > nc_pad)
+        return hipErrorInvalidValue;
     if (nst <= 0) return hipSuccess;
     const cd* P1 = P + (int64_t)m.n0 * W;
     const cd* P2 = P1 + (int64_t)m.n1 * W;
     switch (W) {
-        case 1: return go_axes<1, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s);
-        case 3: return go_axes<3, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s);
-        case 5: return go_axes<5, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s);
-        case 7: return go_axes<7, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s);
-        case 9: return go_axes<9, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s);
-        default: return go_axes<0, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s);
+        case 1: return go_axes<1, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s, cols);
+        case 3: return go_axes<3, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s, cols);
+        case 5: return go_axes<5, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s, cols);
+        case 7: return go_axes<7, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s, cols);
+        case 9: return go_axes<9, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s, cols);
+        default: return go_axes<0, C>(F, rp_pad, nc_pad, box_rp, W, m, P1, P2, nst, line_any, T1, T2, s, cols);
     }
 }
 
@@ -505,13 +513,14 @@ bool axis_transforms_fused(int rmax, int nc_pad, bool f32) {
 
 hipError_t launch_axis_transforms(const cd* F, int rp_pad, int nc_pad, const int32_t* box_rp,
                                   int rmax, Mesh m, const cd* P, int nst, const uint32_t* line_any,
-                                  cd* T1, cd* T2, hipStream_t s) {
-    return axis_transforms<cd>(F, rp_pad, nc_pad, box_rp, rmax, m, P, nst, line_any, T1, T2, s);
+                                  cd* T1, cd* T2, hipStream_t s, AxisCols cols) {
+    return axis_transforms<cd>(F, rp_pad, nc_pad, box_rp, rmax, m, P, nst, line_any, T1, T2, s, cols);
 }
 hipError_t launch_axis_transforms_f32(const cf* F, int rp_pad, int nc_pad, const int32_t* box_rp,
                                       int rmax, Mesh m, const cd* P, int nst,
-                                      const uint32_t* line_any, cf* T1, cf* T2, hipStream_t s) {
-    return axis_transforms<cf>(F, rp_pad, nc_pad, box_rp, rmax, m, P, nst, line_any, T1, T2, s);
+                                      const uint32_t* line_any, cf* T1, cf* T2, hipStream_t s,
+                                      AxisCols cols) {
+    return axis_transforms<cf>(F, rp_pad, nc_pad, box_rp, rmax, m, P, nst, line_any, T1, T2, s, cols);
 }
 
 // ---------------------------------------------------------------------------
@@ -1520,15 +1529,15 @@ constexpr int line_waves_per_simd() {
 // holds 2 x 159 VGPRs per lane instead of 4 x 127, so six (state, line) pairs are
 // resident per CU instead of four (measured on the realistic workload: 2.45 ms per
 // launch against 2.68 ms; one wave of sixteen tiles, 2.47 ms; two waves loading
-// T2 per K step, 2.73 ms).  The plain rates of two and three tiles per wave take the
-// two-wave form as well (the batched plan of 32 systems: 137.9 -> 133.9 ms), and so do
-// the linewidth and adaptive-width variants (phonon linewidth 107 -> 101.5 ms, adaptive
-// rates 541 -> 478 ms per step) and, at two waves per SIMD (181 VGPRs; four
-// pairs per CU against three), the polar one (3.29 -> 3.16 ms per launch); with two
+// T2 per K step, 2.73 ms).  The forms of two and three tiles per wave take two waves as
+// well (20^3 mesh, 9 bands, 9 modes: polar 1.60 -> 1.40 ms a call, linewidths 1.70 -> 1.59,
+// adaptive 6.78 -> 5.16; 8 bands, 6 modes: 1.15 -> 0.98, 1.26 -> 1.18, 4.82 -> 3.50), and so
+// do the linewidth, adaptive and, at two waves per SIMD, polar variants of four (107 -> 101.5,
+// 541 -> 478 ms per step, 3.29 -> 3.16 ms per launch); with two
 // tiles per mode (16 < nW <= 32) the plain rates of one and two modes per wave, the
-// latter in FP32 (batched plan 133.4 -> 132.1 ms); and the plain rates of six and eight
-// tiles per wave, whose T2 is read per K step (12 and 16 tiles in two waves: 132.1 ->
-// 129.9 ms), with one or two tiles per mode (-> 128.6 ms).
+// latter in FP32 (batched plan of 32 systems 133.4 -> 132.1 ms); and the plain rates of six
+// and eight tiles per wave, whose T2 is read per K step (12 and 16 tiles in two waves:
+// 132.1 -> 129.9 ms), with one or two tiles per mode (-> 128.6 ms).
 template <int TN, int KS, class C, int FEAT, int H = 1, int NWV = 4, int MB = 1>
 __global__ __launch_bounds__(64 * NWV, (line_waves_per_simd<FEAT, H, sizeof(C) == sizeof(cd), NWV, MB>())) void
 line_rates_kernel(RateArgs a) {
@@ -1575,7 +1584,7 @@ line_rates_kernel(RateArgs a) {
     const int st = (int)(j % nst);
     if (line >= NL) return;
     uint32_t bands = __builtin_amdgcn_readfirstlane(a.line_bands[(int64_t)st * NL + line]);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (!bands) return;  // its partial sum is 0 (written with the masks)
     const int q1 = line / mesh.n2, q2 = line - q1 * mesh.n2;
     const int li = lane & 15, lg = lane >> 4;
@@ -1612,8 +1621,13 @@ line_rates_kernel(RateArgs a) {
     }
     // tile row li loads column b = perm(li), see above
     const int bcol = F64 ? (((li & 3) << 2) | (li >> 2)) : li;
-    const C* Tst = reinterpret_cast<const C*>(a.T2) + (int64_t)st * W * NL * ldf +
-                   (int64_t)line * ldf + wave * TN * 16 + bcol;
+    // T2's padding (b >= nW of a mode, modes beyond nm) is not written: a lane there reads
+    // the last used column before it, which meets U = 0; a tile there is skipped, or where
+    // it shares a pass with one in use its result is not kept
+    const int nt = nm * H;  // tiles in use
+    const C* Tst = reinterpret_cast<const C*>(a.T2) + (int64_t)st * W * NL * ldf + (int64_t)line * ldf +
+                   wave * TN * 16;
+    const C* const Th[2] = {Tst + min(bcol, nW - 1), Tst + (H == 2 ? min(bcol, nW - 17) : min(bcol, nW - 1))};
     const int64_t Tk = (int64_t)NL * ldf;  // stride of R0 in T2
 
     const uint32_t* lv = a.live + ((int64_t)st * NL + line) * N0;
@@ -1640,7 +1654,7 @@ line_rates_kernel(RateArgs a) {
         for (int ks = 0; ks < KS; ++ks) {
             const int64_t k = min(4 * ks + lg, W - 1);
 #pragma unroll
-            for (int t = 0; t < TN; ++t) tb[ks * TN + t] = Tst[k * Tk + t * 16];
+            for (int t = 0; t < TN; ++t) tb[ks * TN + t] = Th[t & 1][k * Tk + t * 16];
         }
     }
     auto p0_keep = [&](int i) {
@@ -1863,6 +1877,7 @@ line_rates_kernel(RateArgs a) {
             // X^T tiles of the unit's points and Y, two column tiles at a time
 #pragma unroll
             for (int t0 = 0; t0 < TN; t0 += kTP) {
+                if (wave * TN + t0 >= nt) break;
                 constexpr int P = TN < kTP ? TN : kTP;
                 V4 cr[P], ci[P];
 #pragma unroll
@@ -1897,7 +1912,7 @@ line_rates_kernel(RateArgs a) {
                         C bc[P];
 #pragma unroll
                         for (int t = 0; t < P; ++t)
-                            bc[t] = (k < W && t0 + t < TN) ? Tst[k * Tk + (t0 + t) * 16] : C{0, 0};
+                            bc[t] = (k < W && t0 + t < TN) ? Th[t & 1][k * Tk + (t0 + t) * 16] : C{0, 0};
                         kstep(bc, ld_vec(sP + prow + k));
                     }
                 }
@@ -2118,10 +2133,20 @@ static hipError_t line_rates(const RateArgs& a, int nst, hipStream_t s) {
                            : with_feat(integral_constant<int, 1>{}, integral_constant<int, 0>{});
         case 2:
             if (pre && feat == 0) return go_line<4, 2, C, 0, 1, 2>(a, nst, s);
+            if constexpr (sizeof(C) == sizeof(cd)) {
+                if (pre && feat == kLineLW) return go_line<4, 2, C, kLineLW, 1, 2>(a, nst, s);
+                if (pre && feat == kLinePol) return go_line<4, 2, C, kLinePol, 1, 2>(a, nst, s);
+                if (pre && feat == kLineVel) return go_line<4, 2, C, kLineVel, 1, 2>(a, nst, s);
+            }
             return pre ? with_feat(integral_constant<int, 2>{}, integral_constant<int, 2>{})
                        : with_feat(integral_constant<int, 2>{}, integral_constant<int, 0>{});
         case 3:
             if (pre && feat == 0) return go_line<6, 2, C, 0, 1, 2>(a, nst, s);
+            if constexpr (sizeof(C) == sizeof(cd)) {
+                if (pre && feat == kLineLW) return go_line<6, 2, C, kLineLW, 1, 2>(a, nst, s);
+                if (pre && feat == kLinePol) return go_line<6, 2, C, kLinePol, 1, 2>(a, nst, s);
+                if (pre && feat == kLineVel) return go_line<6, 2, C, kLineVel, 1, 2>(a, nst, s);
+            }
             return pre ? with_feat(integral_constant<int, 3>{}, integral_constant<int, 2>{})
                        : with_feat(integral_constant<int, 3>{}, integral_constant<int, 0>{});
         case 4:

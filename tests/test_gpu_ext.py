@@ -345,6 +345,36 @@ def test_adaptive_rates_and_linewidth_match_oracle(lib, form, nW, nat):
     assert mx < P_BOUND and mp < P_BOUND
 
 
+@pytest.mark.parametrize("nW,nat", [(2, 1), (7, 2), (9, 3), (16, 4), (13, 5), (17, 5), (32, 2)])
+def test_line_column_padding(lib, nW, nat):
+    """Mode and band counts that leave padding in the columns of the factorised form, whose
+    transforms are not written: rates, polar rates and linewidths against the direct sum."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    mesh = (6, 3, 5)
+    N = int(np.prod(mesh))
+    for pol in (False, True):
+        s = synth.small_system(61 + nW, n_wannier=nW, n_atoms=nat, r=1)
+        if pol:
+            s = synth.add_polar(s, 61 + nW, alpha=3.0, g_max=2)
+        t, par = _params(s, mesh, sigma=0.2)
+        ds = DeviceSystem.from_host(s)
+        out = {}
+        try:
+            for form in ("direct", "factored"):
+                lib.set_mesh_sum(form)
+                gam = torch.zeros((N, nW), dtype=torch.float64, device="cuda")
+                P = torch.zeros((N, s.n_modes), dtype=torch.float64, device="cuda")
+                lib.scatter_rates(ds, mesh, par, gam)
+                lib.phonon_linewidth(ds, mesh, par, P)
+                out[form] = gam.cpu().numpy(), P.cpu().numpy()
+        finally:
+            lib.set_mesh_sum("auto")
+        assert np.max(out["direct"][0]) > 0
+        for a, b in zip(out["factored"], out["direct"]):
+            assert rel_err(a, b)[0] < 1e-10
+
+
 @pytest.mark.parametrize("nW,nat,mesh,scale,smin", [
     (6, 2, (70, 2, 3), 1.0, 0.01),   # more points a line than a wave has lanes
     (16, 5, (18, 3, 2), 0.5, 1e-4),  # two waves; groups that close before they are full
