@@ -70,6 +70,7 @@ phoebe_status phoebe_gpu_destroy(void* handle) {
         (void)hipEventDestroy(t.stop);
     }
     if (h->ws) (void)hipFree(h->ws);
+    if (h->pin) (void)hipHostFree(h->pin);
     if (h->dflag) (void)hipFree(h->dflag);
     if (h->tc.mem) (void)hipFree(h->tc.mem);
     delete h;
@@ -153,7 +154,7 @@ phoebe_status phoebe_gpu_electron_bands(void* handle, const phoebe_system* sys,
         Arena ar(h->ws, h->ws_cap);
         plan(ar);
         HIPCHK(h, hipGetLastError());
-        HIPCHK(h, hipStreamSynchronize(s));  // host lattice lists are read before return
+        pin_done(h, s);  // host lattice lists are read before return
         flush_timing(h, s);
     });
 }
@@ -183,7 +184,7 @@ phoebe_status phoebe_gpu_phonon_modes(void* handle, const phoebe_system* sys,
         Arena ar(h->ws, h->ws_cap);
         plan(ar);
         HIPCHK(h, hipGetLastError());
-        HIPCHK(h, hipStreamSynchronize(s));  // host lattice lists are read before return
+        pin_done(h, s);  // host lattice lists are read before return
     });
 }
 
@@ -462,7 +463,7 @@ phoebe_status interp_g_impl(Handle* h, const phoebe_system* sys, const double* k
         Arena ar(h->ws, h->ws_cap);
         plan(ar);
         HIPCHK(h, hipGetLastError());
-        HIPCHK(h, hipStreamSynchronize(s));  // host lattice lists are read before return
+        pin_done(h, s);  // host lattice lists are read before return
         flush_timing(h, s);
     });
 }
@@ -757,12 +758,18 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             double* lwacc;       // linewidth sums [N, nm]
         } T{};
         const int64_t rows_cap = k_idx ? nk : N;
+        size_t lists_bytes = 0;
         auto plan_tables = [&](Arena& ar) {
-            T.rh = upload_r(h, ar, sys->rh, sys->n_rh, s);
-            T.rd = upload_r(h, ar, sys->rd, sys->n_rd, s);
-            T.re = upload_r(h, ar, sys->re, n_re, s);
-            T.rp = upload_r(h, ar, sys->rp, n_rp, s);
+            // the host's lists, together: one copy fills them
+            T.rh = ar.take<int32_t>((size_t)3 * sys->n_rh);
+            T.rd = ar.take<int32_t>((size_t)3 * sys->n_rd);
+            T.re = ar.take<int32_t>((size_t)3 * n_re);
+            T.rp = ar.take<int32_t>((size_t)3 * n_rp);
             T.rp_packed = ar.take<int32_t>(n_rp);
+            if (factored) T.box_rp = ar.take<int32_t>((size_t)Wbox * Wbox * Wbox);
+            if (re_fact) T.box_re = ar.take<int32_t>((size_t)We * We * We);
+            if (polar) T.born = ar.take<double>((size_t)9 * sys->n_atoms);
+            lists_bytes = ar.used;
             T.eps = ar.take<double>((size_t)N * nW);
             T.focc = ar.take<double>((size_t)N * nW);
             T.U = ar.take<cd>((size_t)N * nW * nW);
@@ -785,16 +792,13 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             T.st_mhi = ar.take<int32_t>((size_t)rows_cap * nW);
             T.st_urow = ar.take<int32_t>((size_t)rows_cap * nW);
             if (factored) {
-                T.box_rp = ar.take<int32_t>((size_t)Wbox * Wbox * Wbox);
                 T.Pax = ar.take<cd>((size_t)(mesh.n0 + mesh.n1 + mesh.n2) * Wbox);
             }
             if (re_fact) {
-                T.box_re = ar.take<int32_t>((size_t)We * We * We);
                 T.Pre = ar.take<cd>((size_t)(mesh.n0 + mesh.n1 + mesh.n2) * We);
             }
             if (polar) {
                 T.Lpol = ar.take<cd>((size_t)N * nm);
-                T.born = ar.take<double>((size_t)9 * sys->n_atoms);
             }
             if (adaptive) {
                 T.vel = ar.take<double>((size_t)N * nW * 3);
@@ -852,47 +856,43 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         Arena ar(h->ws, h->ws_cap);
         plan_tables(ar);
         {
-            std::vector<int32_t> packed(n_rp);
+            // an image of the lists' memory, copied at once
+            char* pin = pin_take(h, lists_bytes);
+            std::vector<char> own(pin ? 0 : lists_bytes);
+            char* const img = pin ? pin : own.data();
+            auto at = [&](int32_t* d) { return reinterpret_cast<int32_t*>(img + ((char*)d - h->ws)); };
+            std::memcpy(at(T.rh), sys->rh, sizeof(int32_t) * 3 * sys->n_rh);
+            std::memcpy(at(T.rd), sys->rd, sizeof(int32_t) * 3 * sys->n_rd);
+            std::memcpy(at(T.re), sys->re, sizeof(int32_t) * 3 * n_re);
+            std::memcpy(at(T.rp), sys->rp, sizeof(int32_t) * 3 * n_rp);
+            int32_t* const packed = at(T.rp_packed);
             for (int i = 0; i < n_rp; ++i)
                 packed[i] = (sys->rp[3 * i] + rmax_p) | ((sys->rp[3 * i + 1] + rmax_p) << 8) |
                             ((sys->rp[3 * i + 2] + rmax_p) << 16);
-            HIPCHK(h, hipMemcpyAsync(T.rp_packed, packed.data(), sizeof(int32_t) * n_rp,
-                                     hipMemcpyHostToDevice, s));
-            std::vector<int32_t> box;
-            if (factored) {
-                // box position ((R0+r) W + R1+r) W + R2+r -> row of F (-1: no such Rp)
-                box.assign((size_t)Wbox * Wbox * Wbox, -1);
-                for (int i = 0; i < n_rp; ++i) {
-                    const int64_t b = ((int64_t)(sys->rp[3 * i] + rmax_p) * Wbox +
-                                       (sys->rp[3 * i + 1] + rmax_p)) * Wbox +
-                                      (sys->rp[3 * i + 2] + rmax_p);
-                    REQUIRE(h, box[b] < 0, "Rp list holds a vector twice");
-                    box[b] = i;
+            // box position ((R0+r) W + R1+r) W + R2+r -> row of the list (-1: not listed)
+            auto fill_box = [&](int32_t* box, const int32_t* R, int n, int r, const char* name) {
+                const int64_t W = 2 * (int64_t)r + 1;
+                std::fill(box, box + W * W * W, -1);
+                for (int i = 0; i < n; ++i) {
+                    int32_t& b = box[((R[3 * i] + r) * W + (R[3 * i + 1] + r)) * W + (R[3 * i + 2] + r)];
+                    REQUIRE(h, b < 0, "%s list holds a vector twice", name);
+                    b = i;
                 }
-                HIPCHK(h, hipMemcpyAsync(T.box_rp, box.data(), sizeof(int32_t) * box.size(),
-                                         hipMemcpyHostToDevice, s));
-                HIPCHK(h, launch_axis_phases(mesh, rmax_p, T.Pax, s));
-            }
-            std::vector<int32_t> box_e;
+            };
+            if (factored) fill_box(at(T.box_rp), sys->rp, n_rp, rmax_p, "Rp");
+            if (re_fact) fill_box(at(T.box_re), sys->re, n_re, rmax_e, "Re");
+            if (polar)
+                std::memcpy(img + ((char*)T.born - h->ws), sys->polar->born,
+                            sizeof(double) * 9 * sys->n_atoms);
+            HIPCHK(h, hipMemcpyAsync(h->ws, img, lists_bytes, hipMemcpyHostToDevice, s));
+            if (!pin) HIPCHK(h, hipStreamSynchronize(s));  // the image must outlive the copy
+            if (factored) HIPCHK(h, launch_axis_phases(mesh, rmax_p, T.Pax, s));
             if (re_fact) {
-                // box position of Re -> row of g(Re, Rp) (-1: no such Re)
-                box_e.assign((size_t)We * We * We, -1);
-                for (int i = 0; i < n_re; ++i) {
-                    const int64_t b = ((int64_t)(sys->re[3 * i] + rmax_e) * We +
-                                       (sys->re[3 * i + 1] + rmax_e)) * We +
-                                      (sys->re[3 * i + 2] + rmax_e);
-                    REQUIRE(h, box_e[b] < 0, "Re list holds a vector twice");
-                    box_e[b] = i;
-                }
-                HIPCHK(h, hipMemcpyAsync(T.box_re, box_e.data(), sizeof(int32_t) * box_e.size(),
-                                         hipMemcpyHostToDevice, s));
                 if (re_reg && lowp)
                     HIPCHK(h, launch_axis_phases_f32(mesh, rmax_e, reinterpret_cast<cf*>(T.Pre), s));
                 else
                     HIPCHK(h, launch_axis_phases(mesh, rmax_e, T.Pre, s));
             }
-            // the host vector must outlive the copy
-            HIPCHK(h, hipStreamSynchronize(s));
         }
         if (h->preset) {
             // tables lent by a batched plan for this call (built there with the same routines)
@@ -972,12 +972,11 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 }
             }
         }
+        HIPCHK(h, hipGetLastError());  // a launch error of one phase is not reported by the next
         HIPCHK(h, launch_fermi(T.eps, N * nW, par->mu, par->kT, T.focc, s));
         HIPCHK(h, launch_band_extrema(T.eps, N, nW, T.omega, N, nm, T.bmin, T.bmax, T.wmax, s));
         HIPCHK(h, launch_window(T.eps, N, nW, par->win_lo, par->win_hi, T.mask, T.flag, s));
         if (polar) {
-            HIPCHK(h, hipMemcpyAsync(T.born, sys->polar->born, sizeof(double) * 9 * sys->n_atoms,
-                                     hipMemcpyHostToDevice, s));
             HIPCHK(h, launch_polar_factor(nullptr, mesh, N, T.E, false, nm, polar_dev(sys, T.born), T.Lpol, s));
         }
         // adaptive smearing: velocities on the mesh; the widest width any transition
@@ -1012,14 +1011,15 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         if (!k_idx) {
             HIPCHK(h, launch_compact(T.flag, N, T.kept, T.cnt, s));
             int32_t c = 0;
-            HIPCHK(h, hipMemcpyAsync(&c, T.cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            HIPCHK(h, hipStreamSynchronize(s));
-            rows = c;
+            int32_t* const pc = reinterpret_cast<int32_t*>(pin_take(h, sizeof(int32_t)));
+            HIPCHK(h, hipMemcpyAsync(pc ? pc : &c, T.cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+            pin_done(h, s);
+            rows = pc ? *pc : c;
             kept = T.kept;
         } else {
             std::vector<int32_t> kh(nk);
             HIPCHK(h, hipMemcpyAsync(kh.data(), k_idx, sizeof(int32_t) * nk, hipMemcpyDeviceToHost, s));
-            HIPCHK(h, hipStreamSynchronize(s));
+            pin_done(h, s);
             for (int64_t i = 0; i < nk; ++i)
                 REQUIRE(h, kh[i] >= 0 && kh[i] < N, "k_idx[%lld] = %d is not a mesh index",
                         (long long)i, kh[i]);
@@ -1029,10 +1029,30 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         if (rows == 0) return;
         HIPCHK(h, launch_gather_rows(T.mask, kept, rows, nW, T.rowflag, band_mask, kept_k_out, s));
         HIPCHK(h, launch_compact(T.rowflag, rows * nW, T.ids, T.cnt + 1, s));
+        // the state count comes with the kept k and, where the list is short, the states'
+        // ids in full (entries beyond the count are not read): one wait for the three
         int32_t nst_i = 0;
-        HIPCHK(h, hipMemcpyAsync(&nst_i, T.cnt + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIPCHK(h, hipStreamSynchronize(s));
-        const int nst = nst_i;
+        const int64_t n_ids = rows * nW <= 32768 ? rows * nW : 0;
+        int32_t* const down = rates ? reinterpret_cast<int32_t*>(
+                                          pin_take(h, sizeof(int32_t) * (1 + rows + n_ids)))
+                                    : nullptr;
+        HIPCHK(h, hipMemcpyAsync(down ? down : &nst_i, T.cnt + 1, sizeof(int32_t),
+                                 hipMemcpyDeviceToHost, s));
+        if (down) {
+            HIPCHK(h, hipMemcpyAsync(down + 1, kept, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, s));
+            if (n_ids)
+                HIPCHK(h, hipMemcpyAsync(down + 1 + rows, T.ids, sizeof(int32_t) * n_ids,
+                                         hipMemcpyDeviceToHost, s));
+        }
+        pin_done(h, s);
+        // (read before anything else takes a piece)
+        const int nst = down ? down[0] : nst_i;
+        const std::vector<int32_t> kept_h(down ? down + 1 : nullptr, down ? down + 1 + rows : nullptr);
+        std::vector<int32_t> strow;  // row of every state
+        if (down && n_ids && nst <= n_ids) {
+            strow.resize(nst);
+            for (int i = 0; i < nst; ++i) strow[i] = down[1 + rows + i] / nW;
+        }
         if (n_states_out) *n_states_out = nst;
         REQUIRE(h, state_cap < 0 || nst <= state_cap,
                 "%d states in the window exceed the per-state output capacity of %lld", nst,
@@ -1062,11 +1082,14 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             flush_timing(h, s);
             return;
         }
-        std::vector<int32_t> strow(nst);
-        HIPCHK(h, hipMemcpyAsync(strow.data(), T.st_row, sizeof(int32_t) * nst,
-                                 hipMemcpyDeviceToHost, s));
-        HIPCHK(h, hipStreamSynchronize(s));
+        if (strow.empty()) {
+            strow.resize(nst);
+            HIPCHK(h, hipMemcpyAsync(strow.data(), T.st_row, sizeof(int32_t) * nst,
+                                     hipMemcpyDeviceToHost, s));
+            HIPCHK(h, hipStreamSynchronize(s));
+        }
 
+        HIPCHK(h, hipGetLastError());
         // ---- phase B: batches of kept-k rows ----
         // Direct stage 1: BK rows each.  Factorised stage 1: consecutive rows
         // while the batch holds at most BK rows, kD0Max distinct k0 and kD01Max
@@ -1080,9 +1103,12 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         if (!re_fact) {
             for (int64_t r0 = 0; r0 < rows; r0 += BK) batches.push_back({r0, std::min<int64_t>(BK, rows - r0)});
         } else {
-            std::vector<int32_t> kh(rows);
-            HIPCHK(h, hipMemcpyAsync(kh.data(), kept, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, s));
-            HIPCHK(h, hipStreamSynchronize(s));
+            std::vector<int32_t> kh = kept_h;
+            if (kh.empty()) {
+                kh.resize(rows);
+                HIPCHK(h, hipMemcpyAsync(kh.data(), kept, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, s));
+                HIPCHK(h, hipStreamSynchronize(s));
+            }
             const int64_t n12 = (int64_t)mesh.n1 * mesh.n2;
             if (all_planes) {
                 for (int64_t i = 0; i < rows; ++i) planes.push_back((int32_t)(kh[i] / n12));
@@ -1443,6 +1469,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             }
             HIPCHK(h, launch_reduce_partials(partial, ns, n_qtiles, T.st_row + sbeg,
                                              T.st_band + sbeg, nW, scale, gamma_out, s));
+            HIPCHK(h, hipGetLastError());
             sbeg = send;
         }
         if (lw_out)  // (2 pi / N_k) n (n + 1) hbar omega x the sums, with the delta's 1/(sqrt(pi) sigma)
@@ -1568,9 +1595,10 @@ phoebe_status phoebe_gpu_velocities(void* handle, const phoebe_system* sys, cons
             ar.used = std::max(a1.used, a2.used);
             if (!ar.base) return;
             int32_t b = 0;
-            HIPCHK(h, hipMemcpyAsync(&b, bad, sizeof b, hipMemcpyDeviceToHost, s));
+            int32_t* const pb = reinterpret_cast<int32_t*>(pin_take(h, sizeof b));
+            HIPCHK(h, hipMemcpyAsync(pb ? pb : &b, bad, sizeof b, hipMemcpyDeviceToHost, s));
             HIPCHK(h, hipStreamSynchronize(s));
-            if (b) {
+            if (pb ? *pb : b) {
                 set_err(h, "a degenerate group of more than 8 bands in the velocity operator");
                 throw Fail{PHOEBE_E_UNSUPPORTED};
             }
@@ -1581,7 +1609,7 @@ phoebe_status phoebe_gpu_velocities(void* handle, const phoebe_system* sys, cons
         Arena ar(h->ws, h->ws_cap);
         plan(ar);
         HIPCHK(h, hipGetLastError());
-        HIPCHK(h, hipStreamSynchronize(s));
+        pin_done(h, s);
         flush_timing(h, s);
     });
 }
@@ -1622,7 +1650,7 @@ phoebe_status phoebe_gpu_polar_factor(void* handle, const phoebe_system* sys, co
         Arena ar(h->ws, h->ws_cap);
         plan(ar);
         HIPCHK(h, hipGetLastError());
-        HIPCHK(h, hipStreamSynchronize(s));
+        pin_done(h, s);
     });
 }
 

@@ -101,7 +101,7 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
         Arena ar(h->ws, h->ws_cap);
         plan(ar);
         HIPCHK(h, hipGetLastError());
-        HIPCHK(h, hipStreamSynchronize(s));  // host lattice lists are read before return
+        pin_done(h, s);  // host lattice lists are read before return
         flush_timing(h, s);
     });
 }

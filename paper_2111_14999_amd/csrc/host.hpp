@@ -81,6 +81,8 @@ struct Handle {
     bool table_cache = false;  // reuse band and phonon tables across rate calls
     int64_t inject_at = 0;     // testing: report the n-th successful HIP check as failed
     TableCache tc;
+    char* pin = nullptr;  // pinned staging of a call's host lists and counts, see pin_take
+    size_t pin_cap = 0, pin_used = 0;
     const PresetTables* preset = nullptr;  // set only for the duration of a plan's plain call
     std::vector<TimedLaunch> pending;
     std::vector<KernelStat> stats;
@@ -243,9 +245,52 @@ inline void check_system(Handle* h, const phoebe_system* sys, bool need_h, bool 
     }
 }
 
+// Pinned host memory for what a call moves in small pieces (lattice lists up, counts and
+// row lists down): a copy from pageable memory costs the runtime's own staging and a wait,
+// 15 to 20 us each, and a call on a small system made a dozen of them.  The handle keeps one
+// buffer of at most kPinMax; a call takes pieces of it and gives all of them back once it
+// has waited for the stream (pin_done; a call that fails waits for the device first).
+// nullptr where there is none (the non-allocating entry point, larger lists): the caller
+// then copies from its own memory.
+constexpr size_t kPinMax = (size_t)4 << 20;
+inline char* pin_take(Handle* h, size_t bytes) {
+    bytes = (bytes + 255) / 256 * 256;
+    if (h->fixed_ws || bytes > kPinMax) return nullptr;
+    if (h->pin_used + bytes > h->pin_cap) {
+        if (h->pin_used) return nullptr;  // pieces are out: no growing under them
+        size_t cap = (size_t)64 << 10;
+        while (cap < bytes) cap *= 2;
+        if (h->pin) (void)hipHostFree(h->pin);
+        h->pin = nullptr;
+        h->pin_cap = 0;
+        void* p = nullptr;
+        if (hipHostMalloc(&p, cap, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        h->pin = static_cast<char*>(p);
+        h->pin_cap = cap;
+    }
+    char* p = h->pin + h->pin_used;
+    h->pin_used += bytes;
+    return p;
+}
+
+// Waits for the stream; the call's pieces of the staging buffer are free again.
+inline void pin_done(Handle* h, hipStream_t s) {
+    HIPCHK(h, hipStreamSynchronize(s));
+    HIPCHK(h, hipGetLastError());
+    h->pin_used = 0;
+}
+
+// (the caller ends with pin_done)
 inline int32_t* upload_r(Handle* h, Arena& ar, const int32_t* host, int n, hipStream_t s) {
     int32_t* d = ar.take<int32_t>((size_t)3 * n);
-    if (d) HIPCHK(h, hipMemcpyAsync(d, host, sizeof(int32_t) * 3 * n, hipMemcpyHostToDevice, s));
+    if (!d) return d;
+    const size_t bytes = sizeof(int32_t) * 3 * n;
+    char* p = pin_take(h, bytes);
+    if (p) std::memcpy(p, host, bytes);
+    HIPCHK(h, hipMemcpyAsync(d, p ? (const void*)p : host, bytes, hipMemcpyHostToDevice, s));
     return d;
 }
 
@@ -436,9 +481,15 @@ inline phoebe_status run(Handle* h, const char* name, const std::function<void()
         body();
         return PHOEBE_OK;
     } catch (const Fail& f) {
+        if (h->pin_used) {  // copies of the failed call may still read their pieces
+            (void)hipDeviceSynchronize();
+            h->pin_used = 0;
+        }
         if (h->err.empty()) h->err = "workspace sizing error (internal)";
         return f.st;
     } catch (const std::bad_alloc&) {
+        if (h->pin_used) (void)hipDeviceSynchronize();
+        h->pin_used = 0;
         set_err(h, "host allocation failed");
         return PHOEBE_E_NOMEM;
     }
