@@ -176,7 +176,7 @@ phoebe_status phoebe_gpu_phonon_modes(void* handle, const phoebe_system* sys,
         auto plan = [&](Arena& ar) {
             int32_t* rd = upload_r(h, ar, sys->rd, sys->n_rd, s);
             phonon_dev(h, ar, sys, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, 0.0, 0.0, omega_out,
-                       nullptr, nullptr, reinterpret_cast<cd*>(z_out), s);
+                       nullptr, nullptr, reinterpret_cast<cd*>(z_out), s, true, z_out != nullptr);
         };
         Arena dry(nullptr);
         plan(dry);
@@ -345,7 +345,7 @@ phoebe_status interp_g_impl(Handle* h, const phoebe_system* sys, const double* k
                 }
                 Arena sub3 = ar;
                 phonon_dev(h, sub3, sys, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, omega_min, 0.0,
-                           om, E, nullptr, nullptr, s);
+                           om, E, nullptr, nullptr, s, true, !q_mesh);
                 ar.used = std::max(std::max(sub.used, sub2.used), sub3.used);
             }
             if (!ar.base) return;
@@ -1637,7 +1637,7 @@ phoebe_status phoebe_gpu_polar_factor(void* handle, const phoebe_system* sys, co
             double* om = ar.take<double>((size_t)nq * nm);
             cd* E = ar.take<cd>((size_t)nq * nm * nm);
             phonon_dev(h, ar, sys, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, omega_min, 0.0, om, E,
-                       nullptr, nullptr, s);
+                       nullptr, nullptr, s, true, true);
             if (!ar.base) return;
             HIPCHK(h, hipMemcpyAsync(born, sys->polar->born, sizeof(double) * 9 * sys->n_atoms,
                                      hipMemcpyHostToDevice, s));

@@ -369,13 +369,15 @@ inline void electron_bands_dev(Handle* h, Arena& ar, const phoebe_system* sys, c
     te.done();
 }
 
+// ordered: by the solver whose rounding does not change (launch_eig_herm_ordered), where the
+// modes themselves are handed out and q may be any point.
 // E comes as [q, mode, atom axis], or with e_by_mode false as [q, atom axis, mode]: the
 // rate kernels' lanes run over the modes and then read whole cache lines (a line of a
 // column per lane, the other way, is the L1's work of 64 lines for each 16-byte load).
 inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int32_t* rd_d,
                 const double* frac, const int32_t* idx, Mesh m, int64_t np, double omega_min,
                 double kT, double* omega, cd* E, double* nb, cd* z_out, hipStream_t s,
-                bool e_by_mode = true) {
+                bool e_by_mode = true, bool ordered = false) {
     const int nm = 3 * sys->n_atoms, nR = sys->n_rd;
     cd* P = ar.take<cd>((size_t)np * nR);
     double* phic = ar.take<double>((size_t)nR * nm * nm);
@@ -387,7 +389,8 @@ inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int
     HIPCHK(h, launch_mass_weight(sys->phi_r, sys->mass, nR, nm, phic, s));
     HIPCHK(h, launch_zgemm_real_b(P, nR, phic, (int64_t)nm * nm, D, (int64_t)nm * nm, np,
                                   (int64_t)nm * nm, nR, s));
-    HIPCHK(h, launch_eig_herm(D, nm, np, lam, z, false, s));
+    HIPCHK(h, ordered ? launch_eig_herm_ordered(D, nm, np, lam, z, s)
+                      : launch_eig_herm(D, nm, np, lam, z, false, s));
     HIPCHK(h, launch_phonon_post(lam, z, sys->mass, sys->n_atoms, np, omega_min, kT, omega, E,
                                  e_by_mode, nb, s));
 }

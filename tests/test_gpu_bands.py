@@ -104,3 +104,31 @@ def test_eigensolver_orders(lib, n):
     assert np.max(np.abs(eps - ref)) < 1e-13 * scale
     assert np.max(np.abs(H @ U - U * eps[:, None, :])) < 1e-13 * scale
     assert np.max(np.abs(np.conj(np.swapaxes(U, 1, 2)) @ U - np.eye(n))) < 1e-13
+
+
+@pytest.mark.parametrize("nat", [1, 2, 3, 4, 5, 6, 8, 10])
+def test_phonon_solvers(lib, nat):
+    """The solver of modes handed out, every order it has, against D(q) itself; frequencies
+    alone go by the other one and agree."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(80 + nat, n_wannier=1, n_atoms=nat, r=1)
+    ds = DeviceSystem.from_host(s, with_coupling=False)
+    q = np.random.default_rng(nat).uniform(-1, 1, size=(67, 3))
+    nm = 3 * nat
+    om, only = (torch.empty((67, nm), dtype=torch.float64, device="cuda") for _ in range(2))
+    z = torch.empty((67, nm, nm), dtype=torch.complex128, device="cuda")
+    lib.phonon_modes(ds, torch.from_numpy(q).cuda(), om, z)
+    lib.phonon_modes(ds, torch.from_numpy(q).cuda(), only)
+    torch.cuda.synchronize()
+    om, only, z = om.cpu().numpy(), only.cpu().numpy(), z.cpu().numpy()
+    D = bands.dynamical_matrix(q, s.rd, s.phi_r, s.mass)
+    lam = np.linalg.eigvalsh(D)
+    scale = np.max(np.abs(lam))
+    got = np.einsum("qin,qij,qjn->qn", np.conj(z), D, z).real
+    assert np.max(np.abs(got - lam)) < 1e-13 * scale
+    assert np.max(np.abs(D @ z - z * got[:, None, :])) < 1e-13 * scale
+    assert np.max(np.abs(np.conj(np.swapaxes(z, 1, 2)) @ z - np.eye(nm))) < 1e-13
+    # omega = sqrt(lambda) c: an error of 1e-13 of the largest lambda
+    w2 = np.max(om) ** 2
+    assert np.max(np.abs(om ** 2 - only ** 2)) < 2e-13 * w2
