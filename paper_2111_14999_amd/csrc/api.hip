@@ -688,11 +688,11 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                              re_axes_lds(rmax_e, lowp) <= 160 * 1024 &&
                              (h->mesh_sum == PHOEBE_MESH_SUM_FACTORED || 2 * We <= n_re);
         constexpr int kD0Max = 8, kD01Max = 256;
-        // boxes up to 7 wide: the whole sum in one pass over g, with no T0
-        const bool re_reg = re_fact && re_reg_supported(rmax_e, NC2);
+        // narrow boxes: the whole sum in one pass over g, with no T0 (re_reg)
         // nW = 16: the pair and k steps of stage 1 apply the U_k fold themselves and
         // write F; G (nW times larger) never reaches HBM
         const bool fold_fused = re_fact && nW == 16 && cw == 16;
+        const bool re_reg = re_fact && re_reg_supported(rmax_e, NC2, lowp, fold_fused);
         int BK = re_fact ? 256 : 64;
         // G and F of a batch: 8 GB each, or a sixteenth of the workspace budget (a pass of
         // re_reg reads g once per batch, so its batches are as large as F allows)

@@ -186,7 +186,7 @@ struct ReRegBatch {
     const int32_t *pair_k1, *ent, *chunks;
     cd* ue;
 };
-bool re_reg_supported(int rmax, int64_t NC);
+bool re_reg_supported(int rmax, int64_t NC, bool f32, bool fold);
 void re_reg_limits(int rmax, int* pairs, int* ks);
 hipError_t launch_re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
                          const cd* P, const ReRegBatch& b, const FoldOut* fo, cd* G, int64_t ldg,

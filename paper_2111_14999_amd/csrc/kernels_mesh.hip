@@ -1177,17 +1177,15 @@ static bool fold_ok(const FoldOut* fo, int64_t NC) {
                    fo->F);
 }
 
-// the box width as a compile-time constant where it is a common one
-template <class F>
+// the box width as a compile-time constant where it is a common one that comes here
+// (narrower boxes go by re_reg_kernel, see re_reg_supported)
+template <class C, class F>
 static hipError_t with_box_width(int W, F&& f) {
-    switch (W) {
-        case 1: return f(std::integral_constant<int, 1>{});
-        case 3: return f(std::integral_constant<int, 3>{});
-        case 5: return f(std::integral_constant<int, 5>{});
-        case 7: return f(std::integral_constant<int, 7>{});
-        case 9: return f(std::integral_constant<int, 9>{});
-        default: return f(std::integral_constant<int, 0>{});
+    if (W == 9) return f(std::integral_constant<int, 9>{});
+    if constexpr (std::is_same_v<C, cf>) {
+        if (W == 7) return f(std::integral_constant<int, 7>{});
     }
+    return f(std::integral_constant<int, 0>{});
 }
 
 // LDS of the fused kernel: W^2 x 64 staged values
@@ -1204,7 +1202,7 @@ static hipError_t re_axes(const cd* g, int64_t NC, const int32_t* box_re, int rm
     if (W > kMaxW || b.d0 <= 0 || b.d01 <= 0 || b.d_plane || !fold_ok(fo, NC) ||
         re_axes_lds(rmax, sizeof(C) == sizeof(cf)) > 160 * 1024)
         return hipErrorInvalidValue;
-    return with_box_width(W, [&](auto wt) {
+    return with_box_width<C>(W, [&](auto wt) {
         constexpr int WT = decltype(wt)::value;
         hipError_t e = go_re_axis0<WT, C>(g, NC, box_re, W, P, b.d_k0, b.d0, fo != nullptr, T0, s);
         if (e != hipSuccess) return e;
@@ -1218,7 +1216,7 @@ static hipError_t re_planes(const cd* g, int64_t NC, const int32_t* box_re, int 
                             hipStream_t s) {
     const int W = 2 * rmax + 1;
     if (W > kMaxW || n <= 0 || (tr && NC % 256 != 0)) return hipErrorInvalidValue;
-    return with_box_width(W, [&](auto wt) {
+    return with_box_width<C>(W, [&](auto wt) {
         return go_re_axis0<decltype(wt)::value, C>(g, NC, box_re, W, P, k0_list, n, tr, T0, s);
     });
 }
@@ -1230,20 +1228,25 @@ static hipError_t re_pairs(const C* T0, int64_t NC, int rmax, Mesh m, const cd* 
     if (W > kMaxW || b.d0 <= 0 || b.d01 <= 0 || !b.d_plane || !fold_ok(fo, NC) ||
         re_axes_lds(rmax, sizeof(C) == sizeof(cf)) > 160 * 1024)
         return hipErrorInvalidValue;
-    return with_box_width(W, [&](auto wt) {
+    return with_box_width<C>(W, [&](auto wt) {
         return go_re_axis12<decltype(wt)::value, C>(T0, NC, W, m, P, b, fo, G, ldg, s);
     });
 }
 
-bool re_reg_supported(int rmax, int64_t NC) {
-    return 2 * rmax + 1 <= kRegW && NC < ((int64_t)1 << 28);  // (32-bit byte offsets in a row)
+// Boxes up to 7 wide, but in FP32 only 5 where G is written: the sums keep their unfolded
+// order there (12 FMAs a value become 28), and without the fold's saving T0 in HBM, half as
+// large in FP32, is the cheaper way (24^3 mesh, 12 bands, box 7, ms a call: one pass 10.1,
+// T0 8.6; FP64 8.9 and 13.6; FP32 with the fold, 16 bands: 10.4 and 12.3).
+bool re_reg_supported(int rmax, int64_t NC, bool f32, bool fold) {
+    const int W = 2 * rmax + 1;
+    return W <= kRegW && (W < 7 || !f32 || fold) && NC < ((int64_t)1 << 28);  // (32-bit byte offsets in a row)
 }
 
 template <class C>
 static hipError_t re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
                          const C* P, const ReRegBatch& b, const FoldOut* fo, C* G, int64_t ldg,
                          hipStream_t s) {
-    if (!re_reg_supported(rmax, NC) || b.nchunk <= 0 || b.nent <= 0 || m.n2 >= (1 << 23) ||
+    if (!re_reg_supported(rmax, NC, sizeof(C) == sizeof(cf), fo != nullptr) || b.nchunk <= 0 || b.nent <= 0 || m.n2 >= (1 << 23) ||
         !fold_ok(fo, NC) || ((reinterpret_cast<uintptr_t>(b.ent) | reinterpret_cast<uintptr_t>(b.ue)) & 15))
         return hipErrorInvalidValue;
     auto go = [&](auto wt) {
@@ -1255,7 +1258,11 @@ static hipError_t re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rma
         case 0: return go(std::integral_constant<int, 1>{});
         case 1: return go(std::integral_constant<int, 3>{});
         case 2: return go(std::integral_constant<int, 5>{});
-        default: return go(std::integral_constant<int, 7>{});
+        default:
+            if constexpr (std::is_same_v<C, cd>)
+                return go(std::integral_constant<int, 7>{});
+            else
+                return go_re_reg<7, C, true>(g, NC, box_re, m, P, b, *fo, G, ldg, s);
     }
 }
 hipError_t launch_re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
