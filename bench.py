@@ -186,10 +186,10 @@ def main():
     # flops; rotations and rate terms are not counted):
     #   stage2_rates    direct sum over the Rp list: 8 N_q n_rp nModes nW per state
     #   stage1_phase    sum over Re: 8 n_re n_rp nModes nW^2 per kept k
-    #   stage1_axes     the same sum factorised over the Re box, HBM: per batch, the
-    #                   batch's T0 planes read (with g read and T0 written first when
-    #                   the planes are per batch) and G written once
-    #   stage1_planes   T0 of every k0 plane in one pass: g read once, T0 written once
+    #   stage1_planes   the same sum factorised over the Re box, HBM: every plane of the call in
+    #                   one pass, g read once and F or G (boxes of 9 and wider: T0) written once
+    #   stage1_axes     the same per batch of k (boxes of 9 and wider: the batch's T0 planes
+    #                   read, and g read and T0 written first where the planes are per batch)
     #   line_rates      last axis of the factorised sum, rotations and terms at the live points,
     #                   HBM: T2 of every live (state, line), U_{k+q} of every 16-point unit
     #   axis_transforms first two axes, HBM traffic: 16 B (8 B in FP32) nModes nW per state x
@@ -200,7 +200,7 @@ def main():
         "stage1_phase": ("mfma", 8.0 * n_kept * n_re * n_rp * nm * nW * nW),
         # factorised stage 1, HBM (bytes recorded by the library per launch)
         "stage1_axes": ("hbm", None),
-        # T0 of every k0 plane in one pass over g (when the workspace holds them all)
+        # one pass over g for every k0 plane of the call
         "stage1_planes": ("hbm", None),
         # last Rp axis + rotations + terms on the live points only: by its executed
         # intensity (about 6 flop/B, below the FP64 ridge) an HBM kernel; bytes recorded
