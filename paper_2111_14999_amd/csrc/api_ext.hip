@@ -45,6 +45,11 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
         for (int i = 0; i < 3 * n1; ++i) nr1[i] = -sys->r1[i];
         for (int i = 0; i < 3 * n2; ++i) nr2[i] = -sys->r2[i];
         const int64_t qb = std::min<int64_t>(nq, 16);  // q of one stage-1 batch
+        // q whose X is formed and rotated at once, up to 1 GB of it: 1,024 q' make 848
+        // work-groups of the product and 1,024 of the rotations, a few rounds of the chip (4 q,
+        // 15 modes: 350 + 200 us one by one, 284 + 190 together); one where the budget has no
+        // room for more
+        int64_t xb = std::max<int64_t>(1, std::min<int64_t>(qb, ((int64_t)1 << 30) / (16 * nqp * m3)));
         auto plan = [&](Arena& ar) {
             int32_t* rd = upload_r(h, ar, sys->rd, sys->n_rd, s);
             int32_t* r1 = upload_r(h, ar, nr1.data(), n1, s);
@@ -60,7 +65,7 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
             cd* P2 = ar.take<cd>((size_t)nqp * n2);
             cd* S = ar.take<cd>((size_t)qb * n2 * m3);
             cd* T = ar.take<cd>((size_t)qb * n2 * m3);
-            cd* X = ar.take<cd>((size_t)nqp * m3);
+            cd* X = ar.take<cd>((size_t)xb * nqp * m3);
             {
                 Arena a1 = ar, a2 = ar, a3 = ar;
                 phonon_dev(h, a1, &ph, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, omega_min, 0.0, w1, E1,
@@ -84,19 +89,25 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
                                               (int64_t)n2 * m3, nb, (int64_t)n2 * m3, n1, s));
                 t1.done();
                 HIPCHK(h, launch_v3_fold(S, nb, n2, nm, E1 + i0 * nm * nm, T, s));
-                for (int64_t i = 0; i < nb; ++i) {
-                    const int64_t iq = i0 + i;
-                    // X[j, (nu, s'b, s''c)] = sum_R' e^{-i 2 pi q'.R'} T[i, R', ...]
+                for (int64_t i = 0; i < nb; i += xb) {
+                    const int64_t iq = i0 + i, n = std::min(xb, nb - i);
+                    // X[i, j, (nu, s'b, s''c)] = sum_R' e^{-i 2 pi q'.R'} T[i, R', ...]
                     Timer t2(h, s, "v3_stage2");
-                    HIPCHK(h, launch_zgemm(P2, n2, T + i * n2 * m3, m3, X, m3, nqp, m3, n2, s));
+                    HIPCHK(h, launch_zgemm_batch(P2, n2, T + i * n2 * m3, m3, n2 * m3, X, m3, nqp * m3,
+                                                 (int)n, nqp, m3, n2, s));
                     t2.done();
-                    HIPCHK(h, launch_v3_rot(X, nqp, nm, E2, E3 + iq * nqp * nm * nm,
+                    HIPCHK(h, launch_v3_rot(X, n * nqp, nqp, nm, E2, E3 + iq * nqp * nm * nm,
                                             reinterpret_cast<cd*>(v3_out) + iq * nqp * m3, s));
                 }
             }
         };
         Arena dry(nullptr);
         plan(dry);
+        if (dry.used > h->budget) {
+            xb = 1;
+            dry = Arena(nullptr);
+            plan(dry);
+        }
         ensure_ws(h, dry.used);
         Arena ar(h->ws, h->ws_cap);
         plan(ar);

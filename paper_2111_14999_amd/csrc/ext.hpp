@@ -92,8 +92,9 @@ hipError_t launch_neg_pair_sum(const double* q, int64_t nq, const double* qp, in
 // T[i, r, nu, bc] = sum_sa S[i, r, sa, bc] conj(E1[i, nu, sa]), bc < nm^2
 hipError_t launch_v3_fold(const cd* S, int64_t nq, int nr, int nm, const cd* E1, cd* T,
                           hipStream_t s);
-// V[j, nu, nu', nu''] = sum_c conj(E3[j, nu'', c]) sum_b conj(E2[j, nu', b]) X[j, nu, b, c]
-hipError_t launch_v3_rot(const cd* X, int64_t nqp, int nm, const cd* E2, const cd* E3, cd* V,
+// V[j, nu, nu', nu''] = sum_c conj(E3[j, nu'', c]) sum_b conj(E2[j % nqp, nu', b]) X[j, nu, b, c],
+// j < n
+hipError_t launch_v3_rot(const cd* X, int64_t n, int64_t nqp, int nm, const cd* E2, const cd* E3, cd* V,
                          hipStream_t s);
 
 }  // namespace phx

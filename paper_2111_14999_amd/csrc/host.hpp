@@ -371,9 +371,10 @@ inline void electron_bands_dev(Handle* h, Arena& ar, const phoebe_system* sys, c
 
 // ordered: by the solver whose rounding does not change (launch_eig_herm_ordered), where the
 // modes themselves are handed out and q may be any point.
-// E comes as [q, mode, atom axis], or with e_by_mode false as [q, atom axis, mode]: the
-// rate kernels' lanes run over the modes and then read whole cache lines (a line of a
-// column per lane, the other way, is the L1's work of 64 lines for each 16-byte load).
+// E comes as [q, mode, atom axis], or with e_by_mode false as [q, atom axis, mode], the
+// eigensolver's own order, for the rate kernels, whose lanes run over the modes: written and
+// read in whole cache lines (64,000 points: 252 -> 113 us to write; the line kernel, which
+// waits on other things, takes the same time with either).
 inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int32_t* rd_d,
                 const double* frac, const int32_t* idx, Mesh m, int64_t np, double omega_min,
                 double kT, double* omega, cd* E, double* nb, cd* z_out, hipStream_t s,

@@ -16,6 +16,10 @@ hipError_t launch_phase_table(const double* frac, const int32_t* idx, Mesh m, in
 // dimensions (in complex elements).
 hipError_t launch_zgemm(const cd* A, int64_t lda, const cd* B, int64_t ldb, cd* C, int64_t ldc,
                         int64_t M, int64_t N, int K, hipStream_t s);
+// nb products with one A: C + z sc = A (B + z sb).
+hipError_t launch_zgemm_batch(const cd* A, int64_t lda, const cd* B, int64_t ldb, int64_t sb, cd* C,
+                              int64_t ldc, int64_t sc, int nb, int64_t M, int64_t N, int K,
+                              hipStream_t s);
 
 // The same with a real B (half its bytes, two MFMAs per product).
 hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_t ldb, cd* C,

@@ -731,8 +731,8 @@ hipError_t launch_v3_fold(const cd* S, int64_t nq, int nr, int nm, const cd* E1,
     return hipGetLastError();
 }
 
-// Both rotations of X[j, nu, b, c]: V[j, nu, nu', nu''] = sum_c E3[nu'', c]^* sum_b
-// E2[nu', b]^* X[nu, b, c].  A work-group has one j and GS of its nu.  Thread (nu, c) keeps
+// Both rotations of X[j, nu, b, c]: V[j, nu, nu', nu''] = sum_c E3[j, nu'', c]^* sum_b
+// E2[j % nqp, nu', b]^* X[j, nu, b, c] (several q of the same nqp q').  A work-group has one j and GS of its nu.  Thread (nu, c) keeps
 // its column of X over b in registers and forms Y[nu', c] with E2's rows as scalars (j is
 // the work-group's, so they come through the scalar cache and take no LDS reads); Y is
 // turned in LDS, and thread (nu, nu') does the same over c.  Memory sees X once and V
@@ -750,7 +750,7 @@ template <int NM>
 __global__ __launch_bounds__(V3Rot<NM>::TB) void v3_rot_kernel(const cd* __restrict__ X,
                                                                const cd* __restrict__ E2,
                                                                const cd* __restrict__ E3,
-                                                               cd* __restrict__ V) {
+                                                               int nqp, cd* __restrict__ V) {
     constexpr int LD = V3Rot<NM>::LD, GS = V3Rot<NM>::GS, TB = V3Rot<NM>::TB;
     __shared__ cd sY[GS * NM * LD];  // [nu][nu'][c], then V
     const int64_t j = blockIdx.x;
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(V3Rot<NM>::TB) void v3_rot_kernel(const cd* __restr
 #pragma unroll
         for (int b = 0; b < NM; ++b) x[b] = X[o + ((int64_t)g * NM + b) * NM + c];
     }
-    const cd* e2 = E2 + j * NM * NM;
+    const cd* e2 = E2 + j % nqp * NM * NM;
 #pragma unroll 1
     for (int n = 0; n < NM; ++n) {
         cd acc = {0.0, 0.0};
@@ -788,28 +788,29 @@ __global__ __launch_bounds__(V3Rot<NM>::TB) void v3_rot_kernel(const cd* __restr
 }
 
 template <int NM>
-static hipError_t go_v3_rot(const cd* X, int64_t nqp, const cd* E2, const cd* E3, cd* V, hipStream_t s) {
+static hipError_t go_v3_rot(const cd* X, int64_t n, int nqp, const cd* E2, const cd* E3, cd* V,
+                            hipStream_t s) {
     using S = V3Rot<NM>;
-    hipLaunchKernelGGL((v3_rot_kernel<NM>), dim3((unsigned)nqp, (NM + S::GS - 1) / S::GS), dim3(S::TB), 0,
-                       s, X, E2, E3, V);
+    hipLaunchKernelGGL((v3_rot_kernel<NM>), dim3((unsigned)n, (NM + S::GS - 1) / S::GS), dim3(S::TB), 0,
+                       s, X, E2, E3, nqp, V);
     return hipGetLastError();
 }
 
-hipError_t launch_v3_rot(const cd* X, int64_t nqp, int nm, const cd* E2, const cd* E3, cd* V,
+hipError_t launch_v3_rot(const cd* X, int64_t n, int64_t nqp, int nm, const cd* E2, const cd* E3, cd* V,
                          hipStream_t s) {
-    if (nqp <= 0) return hipSuccess;
-    if (nqp > 2147483647LL) return hipErrorInvalidValue;
+    if (n <= 0) return hipSuccess;
+    if (n > 2147483647LL || nqp < 1 || nqp > n) return hipErrorInvalidValue;
     switch (nm) {
-        case 3: return go_v3_rot<3>(X, nqp, E2, E3, V, s);
-        case 6: return go_v3_rot<6>(X, nqp, E2, E3, V, s);
-        case 9: return go_v3_rot<9>(X, nqp, E2, E3, V, s);
-        case 12: return go_v3_rot<12>(X, nqp, E2, E3, V, s);
-        case 15: return go_v3_rot<15>(X, nqp, E2, E3, V, s);
-        case 18: return go_v3_rot<18>(X, nqp, E2, E3, V, s);
-        case 21: return go_v3_rot<21>(X, nqp, E2, E3, V, s);
-        case 24: return go_v3_rot<24>(X, nqp, E2, E3, V, s);
-        case 27: return go_v3_rot<27>(X, nqp, E2, E3, V, s);
-        case 30: return go_v3_rot<30>(X, nqp, E2, E3, V, s);
+        case 3: return go_v3_rot<3>(X, n, (int)nqp, E2, E3, V, s);
+        case 6: return go_v3_rot<6>(X, n, (int)nqp, E2, E3, V, s);
+        case 9: return go_v3_rot<9>(X, n, (int)nqp, E2, E3, V, s);
+        case 12: return go_v3_rot<12>(X, n, (int)nqp, E2, E3, V, s);
+        case 15: return go_v3_rot<15>(X, n, (int)nqp, E2, E3, V, s);
+        case 18: return go_v3_rot<18>(X, n, (int)nqp, E2, E3, V, s);
+        case 21: return go_v3_rot<21>(X, n, (int)nqp, E2, E3, V, s);
+        case 24: return go_v3_rot<24>(X, n, (int)nqp, E2, E3, V, s);
+        case 27: return go_v3_rot<27>(X, n, (int)nqp, E2, E3, V, s);
+        case 30: return go_v3_rot<30>(X, n, (int)nqp, E2, E3, V, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -92,8 +92,10 @@ template <int TM, int TN, int WPS, class BT>
 __global__ __launch_bounds__(256, WPS) void zgemm_kernel(const cd* __restrict__ A, int64_t lda,
                                                       const BT* __restrict__ B, int64_t ldb,
                                                       cd* __restrict__ C, int64_t ldc, int64_t M,
-                                                      int64_t N, int K) {
+                                                      int64_t N, int K, int64_t sb, int64_t sc) {
     using Z = ZgemmB<BT>;
+    B += blockIdx.z * sb;  // product z: the same A
+    C += blockIdx.z * sc;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
     const int64_t m0 = (int64_t)blockIdx.y * (16 * TM);
@@ -177,8 +179,10 @@ constexpr int kKSplit = 8;
 template <class BT>
 __global__ __launch_bounds__(64 * kKSplit) void zgemm_ksplit_kernel(
     const cd* __restrict__ A, int64_t lda, const BT* __restrict__ B, int64_t ldb,
-    cd* __restrict__ C, int64_t ldc, int64_t M, int64_t N, int K) {
+    cd* __restrict__ C, int64_t ldc, int64_t M, int64_t N, int K, int64_t sb, int64_t sc) {
     using Z = ZgemmB<BT>;
+    B += blockIdx.z * sb;
+    C += blockIdx.z * sc;
     __shared__ cd sC[kKSplit][256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, lk = lane >> 4;
@@ -208,29 +212,31 @@ __global__ __launch_bounds__(64 * kKSplit) void zgemm_ksplit_kernel(
 
 template <class BT>
 static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* C, int64_t ldc,
-                        int64_t M, int64_t N, int K, hipStream_t s) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    if (K <= 0) return hipErrorInvalidValue;
+                        int64_t M, int64_t N, int K, hipStream_t s, int nb = 1, int64_t sb = 0,
+                        int64_t sc = 0) {
+    if (M <= 0 || N <= 0 || nb <= 0) return hipSuccess;
+    if (K <= 0 || nb > 65535) return hipErrorInvalidValue;
     auto go = [&](auto kernel, int tm, int tn) {
-        dim3 grid((unsigned)((N + 64 * tn - 1) / (64 * tn)), (unsigned)((M + 16 * tm - 1) / (16 * tm)));
+        dim3 grid((unsigned)((N + 64 * tn - 1) / (64 * tn)), (unsigned)((M + 16 * tm - 1) / (16 * tm)),
+                  (unsigned)nb);
         // A real B of few rows (dynamical matrices, 27 vectors) gains nothing from a split
         // and keeps the order of its sum (see EigShape::SORTED); one tile a wave instead.
-        if (sizeof(BT) == 8 && K <= 64 && (int64_t)grid.x * grid.y < 1024 && M <= 16 * 65535) {
-            grid = dim3((unsigned)((N + 63) / 64), (unsigned)((M + 15) / 16));
+        if (sizeof(BT) == 8 && K <= 64 && (int64_t)grid.x * grid.y * nb < 1024 && M <= 16 * 65535) {
+            grid = dim3((unsigned)((N + 63) / 64), (unsigned)((M + 15) / 16), (unsigned)nb);
             hipLaunchKernelGGL((zgemm_kernel<1, 1, 4, BT>), grid, dim3(256), 0, s, A, lda, B, ldb, C,
-                               ldc, M, N, K);
+                               ldc, M, N, K, sb, sc);
             return hipGetLastError();
         }
         // Under four work-groups (one wave per SIMD each) per CU the tiles wait on their
         // loads: 13,824 points x 256 x 343, 864 work-groups, 243 us against 187 us with K
         // split; 301 points, 20 work-groups, 47 against 12 us.  (Also rows too long for
         // the tiles' 32-bit offsets.)
-        if ((int64_t)grid.x * grid.y < 1024 || lda > ((int64_t)1 << 24)) {
-            grid = dim3((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16));
+        if ((int64_t)grid.x * grid.y * nb < 1024 || lda > ((int64_t)1 << 24)) {
+            grid = dim3((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16), (unsigned)nb);
             hipLaunchKernelGGL(zgemm_ksplit_kernel<BT>, grid, dim3(64 * kKSplit), 0, s, A, lda, B,
-                               ldb, C, ldc, M, N, K);
+                               ldb, C, ldc, M, N, K, sb, sc);
         } else {
-            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, M, N, K);
+            hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, M, N, K, sb, sc);
         }
         return hipGetLastError();
     };
@@ -243,12 +249,20 @@ static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* 
     if (M <= 16) return go(zgemm_kernel<1, 4, 3, BT>, 1, 4);
     if (M <= 32) return go(zgemm_kernel<2, 2, 3, BT>, 2, 2);
     if (M <= 64) return go(zgemm_kernel<4, 2, 2, BT>, 4, 2);
+    // Tall and wide: two by two tiles (4 products of 1,024 q' x 3,375 x 125: 284 us, 315
+    // with four row tiles; 64,000 q x 3,840 x 343: 11.6 and 12.5 ms).
+    if (N >= 1024) return go(zgemm_kernel<2, 2, 3, BT>, 2, 2);
     return go(zgemm_kernel<4, 1, 2, BT>, 4, 1);
 }
 
 hipError_t launch_zgemm(const cd* A, int64_t lda, const cd* B, int64_t ldb, cd* C, int64_t ldc,
                         int64_t M, int64_t N, int K, hipStream_t s) {
     return zgemm<cd>(A, lda, B, ldb, C, ldc, M, N, K, s);
+}
+hipError_t launch_zgemm_batch(const cd* A, int64_t lda, const cd* B, int64_t ldb, int64_t sb, cd* C,
+                              int64_t ldc, int64_t sc, int nb, int64_t M, int64_t N, int K,
+                              hipStream_t s) {
+    return zgemm<cd>(A, lda, B, ldb, C, ldc, M, N, K, s, nb, sb, sc);
 }
 hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_t ldb, cd* C,
                                int64_t ldc, int64_t M, int64_t N, int K, hipStream_t s) {

@@ -459,6 +459,32 @@ def test_v3_rotation_tiles(lib, nat):
     assert np.max(np.abs(np.abs(V.cpu().numpy()) - ref)) < V3_BOUND * np.max(ref)
 
 
+def test_v3_q_batches(lib):
+    """Several q in one product and rotation against one q at a time, which a workspace
+    without room for more takes."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem3, Library
+    nat, nq, nqp = 5, 5, 2050
+    s = synth.small_system(3, n_wannier=1, n_atoms=nat, r=1)
+    r, phi3 = synth.third_order_constants(3, nat)
+    g = np.random.default_rng(3)
+    q = torch.from_numpy(g.uniform(-1, 1, size=(nq, 3))).cuda()
+    qp = torch.from_numpy(g.uniform(-1, 1, size=(nqp, 3))).cuda()
+    d3 = DeviceSystem3.from_host(s, r, phi3)
+    nm = 3 * nat
+    V, one = (torch.zeros((nq, nqp, nm, nm, nm), dtype=torch.complex128, device="cuda")
+              for _ in range(2))
+    x_bytes = nqp * nm**3 * 16
+    small = Library(0, workspace_budget=4 * x_bytes)  # (E, D and z of the 10,250 q'' take one)
+    try:
+        lib.interp_v3(d3, q, qp, V)
+        small.interp_v3(d3, q, qp, one)
+    finally:
+        small.close()
+    torch.cuda.synchronize()
+    assert float((V - one).abs().max()) < 1e-13 * float(V.abs().max())
+
+
 # ---------------------------------------------------------------------------
 # Philox streams, initialisation, training set, gather
 # ---------------------------------------------------------------------------
