@@ -86,7 +86,7 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
                 // S[i, (R', sa, s'b, s''c)] = sum_R e^{-i 2 pi q.R} Phi3[R, ...]
                 Timer t1(h, s, "v3_stage1");
                 HIPCHK(h, launch_zgemm_real_b(P1, n1, sys->phi3, (int64_t)n2 * m3, S,
-                                              (int64_t)n2 * m3, nb, (int64_t)n2 * m3, n1, s));
+                                              (int64_t)n2 * m3, nb, (int64_t)n2 * m3, n1, false, s));
                 t1.done();
                 HIPCHK(h, launch_v3_fold(S, nb, n2, nm, E1 + i0 * nm * nm, T, s));
                 for (int64_t i = 0; i < nb; i += xb) {

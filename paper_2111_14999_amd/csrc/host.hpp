@@ -369,8 +369,9 @@ inline void electron_bands_dev(Handle* h, Arena& ar, const phoebe_system* sys, c
     te.done();
 }
 
-// ordered: by the solver whose rounding does not change (launch_eig_herm_ordered), where the
-// modes themselves are handed out and q may be any point.
+// ordered: D(q) summed in the order of the lattice list and solved by the solver whose
+// rounding does not change (launch_eig_herm_ordered), where the modes themselves are handed
+// out and q may be any point: a q then has the same modes, bit for bit, in every call.
 // E comes as [q, mode, atom axis], or with e_by_mode false as [q, atom axis, mode], the
 // eigensolver's own order, for the rate kernels, whose lanes run over the modes: written and
 // read in whole cache lines (64,000 points: 252 -> 113 us to write; the line kernel, which
@@ -389,7 +390,7 @@ inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int
     HIPCHK(h, launch_phase_table(frac, idx, m, np, rd_d, nR, P, nR, s));
     HIPCHK(h, launch_mass_weight(sys->phi_r, sys->mass, nR, nm, phic, s));
     HIPCHK(h, launch_zgemm_real_b(P, nR, phic, (int64_t)nm * nm, D, (int64_t)nm * nm, np,
-                                  (int64_t)nm * nm, nR, s));
+                                  (int64_t)nm * nm, nR, ordered, s));
     HIPCHK(h, ordered ? launch_eig_herm_ordered(D, nm, np, lam, z, s)
                       : launch_eig_herm(D, nm, np, lam, z, false, s));
     HIPCHK(h, launch_phonon_post(lam, z, sys->mass, sys->n_atoms, np, omega_min, kT, omega, E,

@@ -21,9 +21,11 @@ hipError_t launch_zgemm_batch(const cd* A, int64_t lda, const cd* B, int64_t ldb
                               int64_t ldc, int64_t sc, int nb, int64_t M, int64_t N, int K,
                               hipStream_t s);
 
-// The same with a real B (half its bytes, two MFMAs per product).
+// The same with a real B (half its bytes, two MFMAs per product).  in_order: every element
+// is summed along ascending k, for any M (otherwise the form taken, and with it the order of
+// the sum, depends on the number of rows).
 hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_t ldb, cd* C,
-                               int64_t ldc, int64_t M, int64_t N, int K, hipStream_t s);
+                               int64_t ldc, int64_t M, int64_t N, int K, bool in_order, hipStream_t s);
 
 // Mass-weighted force constants Phi(R)/sqrt(M_s M_s').
 hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int nm, double* out,

@@ -213,15 +213,17 @@ __global__ __launch_bounds__(64 * kKSplit) void zgemm_ksplit_kernel(
 template <class BT>
 static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* C, int64_t ldc,
                         int64_t M, int64_t N, int K, hipStream_t s, int nb = 1, int64_t sb = 0,
-                        int64_t sc = 0) {
+                        int64_t sc = 0, bool in_order = false) {
     if (M <= 0 || N <= 0 || nb <= 0) return hipSuccess;
     if (K <= 0 || nb > 65535) return hipErrorInvalidValue;
     auto go = [&](auto kernel, int tm, int tn) {
         dim3 grid((unsigned)((N + 64 * tn - 1) / (64 * tn)), (unsigned)((M + 16 * tm - 1) / (16 * tm)),
                   (unsigned)nb);
-        // A real B of few rows (dynamical matrices, 27 vectors) gains nothing from a split
-        // and keeps the order of its sum (see EigShape::SORTED); one tile a wave instead.
-        if (sizeof(BT) == 8 && K <= 64 && (int64_t)grid.x * grid.y * nb < 1024 && M <= 16 * 65535) {
+        // A real B of few rows (dynamical matrices, 27 vectors) gains nothing from a split;
+        // one tile a wave instead.  in_order: no split whatever K is, so that a row of C is the
+        // same bits in a call of any M (every unsplit tile sums along ascending k).
+        if ((in_order || (sizeof(BT) == 8 && K <= 64)) && (int64_t)grid.x * grid.y * nb < 1024 &&
+            M <= 16 * 65535 && lda <= ((int64_t)1 << 24)) {
             grid = dim3((unsigned)((N + 63) / 64), (unsigned)((M + 15) / 16), (unsigned)nb);
             hipLaunchKernelGGL((zgemm_kernel<1, 1, 4, BT>), grid, dim3(256), 0, s, A, lda, B, ldb, C,
                                ldc, M, N, K, sb, sc);
@@ -265,8 +267,8 @@ hipError_t launch_zgemm_batch(const cd* A, int64_t lda, const cd* B, int64_t ldb
     return zgemm<cd>(A, lda, B, ldb, C, ldc, M, N, K, s, nb, sb, sc);
 }
 hipError_t launch_zgemm_real_b(const cd* A, int64_t lda, const double* B, int64_t ldb, cd* C,
-                               int64_t ldc, int64_t M, int64_t N, int K, hipStream_t s) {
-    return zgemm<double>(A, lda, B, ldb, C, ldc, M, N, K, s);
+                               int64_t ldc, int64_t M, int64_t N, int K, bool in_order, hipStream_t s) {
+    return zgemm<double>(A, lda, B, ldb, C, ldc, M, N, K, s, 1, 0, 0, in_order);
 }
 
 // ---------------------------------------------------------------------------

@@ -132,3 +132,43 @@ def test_phonon_solvers(lib, nat):
     # omega = sqrt(lambda) c: an error of 1e-13 of the largest lambda
     w2 = np.max(om) ** 2
     assert np.max(np.abs(om ** 2 - only ** 2)) < 2e-13 * w2
+
+
+def _wide_list(s, seed):
+    """The force constants on a list of 125 vectors, with small symmetric ones beyond the first
+    shell and the acoustic sum rule kept."""
+    import dataclasses
+    nat, nm = s.n_atoms, s.n_modes
+    rd = synth.box_vectors(2)
+    phi = 1e-3 * np.random.default_rng(seed).standard_normal((125, nm, nm))
+    row = {tuple(r): i for i, r in enumerate(rd.tolist())}
+    for r, p in zip(s.rd.tolist(), s.phi_r):
+        phi[row[tuple(r)]] += p
+    phi = 0.5 * (phi + np.swapaxes(phi[::-1], 1, 2))
+    total = phi.reshape(125, nat, 3, nat, 3).sum(axis=(0, 3))  # [s, a, b]
+    for a in range(nat):
+        phi[62].reshape(nat, 3, nat, 3)[a, :, a, :] -= 0.5 * (total[a] + total[a].T)
+    return dataclasses.replace(s, rd=rd, phi_r=phi)
+
+
+@pytest.mark.parametrize("nat,wide", [(2, False), (5, False), (5, True), (7, True)])
+def test_phonon_modes_call_size(lib, nat, wide):
+    """The modes of a q are the same bits alone, among 200 and among 20,000 others: near Gamma
+    another order of the sum over R turns the acoustic modes into one another."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(80 + nat, n_wannier=1, n_atoms=nat, r=1)
+    ds = DeviceSystem.from_host(_wide_list(s, nat) if wide else s, with_coupling=False)
+    rng = np.random.default_rng(nat)
+    near = np.concatenate([x * rng.standard_normal((3, 3)) for x in (1e-2, 1e-3, 1e-4, 1e-5)])
+    rest = rng.uniform(-1, 1, size=(20000, 3))
+    nm, out = 3 * nat, []
+    for n in (0, 200, 20000):
+        q = torch.from_numpy(np.concatenate([near, rest[:n]])).cuda()
+        om = torch.zeros((12 + n, nm), dtype=torch.float64, device="cuda")
+        z = torch.zeros((12 + n, nm, nm), dtype=torch.complex128, device="cuda")
+        lib.phonon_modes(ds, q, om, z)
+        out.append((om[:12].cpu().numpy(), z[:12].cpu().numpy()))
+    for om, z in out[1:]:
+        assert np.array_equal(om, out[0][0])
+        assert np.array_equal(z, out[0][1])
