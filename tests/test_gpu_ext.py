@@ -593,3 +593,42 @@ def test_check_finite_and_nomem():
         assert "budget" in str(e.value)
     finally:
         small.close()
+
+
+@pytest.mark.parametrize("nat", [2, 3, 5])
+def test_v3_modes_near_gamma(lib, nat):
+    """V3 is that of the modes phonon_modes hands out, also where q'' comes so near Gamma that
+    the rounding of D decides what its acoustic modes are: the contraction in numpy with
+    the library's own modes."""
+    torch = torch_cuda()
+    from oracle.coupling import phonon_length
+    from paper_2111_14999_amd import DeviceSystem, DeviceSystem3
+    s = synth.small_system(50 + nat, n_wannier=1, n_atoms=nat, r=1)
+    r, phi3 = synth.third_order_constants(50 + nat, nat)
+    keep = np.flatnonzero(np.abs(r).sum(axis=1) <= 1)
+    r = np.ascontiguousarray(r[keep])
+    phi3 = np.ascontiguousarray(phi3[np.ix_(keep, keep)])
+    g = np.random.default_rng(nat)
+    q = g.uniform(-0.5, 0.5, size=(3, 3))
+    qp = np.concatenate([-q + x * g.standard_normal((3, 3)) for x in (1e-3, 1e-4, 1e-5)])
+    nm, omega_min = 3 * nat, 1e-9
+    V = torch.zeros((3, 9, nm, nm, nm), dtype=torch.complex128, device="cuda")
+    lib.interp_v3(DeviceSystem3.from_host(s, r, phi3), torch.from_numpy(q).cuda(),
+                  torch.from_numpy(qp).cuda(), V, omega_min=omega_min)
+    ds = DeviceSystem.from_host(s, with_coupling=False)
+
+    def zl(pts):
+        om = torch.zeros((len(pts), nm), dtype=torch.float64, device="cuda")
+        z = torch.zeros((len(pts), nm, nm), dtype=torch.complex128, device="cuda")
+        lib.phonon_modes(ds, torch.from_numpy(pts).cuda(), om, z)
+        om, z = om.cpu().numpy(), z.cpu().numpy()
+        return z * np.repeat(phonon_length(om, s.mass, omega_min), 3, axis=1)
+
+    e1, e2 = zl(q), zl(qp)
+    e3 = zl(-(q[:, None] + qp[None]).reshape(-1, 3)).reshape(3, 9, nm, nm)
+    S = np.einsum("ir,rsabc->isabc", np.exp(-2j * np.pi * (q @ r.T)), phi3)
+    X = np.einsum("js,isabc->ijabc", np.exp(-2j * np.pi * (qp @ r.T)), S)
+    ref = np.einsum("ijabc,iau,jbv,ijcw->ijuvw", X, np.conj(e1), np.conj(e2), np.conj(e3), optimize=True)
+    # pair by pair: the lengths of the lowest modes grow as q'' falls
+    err = np.abs(V.cpu().numpy() - ref).max(axis=(2, 3, 4)) / np.abs(ref).max(axis=(2, 3, 4))
+    assert err.max() < V3_BOUND
