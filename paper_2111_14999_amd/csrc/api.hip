@@ -175,8 +175,9 @@ phoebe_status phoebe_gpu_phonon_modes(void* handle, const phoebe_system* sys,
         scan_finite(h, sys, false, true, false, s);
         auto plan = [&](Arena& ar) {
             int32_t* rd = upload_r(h, ar, sys->rd, sys->n_rd, s);
+            // (omega is the same bits with and without z)
             phonon_dev(h, ar, sys, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, 0.0, 0.0, omega_out,
-                       nullptr, nullptr, reinterpret_cast<cd*>(z_out), s, true, z_out != nullptr);
+                       nullptr, nullptr, reinterpret_cast<cd*>(z_out), s, true, true);
         };
         Arena dry(nullptr);
         plan(dry);

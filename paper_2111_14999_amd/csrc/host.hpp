@@ -391,7 +391,7 @@ inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int
     HIPCHK(h, launch_mass_weight(sys->phi_r, sys->mass, nR, nm, phic, s));
     HIPCHK(h, launch_zgemm_real_b(P, nR, phic, (int64_t)nm * nm, D, (int64_t)nm * nm, np,
                                   (int64_t)nm * nm, nR, ordered, s));
-    HIPCHK(h, ordered ? launch_eig_herm_ordered(D, nm, np, lam, z, s)
+    HIPCHK(h, ordered ? launch_eig_herm_ordered(D, nm, np, lam, z_out || E ? z : nullptr, s)
                       : launch_eig_herm(D, nm, np, lam, z, false, s));
     HIPCHK(h, launch_phonon_post(lam, z, sys->mass, sys->n_atoms, np, omega_min, kT, omega, E,
                                  e_by_mode, nb, s));

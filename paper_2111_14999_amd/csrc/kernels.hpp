@@ -36,7 +36,8 @@ hipError_t launch_mass_weight(const double* phi, const double* mass, int nR, int
 // (the rate path reads each eigenvector contiguously).
 hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, bool vt,
                            hipStream_t s);
-// The same for n = 3, 6, ..., 30 in an order of operations that stays (V as columns).
+// The same for n = 3, 6, ..., 30 in an order of operations that stays (V as columns, or
+// NULL: the eigenvalues alone, the same bits).
 hipError_t launch_eig_herm_ordered(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s);
 
 // Phonon post-processing: omega = C_OMEGA sqrt(max(lam, 0)); e[q, sa, nu] =

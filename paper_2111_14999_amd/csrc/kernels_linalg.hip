@@ -718,7 +718,8 @@ __device__ inline void rr_pair(int k, int round, int np, int& p, int& q) {
     q = a < b ? b : a;
 }
 
-template <int NT>
+// Without VEC the rotations of V and its store are left out: the eigenvalues are the same bits.
+template <int NT, bool VEC>
 __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, int n_arg,
                                                       double* __restrict__ w_out,
                                                       cd* __restrict__ V_out) {
@@ -728,8 +729,8 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
     // odd row stride: 16 lanes walking down a column of 16-byte elements hit 16
     // distinct 4-bank groups (an even stride such as 16 would serialise them)
     const int ld = n | 1;
-    cd* V = A + n * ld;
-    double* rc = reinterpret_cast<double*>(V + n * ld);  // [n/2+1] c
+    cd* V = A + n * ld;  // VEC
+    double* rc = reinterpret_cast<double*>(A + (VEC ? 2 : 1) * n * ld);  // [n/2+1] c
     double* rs = rc + (n / 2 + 1);                         // s
     cd* re = reinterpret_cast<cd*>(rs + (n / 2 + 1));      // e^{i phi}
     int* rp = reinterpret_cast<int*>(re + (n / 2 + 1));    // p
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
     for (int i = lane; i < n * n; i += 64) {
         const int r = i / n, c = i % n;
         A[r * ld + c] = Ag[i];
-        V[r * ld + c] = cd{r == c ? 1.0 : 0.0, 0.0};
+        if constexpr (VEC) V[r * ld + c] = cd{r == c ? 1.0 : 0.0, 0.0};
     }
     __syncthreads();
     const int np = n + (n & 1);
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
             }
             __syncthreads();
             // columns: A'_ip = c A_ip - s conj(e) A_iq ; A'_iq = s e A_ip + c A_iq ; same for V
-            for (int it = lane; it < 2 * half * n; it += 64) {
+            for (int it = lane; it < (VEC ? 2 : 1) * half * n; it += 64) {
                 const int which = it / (half * n);
                 const int r = it % (half * n);
                 const int k = r / n, i = r % n;
@@ -850,8 +851,10 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
             rank += (wj < wi) || (wj == wi && j < i);
         }
         w_out[b * n + rank] = wi;
-        cd* Vg = V_out + b * (int64_t)n * n;
-        for (int r = 0; r < n; ++r) Vg[r * n + rank] = V[r * ld + i];
+        if constexpr (VEC) {
+            cd* Vg = V_out + b * (int64_t)n * n;
+            for (int r = 0; r < n; ++r) Vg[r * n + rank] = V[r * ld + i];
+        }
     }
 }
 
@@ -863,13 +866,13 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
 // {2I, 2I + 1}: every lane reads, rotates and writes its own elements, and a
 // round needs one barrier after the parameters and one after the update.
 // The pair order, the skip test and the stopping rule are those above.
-template <int NT>
+template <int NT, bool VEC>
 __global__ __launch_bounds__(64) void eig_ordered_blk_kernel(cd* __restrict__ Aall, int n_arg,
                                                           double* __restrict__ w_out,
                                                           cd* __restrict__ V_out) {
     const int n = NT > 0 ? NT : n_arg;
     constexpr int LD = 17;  // odd row stride (see above)
-    __shared__ cd A[16 * LD], V[16 * LD];
+    __shared__ cd A[16 * LD], V[VEC ? 16 * LD : 1];
     __shared__ double prm[8][4];  // c, s, e of every pair of the round
     const int64_t b = blockIdx.x;
     const int lane = threadIdx.x;
@@ -880,7 +883,7 @@ __global__ __launch_bounds__(64) void eig_ordered_blk_kernel(cd* __restrict__ Aa
     for (int i = lane; i < n * n; i += 64) {
         const int r = i / n, c = i - r * n;
         A[r * LD + c] = Ag[i];
-        V[r * LD + c] = cd{r == c ? 1.0 : 0.0, 0.0};
+        if constexpr (VEC) V[r * LD + c] = cd{r == c ? 1.0 : 0.0, 0.0};
     }
     __syncthreads();
     const double eps2 = 4.9e-32;  // (2.2e-16)^2
@@ -967,7 +970,7 @@ __global__ __launch_bounds__(64) void eig_ordered_blk_kernel(cd* __restrict__ Aa
                     if (qIok) A[qI * LD + pJ] = x10;
                     if (qIok && qJok) A[qI * LD + qJ] = x11;
                 }
-                if (sJ != 0.0) {  // V columns p_J, q_J on rows 2I, 2I + 1
+                if (VEC && sJ != 0.0) {  // V columns p_J, q_J on rows 2I, 2I + 1
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const int r = 2 * I + h;
@@ -994,31 +997,33 @@ __global__ __launch_bounds__(64) void eig_ordered_blk_kernel(cd* __restrict__ Aa
             rank += (wj < wi) || (wj == wi && j < i);
         }
         w_out[b * n + rank] = wi;
-        cd* Vg = V_out + b * (int64_t)n * n;
-        for (int r = 0; r < n; ++r) Vg[r * n + rank] = V[r * LD + i];
+        if constexpr (VEC) {
+            cd* Vg = V_out + b * (int64_t)n * n;
+            for (int r = 0; r < n; ++r) Vg[r * n + rank] = V[r * LD + i];
+        }
     }
 }
 
-hipError_t launch_eig_herm_ordered(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s) {
-    if (batch <= 0) return hipSuccess;
+template <bool VEC>
+static hipError_t go_eig_ordered(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s) {
     const int h = n / 2 + 1;
-    const size_t shm = (size_t)2 * n * (n + 1) * sizeof(cd) + 2 * h * sizeof(double) +
+    const size_t shm = (size_t)(VEC ? 2 : 1) * n * (n | 1) * sizeof(cd) + 2 * h * sizeof(double) +
                        h * sizeof(cd) + 2 * h * sizeof(int);
     for (int64_t b0 = 0; b0 < batch; b0 += 2000000000LL) {
         const int64_t nb = batch - b0 < 2000000000LL ? batch - b0 : 2000000000LL;
         cd* Ab = A + b0 * n * n;
         double* wb = w + b0 * n;
-        cd* Vb = V + b0 * n * n;
+        cd* Vb = VEC ? V + b0 * n * n : nullptr;
         switch (n) {
-#define PHX_EIG(NV)                                                                                \
-    case NV:                                                                                       \
-        hipLaunchKernelGGL(eig_ordered_kernel<NV>, dim3((unsigned)nb), dim3(64), shm, s, Ab, n, wb, \
-                           Vb);                                                                    \
+#define PHX_EIG(NV)                                                                                 \
+    case NV:                                                                                        \
+        hipLaunchKernelGGL((eig_ordered_kernel<NV, VEC>), dim3((unsigned)nb), dim3(64), shm, s, Ab, \
+                           n, wb, Vb);                                                              \
         break;
-#define PHX_EIGB(NV)                                                                               \
-    case NV:                                                                                       \
-        hipLaunchKernelGGL(eig_ordered_blk_kernel<NV>, dim3((unsigned)nb), dim3(64), 0, s, Ab, n,  \
-                           wb, Vb);                                                                \
+#define PHX_EIGB(NV)                                                                                \
+    case NV:                                                                                        \
+        hipLaunchKernelGGL((eig_ordered_blk_kernel<NV, VEC>), dim3((unsigned)nb), dim3(64), 0, s,   \
+                           Ab, n, wb, Vb);                                                          \
         break;
             PHX_EIGB(3) PHX_EIGB(6) PHX_EIGB(9) PHX_EIGB(12) PHX_EIGB(15)
             PHX_EIG(18) PHX_EIG(21) PHX_EIG(24) PHX_EIG(27) PHX_EIG(30)
@@ -1028,6 +1033,11 @@ hipError_t launch_eig_herm_ordered(cd* A, int n, int64_t batch, double* w, cd* V
         }
     }
     return hipGetLastError();
+}
+
+hipError_t launch_eig_herm_ordered(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s) {
+    if (batch <= 0) return hipSuccess;
+    return V ? go_eig_ordered<true>(A, n, batch, w, V, s) : go_eig_ordered<false>(A, n, batch, w, V, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -172,3 +172,21 @@ def test_phonon_modes_call_size(lib, nat, wide):
     for om, z in out[1:]:
         assert np.array_equal(om, out[0][0])
         assert np.array_equal(z, out[0][1])
+
+
+@pytest.mark.parametrize("nat", range(1, 11))
+def test_frequencies_alone(lib, nat):
+    """omega has the same bits whether z is asked for or not, near Gamma as well."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(80 + nat, n_wannier=1, n_atoms=nat, r=1)
+    ds = DeviceSystem.from_host(s, with_coupling=False)
+    rng = np.random.default_rng(nat)
+    q = np.concatenate([x * rng.standard_normal((20, 3)) for x in (1.0, 1e-2, 1e-4, 0.0)])
+    nm = 3 * nat
+    om, only = (torch.zeros((80, nm), dtype=torch.float64, device="cuda") for _ in range(2))
+    z = torch.zeros((80, nm, nm), dtype=torch.complex128, device="cuda")
+    lib.phonon_modes(ds, torch.from_numpy(q).cuda(), om, z)
+    lib.phonon_modes(ds, torch.from_numpy(q).cuda(), only)
+    assert float(om.max()) > 0
+    assert torch.equal(om, only)
