@@ -791,7 +791,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             T.st_kmesh = ar.take<int32_t>((size_t)rows_cap * nW);
             T.st_mlo = ar.take<int32_t>((size_t)rows_cap * nW);
             T.st_mhi = ar.take<int32_t>((size_t)rows_cap * nW);
-            T.st_urow = ar.take<int32_t>((size_t)rows_cap * nW);
+            if (re_reg && fold_fused) T.st_urow = ar.take<int32_t>((size_t)rows_cap * nW);
             if (factored) {
                 T.Pax = ar.take<cd>((size_t)(mesh.n0 + mesh.n1 + mesh.n2) * Wbox);
             }
@@ -1294,7 +1294,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 ReBatch rb{(int)o[0], (int)o[1], rbd + o[2], rbd + o[3], rbd + o[4],
                            rbd + o[5], rbd + o[6], rbd + o[7], all_planes ? rbd + o[8] : nullptr,
                            rbd + o[10]};
-                FoldOut fo{rbd + o[9], T.st_kmesh + sbeg, T.st_band + sbeg, T.st_urow + sbeg, T.U,
+                FoldOut fo{rbd + o[9], T.st_kmesh + sbeg, T.st_band + sbeg,
+                           T.st_urow ? T.st_urow + sbeg : nullptr, T.U,
                            nW, nm, n_rp, rp_pad, nc_pad, Fbuf};
                 const FoldOut* fop = fold_fused ? &fo : nullptr;
                 // written once: G, or F when the fold is applied here

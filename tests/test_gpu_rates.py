@@ -468,3 +468,33 @@ def test_mesh_bands_by_axes(lib, nW, r, mesh):
     _, ref, _, _ = _gpu_rates(lib, twice, mesh, par, k_idx=k_idx, ds=DeviceSystem.from_host(twice))
     assert np.max(np.abs(ref)) > 0
     assert rel_err(got, ref)[0] < 1e-10
+
+
+@pytest.mark.parametrize("lists,precision,nbytes", [
+    (False, "fp64", 11466600), (False, "fp32", 5849960),
+    (True, "fp64", 11432080), (True, "bf16x3", 6463120),
+])
+def test_workspace_need(lib, lists, precision, nbytes):
+    """The direct routes ask for no scratch of the one-pass Re sum: calls that fitted these
+    budgets exactly still do."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem, Library
+    s = synth.small_system(3, n_wannier=5, n_atoms=1, r=1)
+    par = dict(mu=0.0, kT=constants.kT_of(300.0), sigma=0.1, win_lo=-1e30, win_hi=1e30, omega_min=1e-4)
+    ds = DeviceSystem.from_host(s)
+    gamma = torch.zeros((210, 5), dtype=torch.float64, device="cuda")
+    kw = {}
+    if lists:
+        g = np.random.default_rng(0)
+        kw = dict(k_idx=torch.arange(20, dtype=torch.int32, device="cuda"),
+                  q_lists=(torch.arange(0, 161, 8, dtype=torch.int64, device="cuda"),
+                           torch.from_numpy(g.integers(0, 210, 160).astype(np.int32)).cuda(),
+                           torch.from_numpy(g.uniform(0.5, 1.5, 160)).cuda()))
+    small = Library(0, workspace_budget=nbytes)
+    try:
+        small.set_mesh_sum("direct")
+        n = small.scatter_rates(ds, (6, 5, 7), par, gamma, precision=precision, **kw)
+    finally:
+        small.close()
+    assert n == (20 if lists else 210)
+    assert float(gamma.max()) > 0
