@@ -152,7 +152,11 @@ void grad_impl(Handle* h, const Net& net, const float* P, const float* X, const 
             split[l] = splits ? mlp_splits(o, i, B, &kchunk[l]) : 1;
             if (split[l] == 1) kchunk[l] = B;
             W[l] = split[l] > 1 ? ar.take<float>((size_t)split[l] * o * i) : nullptr;
-            bs[l] = ar.take<double>((size_t)split[l] * o);
+            // The bias sums take the place of z of the layer, last read in the step before
+            // (the loss's, for the last layer).  They fit: at most B / 128 + 1 splits of 8
+            // bytes against 4 B each, and below three rows one split, against z and the
+            // activations next to it (the last layer has one output).
+            bs[l] = reinterpret_cast<double*>(Z[l]);
         }
         for (auto& d : dZ) d = ar.take<float>((size_t)B * std::max(net.width, 1));
         sums = ar.take<double>(256);

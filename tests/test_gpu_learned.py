@@ -392,3 +392,26 @@ def test_bf16_gradient_tiles(lib, n_in, width, depth, B):
     assert abs(loss - loss_b) < 1e-5 * loss_b
     assert abs(np.mean((y.cpu().numpy().astype(np.float64) - t) ** 2) - loss_b) < 1e-5 * loss_b
     assert np.all(np.abs(gg - g_b) <= 1e-3 * np.abs(g_b) + 3e-5 * gmax)
+
+
+@pytest.mark.parametrize("width,depth,B,nbytes", [
+    (1, 1, 1, 3840), (16, 2, 1, 4352), (64, 4, 64, 166656), (256, 4, 500, 5126400),
+    (512, 5, 4096, 100698368),
+])
+def test_bf16_gradient_workspace(lib, width, depth, B, nbytes):
+    """The smallest budgets the gradient has taken, where no weight gradient is split: the
+    same gradient up to the order of FP32 sums."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import Library
+    theta, X, t = (torch.from_numpy(a.astype(np.float32)).cuda() for a in _net_case(5, 22, width, depth, B))
+    out = []
+    small = Library(0, workspace_budget=nbytes)
+    try:
+        for L in (lib, small):
+            g = torch.full_like(theta, float("nan"))
+            out.append((L.mlp_grad(theta, X, t, g, 22, width, depth, precision="bf16"), g))
+    finally:
+        small.close()
+    assert out[0][0] == out[1][0]
+    # sums over B rows in FP32, split or not
+    assert float((out[0][1] - out[1][1]).abs().max()) <= 2e-5 * float(out[0][1].abs().max())
