@@ -64,7 +64,10 @@ hipError_t launch_phase_table(const double* frac, const int32_t* idx, Mesh m, in
 // BT = double: a real B (force constants), two MFMAs and half the B bytes.
 //
 // Rows and columns past the matrix read a clamped address (their results are not
-// stored) and k past K meets a zero A, so that no load sits under a lane branch.
+// stored) and a step past K reads the last one's and is never used, so that no load sits
+// under a lane branch; k past K meets a zero A in a last step of its own.  40,000 points x
+// 256 columns x 343 vectors: 505 us with loads under lane branches, 568 with A zeroed in
+// every load, 463 so; 27 vectors 58, 61 and 53.
 // ---------------------------------------------------------------------------
 template <class BT>
 struct ZgemmB;
@@ -113,21 +116,20 @@ __global__ __launch_bounds__(256, WPS) void zgemm_kernel(const cd* __restrict__ 
     const BT* B0 = B + n0;
     const int mr = M - m0 < 16 * TM ? (int)(M - m0) : 16 * TM;  // rows and columns of this tile
     const int nc = N - n0 < 16 * TN ? (int)(N - n0) : 16 * TN;
-    int ra[TM], cb[TN];
+    const cd* pa[TM];
+    int cb[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) ra[i] = min(16 * i + li, mr - 1) * (int)lda;
+    for (int i = 0; i < TM; ++i) pa[i] = A0 + min(16 * i + li, mr - 1) * (int)lda;
 #pragma unroll
     for (int j = 0; j < TN; ++j) cb[j] = min(16 * j + li, nc - 1);
+    const int klast = (K - 1) & ~3;  // first k of the last step
     auto load = [&](int k0, cd* av, BT* bv) {
-        const int k = k0 + lk;
-        const int kc = k < K ? k : K - 1;
+        const int kc = min(min(k0, klast) + lk, K - 1);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            av[i] = A0[ra[i] + kc];
-            if (k >= K) av[i] = cd{0.0, 0.0};
-        }
+        for (int i = 0; i < TM; ++i) av[i] = pa[i][kc];
+        const BT* b = B0 + (int64_t)kc * ldb;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bv[j] = B0[(int64_t)kc * ldb + cb[j]];
+        for (int j = 0; j < TN; ++j) bv[j] = b[cb[j]];
     };
     // operands are prefetched two k-steps ahead: one step of MFMA work is
     // shorter than the HBM latency of the streamed B operand
@@ -135,12 +137,9 @@ __global__ __launch_bounds__(256, WPS) void zgemm_kernel(const cd* __restrict__ 
     BT b_cur[TN], b_n1[TN];
     load(0, a_cur, b_cur);
     load(4, a_n1, b_n1);
-    for (int k0 = 0; k0 < K; k0 += 4) {
-        cd a_n2[TM];
-        BT b_n2[TN];
-        load(k0 + 8, a_n2, b_n2);
-        // two passes over the tiles, so that dependent MFMAs on one accumulator
-        // are 2 TM TN - 1 instructions apart
+    // two passes over the tiles, so that dependent MFMAs on one accumulator
+    // are 2 TM TN - 1 instructions apart
+    auto step = [&] {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -149,6 +148,13 @@ __global__ __launch_bounds__(256, WPS) void zgemm_kernel(const cd* __restrict__ 
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) Z::step2(a_cur[i], b_cur[j], cr[i][j], ci[i][j]);
+    };
+    const int kfull = K & ~3;
+    for (int k0 = 0; k0 < kfull; k0 += 4) {
+        cd a_n2[TM];
+        BT b_n2[TN];
+        load(k0 + 8, a_n2, b_n2);
+        step();
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             a_cur[i] = a_n1[i];
@@ -159,6 +165,12 @@ __global__ __launch_bounds__(256, WPS) void zgemm_kernel(const cd* __restrict__ 
             b_cur[j] = b_n1[j];
             b_n1[j] = b_n2[j];
         }
+    }
+    if (kfull < K) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            if (kfull + lk >= K) a_cur[i] = cd{0.0, 0.0};
+        step();
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -219,21 +231,23 @@ static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* 
     auto go = [&](auto kernel, int tm, int tn) {
         dim3 grid((unsigned)((N + 64 * tn - 1) / (64 * tn)), (unsigned)((M + 16 * tm - 1) / (16 * tm)),
                   (unsigned)nb);
-        // A real B of few rows (dynamical matrices, 27 vectors) gains nothing from a split;
-        // one tile a wave instead.  in_order: no split whatever K is, so that a row of C is the
-        // same bits in a call of any M (every unsplit tile sums along ascending k).
-        if ((in_order || (sizeof(BT) == 8 && K <= 64)) && (int64_t)grid.x * grid.y * nb < 1024 &&
-            M <= 16 * 65535 && lda <= ((int64_t)1 << 24)) {
+        // Under four work-groups (one wave per SIMD each) per CU the tiles wait on their
+        // loads, and K is split over waves: 13,824 points x 256 x 343, 864 work-groups, 243 us
+        // against 187 us split; 301 points, 20 work-groups, 52 against 12 us.  (The two by two
+        // tiles wait less: down to half as many, 3,000 x 1,024 x 343, 136 us, 158 split.)  Up to
+        // 32 k, a step or less for each of the waves, the split has nothing to share out and one
+        // tile a wave is as quick or quicker: 14,000 x 256 x 27, 32 us split, 23 so.  A real B
+        // (dynamical matrices) gains nothing from a split up to 64.  in_order: no split
+        // whatever K is, so that a row of C is the same bits in a call of any M (every unsplit
+        // tile sums along ascending k).  (Rows too long for the tiles' 32-bit offsets are split
+        // as well.)
+        const bool few = (int64_t)grid.x * grid.y * nb < (tm == 2 && M > 64 ? 512 : 1024);
+        const bool long_rows = lda > ((int64_t)1 << 24);
+        if (few && !long_rows && M <= 16 * 65535 && (in_order || K <= (sizeof(BT) == 8 ? 64 : 32))) {
             grid = dim3((unsigned)((N + 63) / 64), (unsigned)((M + 15) / 16), (unsigned)nb);
             hipLaunchKernelGGL((zgemm_kernel<1, 1, 4, BT>), grid, dim3(256), 0, s, A, lda, B, ldb, C,
                                ldc, M, N, K, sb, sc);
-            return hipGetLastError();
-        }
-        // Under four work-groups (one wave per SIMD each) per CU the tiles wait on their
-        // loads: 13,824 points x 256 x 343, 864 work-groups, 243 us against 187 us with K
-        // split; 301 points, 20 work-groups, 47 against 12 us.  (Also rows too long for
-        // the tiles' 32-bit offsets.)
-        if ((int64_t)grid.x * grid.y * nb < 1024 || lda > ((int64_t)1 << 24)) {
+        } else if (few || long_rows) {
             grid = dim3((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16), (unsigned)nb);
             hipLaunchKernelGGL(zgemm_ksplit_kernel<BT>, grid, dim3(64 * kKSplit), 0, s, A, lda, B,
                                ldb, C, ldc, M, N, K, sb, sc);
@@ -253,7 +267,8 @@ static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* 
     if (M <= 64) return go(zgemm_kernel<4, 2, 2, BT>, 4, 2);
     // Tall and wide: two by two tiles (4 products of 1,024 q' x 3,375 x 125: 284 us, 315
     // with four row tiles; 64,000 q x 3,840 x 343: 11.6 and 12.5 ms).
-    if (N >= 1024) return go(zgemm_kernel<2, 2, 3, BT>, 2, 2);
+    // (Twice the grid rows: above 2.1 million rows more than a launch has.)
+    if (N >= 1024 && M <= 32 * 65535) return go(zgemm_kernel<2, 2, 3, BT>, 2, 2);
     return go(zgemm_kernel<4, 1, 2, BT>, 4, 1);
 }
 

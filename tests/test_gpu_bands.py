@@ -190,3 +190,54 @@ def test_frequencies_alone(lib, nat):
     lib.phonon_modes(ds, torch.from_numpy(q).cuda(), only)
     assert float(om.max()) > 0
     assert torch.equal(om, only)
+
+
+@pytest.mark.parametrize("nW,n_rh,npts", [
+    (3, 1, 1), (5, 2, 16), (9, 3, 17), (16, 7, 33), (7, 32, 70),  # one tile a wave, K of 1 to 32
+    (5, 33, 15), (9, 35, 40), (16, 66, 65), (4, 125, 1000),         # K split over waves
+    (16, 1, 16390), (16, 5, 16390), (13, 34, 22000),                # four row tiles
+    (32, 1, 2050), (32, 6, 2050), (32, 35, 2080),                   # two by two tiles
+])
+def test_fourier_sum_tiles(lib, nW, n_rh, npts):
+    """Every form of the sum over lattice vectors with each remainder of its K steps, and row
+    counts that leave a ragged last tile: eigenvalues of H(k)."""
+    torch = torch_cuda()
+    import dataclasses
+    from paper_2111_14999_amd import DeviceSystem
+    rng = np.random.default_rng(100 * nW + n_rh)
+    s = synth.small_system(70, n_wannier=nW, n_atoms=1, r=1)
+    half = synth.box_vectors(3)[172:][:n_rh // 2]  # one of every pair R, -R
+    h = 0.2 * (rng.standard_normal((len(half), nW, nW)) + 1j * rng.standard_normal((len(half), nW, nW)))
+    R, H = [half, -half], [h, np.conj(np.swapaxes(h, 1, 2))]
+    if n_rh % 2:
+        R.append(np.zeros((1, 3)))
+        H.append((h[:1] + np.conj(np.swapaxes(h[:1], 1, 2))) if len(half) else np.diag(np.arange(nW))[None])
+    s = dataclasses.replace(s, rh=np.concatenate(R).astype(np.int32),
+                            h_r=np.concatenate(H).astype(np.complex128))
+    assert len(s.rh) == n_rh
+    k = rng.uniform(-1, 1, size=(npts, 3))
+    eps = torch.full((npts, nW), float("nan"), dtype=torch.float64, device="cuda")
+    lib.electron_bands(DeviceSystem.from_host(s, with_coupling=False), torch.from_numpy(k).cuda(), eps)
+    ref = np.linalg.eigvalsh(bands.hamiltonian_k(k, s.rh, s.h_r))
+    # the oracle's phases of k.R (|k.R| < 9) carry up to 1e-14 each
+    assert np.max(np.abs(eps.cpu().numpy() - ref)) < 1e-12 * max(1.0, np.max(np.abs(ref)))
+
+
+def test_fourier_sum_many_rows(lib):
+    """32 bands at more points than two by two tiles have grid rows for."""
+    torch = torch_cuda()
+    import dataclasses
+    from paper_2111_14999_amd import DeviceSystem, Library
+    n = 32 * 65535 + 17
+    s = synth.small_system(70, n_wannier=32, n_atoms=1, r=1)
+    s = dataclasses.replace(s, rh=np.zeros((1, 3), dtype=np.int32), h_r=np.ascontiguousarray(s.h_r[13:14]))
+    eps = torch.full((n, 32), float("nan"), dtype=torch.float64, device="cuda")
+    k = torch.zeros((n, 3), dtype=torch.float64, device="cuda")
+    own = Library(0)
+    try:
+        own.electron_bands(DeviceSystem.from_host(s, with_coupling=False), k, eps)
+    finally:
+        own.close()
+    assert torch.equal(eps, eps[:1].expand(n, 32).contiguous())
+    ref = np.linalg.eigvalsh(s.h_r[0])
+    assert np.max(np.abs(eps[0].cpu().numpy() - ref)) < 1e-13 * np.max(np.abs(ref))
