@@ -734,11 +734,17 @@ __device__ inline void rr_pair(int k, int round, int np, int& p, int& q) {
 }
 
 // Without VEC the rotations of V and its store are left out: the eigenvalues are the same bits.
+// Four waves share a matrix (orders 18 to 30): every element's operations are those of one
+// wave, and the sums behind the stopping test are taken by one wave in its order.  A round
+// waits on its passes over the rows and columns, 8 and 15 trips of one wave at order 30:
+// modes of 300 q, 30 of them, 1331 us with one wave, 609 with four; 3,000 q 4038 and 2206 us.
+constexpr int kOrdThreads = 256;
 template <int NT, bool VEC>
-__global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, int n_arg,
-                                                      double* __restrict__ w_out,
-                                                      cd* __restrict__ V_out) {
-    const int n = NT > 0 ? NT : n_arg;
+__global__ __launch_bounds__(kOrdThreads) void eig_ordered_kernel(cd* __restrict__ Aall,
+                                                                  double* __restrict__ w_out,
+                                                                  cd* __restrict__ V_out) {
+    constexpr int n = NT, NTH = kOrdThreads;
+    __shared__ double norms[2];
     extern __shared__ char smem_raw[];
     cd* A = reinterpret_cast<cd*>(smem_raw);
     // odd row stride: 16 lanes walking down a column of 16-byte elements hit 16
@@ -751,9 +757,9 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
     int* rp = reinterpret_cast<int*>(re + (n / 2 + 1));    // p
     int* rq = rp + (n / 2 + 1);                            // q
     const int64_t b = blockIdx.x;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x;  // (of the work-group)
     cd* Ag = Aall + b * (int64_t)n * n;
-    for (int i = lane; i < n * n; i += 64) {
+    for (int i = lane; i < n * n; i += NTH) {
         const int r = i / n, c = i % n;
         A[r * ld + c] = Ag[i];
         if constexpr (VEC) V[r * ld + c] = cd{r == c ? 1.0 : 0.0, 0.0};
@@ -764,17 +770,25 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
     const double eps2 = 4.9e-32;  // (2.2e-16)^2
     for (int sweep = 0; sweep < 40 && n > 1; ++sweep) {
         int rotated = 0;
-        double off = 0.0, dia = 0.0;
-        for (int i = lane; i < n * n; i += 64) {
-            const int r = i / n, c = i % n;
-            const double v = cabs2(A[r * ld + c]);
-            if (r == c)
-                dia += v;
-            else
-                off += v;
+        if (lane < 64) {
+            double off = 0.0, dia = 0.0;
+            for (int i = lane; i < n * n; i += 64) {
+                const int r = i / n, c = i % n;
+                const double v = cabs2(A[r * ld + c]);
+                if (r == c)
+                    dia += v;
+                else
+                    off += v;
+            }
+            off = wave_sum(off);
+            dia = wave_sum(dia);
+            if (lane == 0) {
+                norms[0] = off;
+                norms[1] = dia;
+            }
         }
-        off = wave_sum(off);
-        dia = wave_sum(dia);
+        __syncthreads();
+        const double off = norms[0], dia = norms[1];
         if (!(off > 1e-32 * dia)) break;
         // A pair is left alone once |A_pq|^2 is at the rounding level of its own diagonal
         // entries or of the mean squared diagonal entry, whichever is larger: with the
@@ -811,7 +825,7 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
             }
             __syncthreads();
             // rows: A'_pj = c A_pj - s e A_qj ; A'_qj = s conj(e) A_pj + c A_qj
-            for (int it = lane; it < half * n; it += 64) {
+            for (int it = lane; it < half * n; it += NTH) {
                 const int k = it / n, j = it % n;
                 const int q = rq[k];
                 if (q < 0 || rs[k] == 0.0) continue;
@@ -826,7 +840,7 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
             }
             __syncthreads();
             // columns: A'_ip = c A_ip - s conj(e) A_iq ; A'_iq = s e A_ip + c A_iq ; same for V
-            for (int it = lane; it < (VEC ? 2 : 1) * half * n; it += 64) {
+            for (int it = lane; it < (VEC ? 2 : 1) * half * n; it += NTH) {
                 const int which = it / (half * n);
                 const int r = it % (half * n);
                 const int k = r / n, i = r % n;
@@ -855,10 +869,10 @@ __global__ __launch_bounds__(64) void eig_ordered_kernel(cd* __restrict__ Aall, 
             }
             __syncthreads();
         }
-        if (!__any(rotated)) break;  // a sweep with no rotation leaves A unchanged
+        if (!__syncthreads_or(rotated)) break;  // a sweep with no rotation leaves A unchanged
     }
     // ascending order, ties by index
-    for (int i = lane; i < n; i += 64) {
+    for (int i = lane; i < n; i += NTH) {
         const double wi = A[i * ld + i].x;
         int rank = 0;
         for (int j = 0; j < n; ++j) {
@@ -1032,8 +1046,8 @@ static hipError_t go_eig_ordered(cd* A, int n, int64_t batch, double* w, cd* V, 
         switch (n) {
 #define PHX_EIG(NV)                                                                                 \
     case NV:                                                                                        \
-        hipLaunchKernelGGL((eig_ordered_kernel<NV, VEC>), dim3((unsigned)nb), dim3(64), shm, s, Ab, \
-                           n, wb, Vb);                                                              \
+        hipLaunchKernelGGL((eig_ordered_kernel<NV, VEC>), dim3((unsigned)nb), dim3(kOrdThreads),    \
+                           shm, s, Ab, wb, Vb);                                                     \
         break;
 #define PHX_EIGB(NV)                                                                                \
     case NV:                                                                                        \
