@@ -417,8 +417,8 @@ struct EigShape {
     static constexpr int NW = (L + 63) / 64;                       // waves of a work-group
     // Where pivots are equal by the crystal's structure (CsCl: order 6), the direction of
     // a rotation, and with it the phases of the eigenvectors, hangs on the last bit.
-    // Orders up to 8, which have the cycles to spare, therefore rotate each pair in
-    // index order, operation for operation as before.
+    // Orders up to 8 therefore rotate each pair in index order, as eig_ordered_blk_kernel does
+    // (the same operations; not always the same bits, the compiler contracts them differently).
     static constexpr bool SORTED = N <= 8;
     static constexpr int LD = H <= 2 ? NP : NP + (8 - H % 8) % 8;  // = H modulo 8
 };
@@ -694,22 +694,6 @@ static hipError_t go_eig(const cd* A, int64_t batch, bool vt, double* w, cd* V, 
     return hipGetLastError();
 }
 
-hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, bool vt,
-                           hipStream_t s) {
-    if (batch <= 0) return hipSuccess;
-    switch (n) {
-#define PHX_EIG(NV) \
-    case NV: return go_eig<NV>(A, batch, vt, w, V, s);
-        PHX_EIG(1) PHX_EIG(2) PHX_EIG(3) PHX_EIG(4) PHX_EIG(5) PHX_EIG(6) PHX_EIG(7) PHX_EIG(8)
-        PHX_EIG(9) PHX_EIG(10) PHX_EIG(11) PHX_EIG(12) PHX_EIG(13) PHX_EIG(14) PHX_EIG(15)
-        PHX_EIG(16) PHX_EIG(17) PHX_EIG(18) PHX_EIG(19) PHX_EIG(20) PHX_EIG(21) PHX_EIG(22)
-        PHX_EIG(23) PHX_EIG(24) PHX_EIG(25) PHX_EIG(26) PHX_EIG(27) PHX_EIG(28) PHX_EIG(29)
-        PHX_EIG(30) PHX_EIG(31) PHX_EIG(32)
-#undef PHX_EIG
-        default: return hipErrorInvalidValue;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // The eigensolver for modes that are handed out at any q: cyclic Jacobi on sorted pairs,
 // one wavefront per matrix.  Near Gamma the acoustic modes' eigenvalues lie within 1e-8 of
@@ -896,10 +880,10 @@ __global__ __launch_bounds__(kOrdThreads) void eig_ordered_kernel(cd* __restrict
 // round needs one barrier after the parameters and one after the update.
 // The pair order, the skip test and the stopping rule are those above.
 template <int NT, bool VEC>
-__global__ __launch_bounds__(64) void eig_ordered_blk_kernel(cd* __restrict__ Aall, int n_arg,
+__global__ __launch_bounds__(64) void eig_ordered_blk_kernel(const cd* __restrict__ Aall, int vt,
                                                           double* __restrict__ w_out,
                                                           cd* __restrict__ V_out) {
-    const int n = NT > 0 ? NT : n_arg;
+    constexpr int n = NT;
     constexpr int LD = 17;  // odd row stride (see above)
     __shared__ cd A[16 * LD], V[VEC ? 16 * LD : 1];
     __shared__ double prm[8][4];  // c, s, e of every pair of the round
@@ -1028,7 +1012,7 @@ __global__ __launch_bounds__(64) void eig_ordered_blk_kernel(cd* __restrict__ Aa
         w_out[b * n + rank] = wi;
         if constexpr (VEC) {
             cd* Vg = V_out + b * (int64_t)n * n;
-            for (int r = 0; r < n; ++r) Vg[r * n + rank] = V[r * LD + i];
+            for (int r = 0; r < n; ++r) Vg[vt ? rank * n + r : r * n + rank] = V[r * LD + i];
         }
     }
 }
@@ -1052,7 +1036,7 @@ static hipError_t go_eig_ordered(cd* A, int n, int64_t batch, double* w, cd* V, 
 #define PHX_EIGB(NV)                                                                                \
     case NV:                                                                                        \
         hipLaunchKernelGGL((eig_ordered_blk_kernel<NV, VEC>), dim3((unsigned)nb), dim3(64), 0, s,   \
-                           Ab, n, wb, Vb);                                                          \
+                           Ab, 0, wb, Vb);                                                          \
         break;
             PHX_EIGB(3) PHX_EIGB(6) PHX_EIGB(9) PHX_EIGB(12) PHX_EIGB(15)
             PHX_EIG(18) PHX_EIG(21) PHX_EIG(24) PHX_EIG(27) PHX_EIG(30)
@@ -1067,6 +1051,40 @@ static hipError_t go_eig_ordered(cd* A, int n, int64_t batch, double* w, cd* V, 
 hipError_t launch_eig_herm_ordered(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s) {
     if (batch <= 0) return hipSuccess;
     return V ? go_eig_ordered<true>(A, n, batch, w, V, s) : go_eig_ordered<false>(A, n, batch, w, V, s);
+}
+
+hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, bool vt,
+                           hipStream_t s) {
+    if (batch <= 0) return hipSuccess;
+    // Orders 4 to 8 of no more matrices than the chip has SIMDs (1,024; odd orders, where a
+    // pair is idle, a quarter of that): a wave for each, by the block kernel.  There a round's
+    // latency counts, and the pair swaps of EigShape::SORTED lengthen it: 216 matrices of
+    // order 4, 6, 8: 14.8, 26.0, 42.9 us, 18.9, 35.2, 49.6 several to a wave; 1,024: 17.7, 28.5,
+    // 47.5 and 19.2, 35.8, 50.5; 1,280: 20.2, 34.6, 57.4 and 19.2, 36.1, 52.2.
+    if (batch <= (n & 1 ? 256 : 1024)) {
+        const int t = vt ? 1 : 0;
+        switch (n) {
+#define PHX_EIG(NV)                                                                                  \
+    case NV:                                                                                         \
+        hipLaunchKernelGGL((eig_ordered_blk_kernel<NV, true>), dim3((unsigned)batch), dim3(64), 0, s, A, \
+                           t, w, V);                                                                 \
+        return hipGetLastError();
+            PHX_EIG(4) PHX_EIG(5) PHX_EIG(6) PHX_EIG(7) PHX_EIG(8)
+#undef PHX_EIG
+            default: break;
+        }
+    }
+    switch (n) {
+#define PHX_EIG(NV) \
+    case NV: return go_eig<NV>(A, batch, vt, w, V, s);
+        PHX_EIG(1) PHX_EIG(2) PHX_EIG(3) PHX_EIG(4) PHX_EIG(5) PHX_EIG(6) PHX_EIG(7) PHX_EIG(8)
+        PHX_EIG(9) PHX_EIG(10) PHX_EIG(11) PHX_EIG(12) PHX_EIG(13) PHX_EIG(14) PHX_EIG(15)
+        PHX_EIG(16) PHX_EIG(17) PHX_EIG(18) PHX_EIG(19) PHX_EIG(20) PHX_EIG(21) PHX_EIG(22)
+        PHX_EIG(23) PHX_EIG(24) PHX_EIG(25) PHX_EIG(26) PHX_EIG(27) PHX_EIG(28) PHX_EIG(29)
+        PHX_EIG(30) PHX_EIG(31) PHX_EIG(32)
+#undef PHX_EIG
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -241,3 +241,24 @@ def test_fourier_sum_many_rows(lib):
     assert torch.equal(eps, eps[:1].expand(n, 32).contiguous())
     ref = np.linalg.eigvalsh(s.h_r[0])
     assert np.max(np.abs(eps[0].cpu().numpy() - ref)) < 1e-13 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("n,npts", [(4, 1024), (4, 1025), (5, 256), (5, 257), (6, 1), (6, 1024), (7, 256),
+                                    (8, 1024), (8, 1025)])
+def test_eigensolver_small_batches(lib, n, npts):
+    """Orders 4 to 8 on both sides of the batch at which several matrices share a wave."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(70, n_wannier=n, n_atoms=1, r=1)
+    s.h_r[13] -= np.diag(np.diag(s.h_r[13])) - 0.25 * np.eye(n)
+    k = np.random.default_rng(n).uniform(-1, 1, size=(npts, 3))
+    eps = torch.empty((npts, n), dtype=torch.float64, device="cuda")
+    U = torch.empty((npts, n, n), dtype=torch.complex128, device="cuda")
+    lib.electron_bands(DeviceSystem.from_host(s, with_coupling=False), torch.from_numpy(k).cuda(), eps, U)
+    eps, U = eps.cpu().numpy(), U.cpu().numpy()
+    H = bands.hamiltonian_k(k, s.rh, s.h_r)
+    ref = np.linalg.eigvalsh(H)
+    scale = np.max(np.abs(ref))
+    assert np.max(np.abs(eps - ref)) < 1e-13 * scale
+    assert np.max(np.abs(H @ U - U * eps[:, None, :])) < 1e-13 * scale
+    assert np.max(np.abs(np.conj(np.swapaxes(U, 1, 2)) @ U - np.eye(n))) < 1e-13
