@@ -73,6 +73,12 @@ template <class BT>
 struct ZgemmB;
 template <>
 struct ZgemmB<cd> {
+    // STREAM: B goes past the caches, which it would only sweep
+    template <bool STREAM>
+    static __device__ inline cd load(const cd* p) {
+        if constexpr (STREAM) return cd{__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y)};
+        return *p;
+    }
     static __device__ inline void step1(const cd& a, const cd& b, d4& cr, d4& ci) {
         cr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, cr, 0, 0, 0);
         ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, ci, 0, 0, 0);
@@ -84,6 +90,11 @@ struct ZgemmB<cd> {
 };
 template <>
 struct ZgemmB<double> {
+    template <bool STREAM>
+    static __device__ inline double load(const double* p) {
+        if constexpr (STREAM) return __builtin_nontemporal_load(p);
+        return *p;
+    }
     static __device__ inline void step1(const cd& a, const double& b, d4& cr, d4& ci) {
         cr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b, cr, 0, 0, 0);
         ci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b, ci, 0, 0, 0);
@@ -129,7 +140,7 @@ __global__ __launch_bounds__(256, WPS) void zgemm_kernel(const cd* __restrict__ 
         for (int i = 0; i < TM; ++i) av[i] = pa[i][kc];
         const BT* b = B0 + (int64_t)kc * ldb;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bv[j] = b[cb[j]];
+        for (int j = 0; j < TN; ++j) bv[j] = Z::template load<TM == 1 && TN == 4>(b + cb[j]);
     };
     // operands are prefetched two k-steps ahead: one step of MFMA work is
     // shorter than the HBM latency of the streamed B operand
@@ -259,8 +270,9 @@ static hipError_t zgemm(const cd* A, int64_t lda, const BT* B, int64_t ldb, cd* 
     // Short-and-wide products (stage 1, M = a batch of up to 64 k) cover all rows in one
     // work-group, so each B column is read once, with no more row tiles than the rows
     // fill: up to 32 rows the product is bound by the read of B, above by its MFMAs
-    // (4 k x 343 Re x 1.3M columns, 7.2 GB: 4.05 ms with four row tiles, 1.36 ms with
-    // one).  Tall-and-narrow ones (Fourier transforms over many points) use 4 row tiles
+    // (4 k x 343 Re x 1.3M columns, 7.2 GB: 4.05 ms with four row tiles, 1.33 ms with
+    // one, 1.26 with B's loads past the caches; 40 k x 1.2M columns 3.6 -> 3.0 ms with the K
+    // tail apart).  Tall-and-narrow ones (Fourier transforms over many points) use 4 row tiles
     // per wave.
     if (M <= 16) return go(zgemm_kernel<1, 4, 3, BT>, 1, 4);
     if (M <= 32) return go(zgemm_kernel<2, 2, 3, BT>, 2, 2);
