@@ -177,7 +177,7 @@ phoebe_status phoebe_gpu_phonon_modes(void* handle, const phoebe_system* sys,
             int32_t* rd = upload_r(h, ar, sys->rd, sys->n_rd, s);
             // (omega is the same bits with and without z)
             phonon_dev(h, ar, sys, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, 0.0, 0.0, omega_out,
-                       nullptr, nullptr, reinterpret_cast<cd*>(z_out), s, true, true);
+                       nullptr, nullptr, reinterpret_cast<cd*>(z_out), s, true);
         };
         Arena dry(nullptr);
         plan(dry);
@@ -346,14 +346,14 @@ phoebe_status interp_g_impl(Handle* h, const phoebe_system* sys, const double* k
                 }
                 Arena sub3 = ar;
                 phonon_dev(h, sub3, sys, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, omega_min, 0.0,
-                           om, E, nullptr, nullptr, s, true, !q_mesh);
+                           om, E, nullptr, nullptr, s, !q_mesh);
                 ar.used = std::max(std::max(sub.used, sub2.used), sub3.used);
             }
             if (!ar.base) return;
             if (polar) {
                 HIPCHK(h, hipMemcpyAsync(born, sys->polar->born, sizeof(double) * 9 * sys->n_atoms,
                                          hipMemcpyHostToDevice, s));
-                HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, true, nm, polar_dev(sys, born),
+                HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, nm, polar_dev(sys, born),
                                               Lq, s));
             }
             if (fact) {
@@ -932,7 +932,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 // (eigenvectors as rows: the rate kernels read each one contiguously)
                 electron_bands_dev(h, b1, sys, T.rh, nullptr, nullptr, mesh, N, T.eps, T.U, s, true);
                 phonon_dev(h, b2, sys, T.rd, nullptr, nullptr, mesh, N, par->omega_min, par->kT,
-                           T.omega, T.E, T.nb, nullptr, s, false);
+                           T.omega, T.E, T.nb, nullptr, s);
                 if (use_cache) {
                     tc.valid = false;
                     if (tc.bytes < tc_bytes) {
@@ -978,7 +978,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         HIPCHK(h, launch_band_extrema(T.eps, N, nW, T.omega, N, nm, T.bmin, T.bmax, T.wmax, s));
         HIPCHK(h, launch_window(T.eps, N, nW, par->win_lo, par->win_hi, T.mask, T.flag, s));
         if (polar) {
-            HIPCHK(h, launch_polar_factor(nullptr, mesh, N, T.E, false, nm, polar_dev(sys, T.born), T.Lpol, s));
+            HIPCHK(h, launch_polar_factor(nullptr, mesh, N, T.E, nm, polar_dev(sys, T.born), T.Lpol, s));
         }
         // adaptive smearing: velocities on the mesh; the widest width any transition
         // can take bounds the final-band pruning
@@ -1639,11 +1639,11 @@ phoebe_status phoebe_gpu_polar_factor(void* handle, const phoebe_system* sys, co
             double* om = ar.take<double>((size_t)nq * nm);
             cd* E = ar.take<cd>((size_t)nq * nm * nm);
             phonon_dev(h, ar, sys, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, omega_min, 0.0, om, E,
-                       nullptr, nullptr, s, true, true);
+                       nullptr, nullptr, s, true);
             if (!ar.base) return;
             HIPCHK(h, hipMemcpyAsync(born, sys->polar->born, sizeof(double) * 9 * sys->n_atoms,
                                      hipMemcpyHostToDevice, s));
-            HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, true, nm, polar_dev(sys, born),
+            HIPCHK(h, launch_polar_factor(q_frac, Mesh{1, 1, 1}, nq, E, nm, polar_dev(sys, born),
                                           reinterpret_cast<cd*>(l_out), s));
         };
         Arena dry(nullptr);

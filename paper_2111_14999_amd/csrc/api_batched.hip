@@ -347,7 +347,7 @@ phoebe_status phoebe_gpu_batched_plan(void* handle, const phoebe_system* systems
                 electron_bands_dev(h, b1, sys, p.rh, nullptr, nullptr, p.mesh, p.N, p.eps, p.U, s,
                                    true);
                 phonon_dev(h, b2, sys, p.rd, nullptr, nullptr, p.mesh, p.N, par->omega_min, par->kT,
-                           p.omega, p.E, p.nb, nullptr, s, false);
+                           p.omega, p.E, p.nb, nullptr, s);
             }
             HIPCHK(h, launch_fermi(p.eps, p.N * p.nW, par->mu, par->kT, p.focc, s));
             HIPCHK(h, launch_band_extrema(p.eps, p.N, p.nW, p.omega, p.N, p.nm, p.bmin, p.bmax,

@@ -70,12 +70,12 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
                 // (V3 is handed out mode by mode and q'' = -(q + q') may be any point)
                 Arena a1 = ar, a2 = ar, a3 = ar;
                 phonon_dev(h, a1, &ph, rd, q_frac, nullptr, Mesh{1, 1, 1}, nq, omega_min, 0.0, w1, E1,
-                           nullptr, nullptr, s, true, true);
+                           nullptr, nullptr, s, true);
                 phonon_dev(h, a2, &ph, rd, qp_frac, nullptr, Mesh{1, 1, 1}, nqp, omega_min, 0.0, w2,
-                           E2, nullptr, nullptr, s, true, true);
+                           E2, nullptr, nullptr, s, true);
                 if (ar.base) HIPCHK(h, launch_neg_pair_sum(q_frac, nq, qp_frac, nqp, qpp, s));
                 phonon_dev(h, a3, &ph, rd, qpp, nullptr, Mesh{1, 1, 1}, nq * nqp, omega_min, 0.0, w3,
-                           E3, nullptr, nullptr, s, true, true);
+                           E3, nullptr, nullptr, s, true);
                 ar.used = std::max(std::max(a1.used, a2.used), a3.used);
             }
             if (!ar.base) return;

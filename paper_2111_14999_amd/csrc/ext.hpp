@@ -20,8 +20,8 @@ struct PolarDev {
 // L[p, nu] = pref sum_sa D_sa(q_p) E[p, nu, sa], D_{s b}(q) = sum_{G: q+G != 0}
 // w(q+G) sum_a K_a Z*_{s, a b}, w(K) = e^{-K.eps.K/(4 alpha)} / (K.eps.K), K = 2 pi (q+G).
 // Points: fractional coordinates (frac) or every point of mesh m (frac == nullptr).
-hipError_t launch_polar_factor(const double* frac, Mesh m, int64_t np, const cd* E, bool by_mode,
-                               int nm, const PolarDev& pd, cd* L, hipStream_t s);
+hipError_t launch_polar_factor(const double* frac, Mesh m, int64_t np, const cd* E, int nm,
+                               const PolarDev& pd, cd* L, hipStream_t s);
 
 // g[q, nu, n, m] += i L[q, nu] [U_k^dagger U_{k+q}]_{n m} for the q of one k
 // (U_k [nW, nW] and U_{k+q} [nq, nW, nW] with eigenvectors as columns).

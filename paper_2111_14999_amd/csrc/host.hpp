@@ -62,7 +62,7 @@ struct PresetTables {
     double* eps;    // [N, nW]
     cd* U;          // [N, band, orbital] (transposed eigenvectors)
     double* omega;  // [N, nModes]
-    cd* E;          // [N, atom axis, mode]
+    cd* E;          // [N, mode, atom axis]
     double* nb;     // [N, nModes]
 };
 
@@ -372,14 +372,11 @@ inline void electron_bands_dev(Handle* h, Arena& ar, const phoebe_system* sys, c
 // ordered: D(q) summed in the order of the lattice list and solved by the solver whose
 // rounding does not change (launch_eig_herm_ordered), where the modes themselves are handed
 // out and q may be any point: a q then has the same modes, bit for bit, in every call.
-// E comes as [q, mode, atom axis], or with e_by_mode false as [q, atom axis, mode], the
-// eigensolver's own order, for the rate kernels, whose lanes run over the modes: written and
-// read in whole cache lines (64,000 points: 252 -> 113 us to write; the line kernel, which
-// waits on other things, takes the same time with either).
+// E comes as [q, mode, atom axis].
 inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int32_t* rd_d,
                 const double* frac, const int32_t* idx, Mesh m, int64_t np, double omega_min,
                 double kT, double* omega, cd* E, double* nb, cd* z_out, hipStream_t s,
-                bool e_by_mode = true, bool ordered = false) {
+                bool ordered = false) {
     const int nm = 3 * sys->n_atoms, nR = sys->n_rd;
     cd* P = ar.take<cd>((size_t)np * nR);
     double* phic = ar.take<double>((size_t)nR * nm * nm);
@@ -393,8 +390,8 @@ inline void phonon_dev(Handle* h, Arena& ar, const phoebe_system* sys, const int
                                   (int64_t)nm * nm, nR, ordered, s));
     HIPCHK(h, ordered ? launch_eig_herm_ordered(D, nm, np, lam, z_out || E ? z : nullptr, s)
                       : launch_eig_herm(D, nm, np, lam, z, false, s));
-    HIPCHK(h, launch_phonon_post(lam, z, sys->mass, sys->n_atoms, np, omega_min, kT, omega, E,
-                                 e_by_mode, nb, s));
+    HIPCHK(h, launch_phonon_post(lam, z, sys->mass, sys->n_atoms, np, omega_min, kT, omega, E, nb,
+                                 s));
 }
 
 inline void check_polar(Handle* h, const phoebe_system* sys) {

@@ -40,12 +40,12 @@ hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, 
 // NULL: the eigenvalues alone, the same bits).
 hipError_t launch_eig_herm_ordered(cd* A, int n, int64_t batch, double* w, cd* V, hipStream_t s);
 
-// Phonon post-processing: omega = C_OMEGA sqrt(max(lam, 0)); e[q, sa, nu] =
+// Phonon post-processing: omega = C_OMEGA sqrt(max(lam, 0)); e[q, nu, sa] =
 // z[q, sa, nu] l_{s, q nu} (0 when omega < omega_min); nb Bose occupation
 // (0 when inactive or kT <= 0).
 hipError_t launch_phonon_post(const double* lam, const cd* z, const double* mass, int nat,
                               int64_t nq, double omega_min, double kT, double* omega, cd* e,
-                              bool by_mode, double* nb, hipStream_t s);
+                              double* nb, hipStream_t s);
 
 // Fermi occupations of a band table.
 hipError_t launch_fermi(const double* eps, int64_t n, double mu, double kT, double* f,
@@ -96,7 +96,7 @@ struct RateArgs {
     const cd* U;               // [Nk, nW, nW] transposed: U[k, band, orbital]
     const double* omega;       // [Nq, nm]
     const double* nb;          // [Nq, nm]
-    const cd* E;               // [Nq, nm, nm]: E[q, sa, nu] = z[q][sa][nu] l_{sa,nu}
+    const cd* E;               // [Nq, nm, nm]: E[q, nu, sa] = z[q][sa][nu] l_{sa,nu}
     int nW, nm;
     double sigma;
     double* partial;           // [nst, n_qtiles]

@@ -26,7 +26,7 @@ static inline unsigned grid_n(int64_t n, int block) {
 constexpr int kPolarLanes = 16;
 
 __global__ __launch_bounds__(256) void polar_factor_kernel(const double* frac, Mesh m, int64_t np,
-                                                           const cd* __restrict__ E, bool by_mode, int nm,
+                                                           const cd* __restrict__ E, int nm,
                                                            PolarDev pd, double pref, cd* __restrict__ L) {
     const int lane = threadIdx.x % kPolarLanes;
     constexpr int G = 256 / kPolarLanes;
@@ -67,13 +67,12 @@ __global__ __launch_bounds__(256) void polar_factor_kernel(const double* frac, M
             S2 += __shfl_xor(S2, o, 64);
         }
         const cd* Ep = E + p * nm * nm;
-        const int sn = by_mode ? nm : 1, ss = by_mode ? 1 : nm;
         for (int nu = lane; nu < nm; nu += kPolarLanes) {
             cd acc = {0.0, 0.0};
             for (int sa = 0; sa < nm; ++sa) {
                 const double* Z = pd.born + 9 * (sa / 3) + sa % 3;
                 const double D = S0 * Z[0] + S1 * Z[3] + S2 * Z[6];
-                const cd e = Ep[nu * sn + sa * ss];
+                const cd e = Ep[nu * nm + sa];
                 acc.x += D * e.x;
                 acc.y += D * e.y;
             }
@@ -82,14 +81,14 @@ __global__ __launch_bounds__(256) void polar_factor_kernel(const double* frac, M
     }
 }
 
-hipError_t launch_polar_factor(const double* frac, Mesh m, int64_t np, const cd* E, bool by_mode,
-                               int nm, const PolarDev& pd, cd* L, hipStream_t s) {
+hipError_t launch_polar_factor(const double* frac, Mesh m, int64_t np, const cd* E, int nm,
+                               const PolarDev& pd, cd* L, hipStream_t s) {
     if (np <= 0) return hipSuccess;
     if (pd.nat > 10 || nm != 3 * pd.nat) return hipErrorInvalidValue;
     // 4 pi (e^2 / (4 pi eps0)) in eV A^2 for V = 1 A^3 (CODATA 2018: e / (4 pi eps0 A))
     const double e2 = 1.602176634e-19 / (4.0 * kPi * 8.8541878128e-12 * 1.0e-10);
     hipLaunchKernelGGL(polar_factor_kernel, dim3(grid_n(np, 256 / kPolarLanes)), dim3(256), 0, s, frac,
-                       m, np, E, by_mode, nm, pd, 4.0 * kPi * e2, L);
+                       m, np, E, nm, pd, 4.0 * kPi * e2, L);
     return hipGetLastError();
 }
 

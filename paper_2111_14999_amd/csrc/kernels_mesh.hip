@@ -1719,9 +1719,10 @@ line_rates_kernel(RateArgs a) {
         if (fabs(y1) > cut && fabs(y2) > cut) return;
         const int64_t q = (int64_t)q0 * NL + q12;
         const C* Yr = sY + c * nm;
-        const cd* Eq = a.E + q * nm * nm + nu;
+        const cd* Eq = a.E + (q * nm + nu) * nm;
         C z = {0, 0};
-        for (int sa = 0; sa < nm; ++sa) z = cfma(to_c<C>(Eq[sa * nm]), Yr[sa], z);
+#pragma unroll 3  // (three axes an atom: no remainder)
+        for (int sa = 0; sa < nm; ++sa) z = cfma(to_c<C>(Eq[sa]), Yr[sa], z);
         if constexpr (POL) {
             if (a.Lpol) {  // + i L(q, nu) O_nm
                 const cd l = a.Lpol[q * nm + nu];
@@ -1777,10 +1778,10 @@ line_rates_kernel(RateArgs a) {
             any |= on[j];
         }
         if (!any) return;
-        const cd* Eq = a.E + q * nm * nm + nu;
-#pragma unroll 4
+        const cd* Eq = a.E + (q * nm + nu) * nm;
+#pragma unroll 3
         for (int sa = 0; sa < nm; ++sa) {
-            const C ev = to_c<C>(Eq[sa * nm]);
+            const C ev = to_c<C>(Eq[sa]);
 #pragma unroll
             for (int j = 0; j < MB; ++j)
                 if (j < nb) z[j] = cfma(ev, sY[(j * 16 + c) * nm + sa], z[j]);

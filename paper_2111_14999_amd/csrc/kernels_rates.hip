@@ -309,9 +309,9 @@ __global__ __launch_bounds__(256, (TN >= 12 ? 1 : 2)) void stage2_rates_kernel(R
                 if (kq < 0) continue;
                 const int64_t q = sQ[c];
                 const cd* Yr = sY + (c * kMB + mb) * nm;
-                const cd* Eq = a.E + q * nm * nm + nu;
+                const cd* Eq = a.E + (q * nm + nu) * nm;
                 cd z = {0.0, 0.0};
-                for (int sa = 0; sa < nm; ++sa) z = cfma(Eq[sa * nm], Yr[sa], z);
+                for (int sa = 0; sa < nm; ++sa) z = cfma(Eq[sa], Yr[sa], z);
                 const int m = m0 + mb;
                 if (a.Lpol) {  // + i L(q, nu) [U_k^dagger U_{k+q}]_{n m}
                     const cd* Ukq = a.U + ((int64_t)kq * nW + m) * nW;

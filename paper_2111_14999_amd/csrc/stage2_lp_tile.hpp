@@ -385,17 +385,17 @@ __device__ __forceinline__ void stage2_lp_tile(const RateArgsLP& a, int st, int 
                 const cf* Yr = sY + (cc * kMBLP + mb) * nm;
                 float zr = 0.f, zi = 0.f;
                 if (stg) {
-                    const cf* Er = sE + cc * nm * nm + nu;
+                    const cf* Er = sE + (cc * nm + nu) * nm;
                     for (int sa = 0; sa < nm; ++sa) {
-                        const cf e = Er[sa * nm];
+                        const cf e = Er[sa];
                         const cf y = Yr[sa];
                         zr = fmaf(e.x, y.x, fmaf(-e.y, y.y, zr));
                         zi = fmaf(e.x, y.y, fmaf(e.y, y.x, zi));
                     }
                 } else {
-                    const cd* Eq = a.E + q * nm * nm + nu;
+                    const cd* Eq = a.E + (q * nm + nu) * nm;
                     for (int sa = 0; sa < nm; ++sa) {
-                        const cd e = Eq[sa * nm];
+                        const cd e = Eq[sa];
                         const float er = (float)e.x, ei = (float)e.y;
                         const cf y = Yr[sa];
                         zr = fmaf(er, y.x, fmaf(-ei, y.y, zr));
