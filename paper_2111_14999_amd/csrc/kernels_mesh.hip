@@ -1511,15 +1511,20 @@ constexpr int kLineLW = 1, kLinePol = 2, kLineVel = 4;
 // MB: bands a work-group takes together, sharing the list of points and with it the MFMA
 // part of a unit, the E_q loads and, per band and point, the width and its divisions.  The
 // adaptive widths leave about four live bands at a point (24^3 mesh, 16 bands: 52,900 live
-// (q, band) against 13,800 live q a state), where one list per band computes X four times;
-// the plain Gaussian at the band edge leaves one, and there the registers of the further
-// bands only cost occupancy.  Adaptive rates of that mesh, 543 states, ms in this kernel:
-// MB 1 25.1; MB 2, 3, 4, 6 16.9, 16.5, 18.0, 18.1 (three waves per SIMD up to MB 3, two
-// above); four waves of MB 4 18.5.  What is left is the terms' FP64 arithmetic (the two
-// exponentials; 5 ms), the MFMA part (4 ms), Y (2 ms) and the waits between them.
-template <int FEAT, int H>
+// (q, band) against 13,800 live q a state), where one list per band computes X four times.
+// Adaptive rates of that mesh, 543 states, ms in this kernel: MB 1 25.1; MB 2, 3, 4, 6 16.9,
+// 16.5, 18.0, 18.1 (three waves per SIMD up to MB 3, two above); four waves of MB 4 18.5.  What
+// is left is the terms' FP64 arithmetic (the two exponentials; 5 ms), the MFMA part (4 ms),
+// Y (2 ms) and the waits between them.  The plain Gaussian takes one band a list, whatever
+// its width against the bands: at a band edge it leaves one live band at a point, and the
+// registers of the further ones only cost occupancy (linewidths of a polar crystal, 9 bands,
+// 9 modes, 20^3: 470 us with one, 685 with up to three); where every band is live, as in a
+// coarse mesh taken whole, lists of several bands have not been tried.  Nor do three modes
+// (one tile a wave) with another extension gain: 4 bands, 20^3, polar, 2.36 ms with one, 2.67.
+template <int FEAT, int H, int TN>
 constexpr int line_bands_at_once() {
-    return FEAT & kLineVel ? (H == 2 ? 2 : 3) : 1;
+    if (!(FEAT & kLineVel) || (TN == 1 && FEAT != kLineVel)) return 1;
+    return H == 2 ? 2 : 3;
 }
 
 template <int FEAT, int H, bool F64, int NWV = 4, int MB = 1>
@@ -1552,6 +1557,8 @@ line_rates_kernel(RateArgs a) {
     static_assert(H == 1 || (H == 2 && TN % 2 == 0 && kTP == 2),
                   "two tiles per mode: whole modes per wave and per pass");
     constexpr bool LW = FEAT & kLineLW, POL = FEAT & kLinePol, VEL = FEAT & kLineVel;
+    // what the terms of a band and point share (with adaptive widths its width) is formed once
+    constexpr bool SHARED = MB > 1 || VEL;
     using R = decltype(C::x);
     constexpr bool F64 = sizeof(R) == 8;
     using V4 = std::conditional_t<F64, d4, f4>;
@@ -1576,7 +1583,7 @@ line_rates_kernel(RateArgs a) {
     struct BandPoint {
         double x, f, is2, wt, cut;
     };
-    __shared__ BandPoint sB[MB > 1 ? MB * 16 : 1];  // [MB][16], see band_point
+    __shared__ BandPoint sB[SHARED ? MB * 16 : 1];  // [MB][16], see band_point
     __shared__ cd sO[MB * 16];  // POL: overlap [U_k^dagger U_{k+q}]_{n m} at the unit's points
 
     // XCD-aware order: work-groups are dealt to the 8 XCDs round-robin, so
@@ -1701,7 +1708,7 @@ line_rates_kernel(RateArgs a) {
                                             : C{0, 0};
         }
         d.em = d.fm = d.om = d.nbq = 0.0;
-        if (MB == 1 && has_item && pc >= 0) {
+        if (!SHARED && has_item && pc >= 0) {
             const int64_t q = (int64_t)pc * NL + q12;
             const int64_t kq = kq_of(pc);
             d.em = a.eps[kq * nW + m];
@@ -1872,7 +1879,7 @@ line_rates_kernel(RateArgs a) {
             const int pc = has_item && g + ic < cnt ? sList[g + ic] : -1;
             Unit d;
             load_unit(pl, pc, m, nb, mj, d);
-            if constexpr (MB > 1) {
+            if constexpr (SHARED) {
                 for (int i = tid; i < MB * 16; i += BT) {
                     const int j = i >> 4, c = i & 15;
                     int mm = m;
@@ -1980,12 +1987,12 @@ line_rates_kernel(RateArgs a) {
             }
             __syncthreads();
             // Z[c, nu] = sum_sa E_q[sa, nu] Y[c, sa] and the rate terms
-            if (MB == 1 && pc >= 0) item_term(pc, ic, inu, d.em, d.fm, d.om, d.nbq, m);
-            for (int it = MB == 1 ? tid + BT : tid; it < 16 * nm; it += BT) {
+            if (!SHARED && pc >= 0) item_term(pc, ic, inu, d.em, d.fm, d.om, d.nbq, m);
+            for (int it = SHARED ? tid : tid + BT; it < 16 * nm; it += BT) {
                 const int c = it / nm, nu = it - c * nm;
                 if (g + c >= cnt) continue;
                 const int q0 = sList[g + c];
-                if constexpr (MB > 1) {
+                if constexpr (SHARED) {
                     item_terms(q0, c, nu, nb, mj);
                 } else {
                     const int64_t q = (int64_t)q0 * NL + q12;
@@ -2046,7 +2053,7 @@ template <int TN, int KS, class C, int FEAT, int H = 1, int NWV = 4>
 static hipError_t go_line(const RateArgs& a, int nst, hipStream_t s) {
     if (line_rates_lds(a.W, a.mesh.n0, a.nm, sizeof(C) == sizeof(cf), a.lw != nullptr) > 64 * 1024)
         return hipErrorInvalidValue;
-    constexpr int MB = line_bands_at_once<FEAT, H>();
+    constexpr int MB = line_bands_at_once<FEAT, H, TN>();
     // (the further bands' Y: up to 16 KB above that limit, within a CU's 160 KB)
     const size_t shm = line_lds(a.W, a.mesh.n0, a.nm, sizeof(C) == sizeof(cf), a.lw != nullptr, MB);
     hipError_t e = hipFuncSetAttribute((const void*)line_rates_kernel<TN, KS, C, FEAT, H, NWV, MB>,
@@ -2093,6 +2100,7 @@ static hipError_t line_rates(const RateArgs& a, int nst, hipStream_t s) {
                 case kLineLW: return go_line<TN, KS, C, kLineLW>(a, nst, s);
                 case kLinePol: return go_line<TN, KS, C, kLinePol>(a, nst, s);
                 case kLineVel: return go_line<TN, KS, C, kLineVel>(a, nst, s);
+                case kLineLW | kLinePol: return go_line<TN, KS, C, kLineLW | kLinePol>(a, nst, s);
                 default: return go_line<TN, KS, C, kLineLW | kLinePol | kLineVel>(a, nst, s);
             }
         } else {
@@ -2109,6 +2117,7 @@ static hipError_t line_rates(const RateArgs& a, int nst, hipStream_t s) {
                     case kLineLW: return go_line<TN, KS, C, kLineLW, 2>(a, nst, s);
                     case kLinePol: return go_line<TN, KS, C, kLinePol, 2>(a, nst, s);
                     case kLineVel: return go_line<TN, KS, C, kLineVel, 2>(a, nst, s);
+                    case kLineLW | kLinePol: return go_line<TN, KS, C, kLineLW | kLinePol, 2>(a, nst, s);
                     default: return go_line<TN, KS, C, kLineLW | kLinePol | kLineVel, 2>(a, nst, s);
                 }
             } else {

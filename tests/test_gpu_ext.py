@@ -632,3 +632,34 @@ def test_v3_modes_near_gamma(lib, nat):
     # pair by pair: the lengths of the lowest modes grow as q'' falls
     err = np.abs(V.cpu().numpy() - ref).max(axis=(2, 3, 4)) / np.abs(ref).max(axis=(2, 3, 4))
     assert err.max() < V3_BOUND
+
+
+@pytest.mark.parametrize("nW,nat,mesh", [(3, 1, (7, 3, 4)), (4, 1, (20, 2, 3)), (6, 2, (18, 2, 3)), (20, 3, (6, 3, 2))])
+@pytest.mark.parametrize("smearing", ["gaussian", "adaptive"])
+def test_line_extensions_together(lib, nW, nat, mesh, smearing):
+    """Polar terms with linewidths, adaptive widths and both, one atom (one band a list) and
+    several, against the direct sum."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.small_system(97 + nW, n_wannier=nW, n_atoms=nat, r=1)
+    s.h_r *= 0.3
+    s = synth.add_polar(s, 97 + nW, alpha=3.0, g_max=2)
+    t, par = _params(s, mesh, sigma=0.02)
+    if smearing == "adaptive":
+        par = dict(par, smearing="adaptive", adaptive_scale=1.0)
+    ds = DeviceSystem.from_host(s)
+    N = int(np.prod(mesh))
+    out = {}
+    try:
+        for form in ("direct", "factored"):
+            lib.set_mesh_sum(form)
+            gam = torch.zeros((N, nW), dtype=torch.float64, device="cuda")
+            P = torch.zeros((N, s.n_modes), dtype=torch.float64, device="cuda")
+            lib.scatter_rates(ds, mesh, par, gam)
+            lib.phonon_linewidth(ds, mesh, par, P)
+            out[form] = gam.cpu().numpy(), P.cpu().numpy()
+    finally:
+        lib.set_mesh_sum("auto")
+    assert np.max(out["direct"][0]) > 0
+    for a, b in zip(out["factored"], out["direct"]):
+        assert rel_err(a, b)[0] < 1e-10
