@@ -1437,6 +1437,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                     rb.line_bands = lineany;
                     // live bands of every (state, line, chunk) first: T2 is formed for live lines only
                     HIPCHK(h, launch_line_live(rb, nn, livebuf, lineany, nl, s));
+                    if (h->timing && adaptive)
+                        HIPCHK(h, launch_line_units(rb, nn, livebuf, lineany, nl + 1, s));
                     const AxisCols acols{nW <= 16 ? 16 : 32, nW, nm};  // F's columns in use
                     Timer ta(h, s, "axis_transforms");
                     if (lowp)
@@ -1461,8 +1463,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                         HIPCHK(h, launch_line_rates_f32(rb, nn, s));
                     else
                         HIPCHK(h, launch_line_rates(rb, nn, s));
-                    // T2 of every live (state, line) read once; U_{k+q} of band m at the 16
-                    // points of every unit
+                    // T2 of every live (state, line) read once; U_{k+q} of a list's bands at the
+                    // 16 points of every unit
                     tl.done(0.0, nl, (double)g_elem * Wbox * nm * nW, nl + 1, 16.0 * nW * sizeof(cd));
                     if (lwbuf)
                         HIPCHK(h, launch_lw_reduce_lines(lwbuf, lineany, livebuf, nn, (int)NL,

@@ -232,6 +232,10 @@ size_t re_axes_lds(int rmax, bool f32);
 // here (the line kernel skips such pairs).
 hipError_t launch_line_live(const RateArgs& a, int nst, uint32_t* live, uint32_t* line_bands,
                             uint32_t* n_live, hipStream_t s);
+// The same count of units with adaptive widths (a.vel), where launch_line_live leaves
+// n_live[1] alone: per list of several bands, its bands times its units.
+hipError_t launch_line_units(const RateArgs& a, int nst, const uint32_t* live, const uint32_t* line_bands,
+                             uint32_t* n_units, hipStream_t s);
 hipError_t launch_line_rates(const RateArgs& a, int nst, hipStream_t s);
 hipError_t launch_line_rates_f32(const RateArgs& a, int nst, hipStream_t s);
 size_t line_rates_lds(int W, int N0, int nm, bool f32, bool lw = false);

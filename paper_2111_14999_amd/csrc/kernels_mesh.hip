@@ -1375,9 +1375,9 @@ __device__ inline R rows4_reduce_scatter(R u0, R u1, R u2, R u3) {
 // masks of one line are contiguous, so the line kernel reads them as one
 // block.  The thread also leaves
 // the union of its line's bands in line_bands and counts (one atomic per wave)
-// n_live[0] the lines with a live band and n_live[1] the units of 16 points of its bands
-// (per band, its live points / 16 rounded up), and writes
-// the zero partial sum of every pair without a live band.
+// n_live[0] the lines with a live band and, with one band a list, n_live[1] the units of 16
+// points of its bands (per band, its live points / 16 rounded up; adaptive widths:
+// line_units_kernel), and writes the zero partial sum of every pair without a live band.
 __global__ __launch_bounds__(256, 8) void line_live_kernel(RateArgs a, uint32_t* __restrict__ live,
                                  uint32_t* __restrict__ line_bands, uint32_t* __restrict__ n_live) {
     const Mesh mesh = a.mesh;
@@ -1455,7 +1455,7 @@ __global__ __launch_bounds__(256, 8) void line_live_kernel(RateArgs a, uint32_t*
     for (int o = 32; o > 0; o >>= 1) units += __shfl_xor(units, o, 64);
     if ((threadIdx.x & 63) == 0) {
         if (bal) atomicAdd(n_live, (uint32_t)__popcll(bal));
-        if (units) atomicAdd(n_live + 1, units);
+        if (units && !a.vel) atomicAdd(n_live + 1, units);
     }
 }
 
@@ -1525,6 +1525,66 @@ template <int FEAT, int H, int TN>
 constexpr int line_bands_at_once() {
     if (!(FEAT & kLineVel) || (TN == 1 && FEAT != kLineVel)) return 1;
     return H == 2 ? 2 : 3;
+}
+
+// The next group of a line's live bands, taken from `bands` (lowest first): bands are added
+// as long as one list for all of them is cheaper than a list for the next band by itself
+// (the MFMA part of a unit counts 2, each band's contraction and terms 1).  units_of(mask):
+// the units of the points where a band of the mask is live.  Returns the group's mask and
+// its nb bands in mj.
+template <int MB, class F>
+__device__ inline uint32_t next_band_group(uint32_t bands, F&& units_of, int (&mj)[MB], int& nb) {
+    uint32_t gm = bands & (0u - bands);
+    nb = 1;
+#pragma unroll
+    for (int j = 0; j < MB; ++j) mj[j] = __builtin_ctz(bands);
+    if constexpr (MB > 1) {
+        int ug = units_of(gm);
+        bool open = true;
+#pragma unroll
+        for (int j = 1; j < MB; ++j) {
+            const uint32_t rest = bands & ~gm;
+            if (open && rest) {
+                const uint32_t b1 = rest & (0u - rest);
+                const int u1 = units_of(gm | b1);
+                if (u1 * (3 + nb) <= ug * (2 + nb) + 3 * units_of(b1)) {
+                    gm |= b1;
+                    ug = u1;
+                    mj[j] = __builtin_ctz(b1);
+                    ++nb;
+                } else {
+                    open = false;
+                }
+            }
+        }
+    }
+    return gm;
+}
+
+// Adds to *n_units, for every live line, its groups' bands times units: what the line kernel
+// contracts with adaptive widths (the library's byte accounting; not launched without it).
+template <int MB>
+__global__ __launch_bounds__(256) void line_units_kernel(const uint32_t* __restrict__ live,
+                                                         const uint32_t* __restrict__ line_bands,
+                                                         int64_t lines, int N0, uint32_t* n_units) {
+    const int64_t i = blockIdx.x * 256LL + threadIdx.x;
+    uint32_t units = 0;
+    uint32_t bands = i < lines ? line_bands[i] : 0;
+    const uint32_t* lv = live + (bands ? i : 0) * N0;
+    auto units_of = [&](uint32_t mask) {
+        int n = 0;
+        for (int p = 0; p < N0; ++p) n += (lv[p] & mask) != 0;
+        return (n + 15) >> 4;
+    };
+    while (bands) {
+        int mj[MB], nb;
+        const uint32_t gm = next_band_group<MB>(bands, units_of, mj, nb);
+        bands &= ~gm;
+        units += (uint32_t)(nb * units_of(gm));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) units += __shfl_xor(units, o, 64);
+    if ((threadIdx.x & 63) == 0 && units) atomicAdd(n_units, units);
 }
 
 template <int FEAT, int H, bool F64, int NWV = 4, int MB = 1>
@@ -1828,36 +1888,9 @@ line_rates_kernel(RateArgs a) {
         return (n + 15) >> 4;
     };
     while (bands) {
-        const int m = __builtin_ctz(bands);
-        // the group: bands from m on, as long as one list for all of them is cheaper than a
-        // list for the next band by itself (the MFMA part of a unit counts 2, each band's
-        // contraction and terms 1)
-        uint32_t gm = bands & (0u - bands);
-        int nb = 1;
-        int mj[MB];
-        mj[0] = m;
-#pragma unroll
-        for (int j = 1; j < MB; ++j) mj[j] = m;
-        if constexpr (MB > 1) {
-            int ug = units_of(gm);
-            bool open = true;
-#pragma unroll
-            for (int j = 1; j < MB; ++j) {
-                const uint32_t rest = bands & ~gm;
-                if (open && rest) {
-                    const uint32_t b1 = rest & (0u - rest);
-                    const int u1 = units_of(gm | b1);
-                    if (u1 * (3 + nb) <= ug * (2 + nb) + 3 * units_of(b1)) {
-                        gm |= b1;
-                        ug = u1;
-                        mj[j] = __builtin_ctz(b1);
-                        ++nb;
-                    } else {
-                        open = false;
-                    }
-                }
-            }
-        }
+        int mj[MB], nb;
+        const uint32_t gm = next_band_group<MB>(bands, units_of, mj, nb);
+        const int m = mj[0];
         bands &= ~gm;
         // live points of the group, ascending
         if (wave == 0) {
@@ -2031,6 +2064,23 @@ static size_t line_lds(int W, int N0, int nm, bool f32, bool lw, int mb) {
     return ((size_t)(N0 + 1) * (Wp + 1) + 16 * (size_t)nm * mb) * (f32 ? sizeof(cf) : sizeof(cd)) +
            2 * (size_t)N0 * sizeof(uint32_t) +
            (lw ? sizeof(uint32_t) * (size_t)(N0 & 1) + (size_t)N0 * nm * sizeof(double) : 0);
+}
+
+hipError_t launch_line_units(const RateArgs& a, int nst, const uint32_t* live, const uint32_t* line_bands,
+                             uint32_t* n_units, hipStream_t s) {
+    if (nst <= 0) return hipSuccess;
+    if (!a.vel || !live || !line_bands || !n_units) return hipErrorInvalidValue;
+    const int64_t lines = (int64_t)nst * a.mesh.n1 * a.mesh.n2;
+    const dim3 grid((unsigned)((lines + 255) / 256));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, live, line_bands, lines, a.mesh.n0, n_units);
+        return hipGetLastError();
+    };
+    // the form that launch_line_rates takes for these arguments
+    constexpr int kAll = kLineLW | kLinePol | kLineVel;
+    if (a.nW > 16) return go(line_units_kernel<line_bands_at_once<kLineVel, 2, 2>()>);
+    if (a.nc_pad == 64 && (a.lw || a.Lpol)) return go(line_units_kernel<line_bands_at_once<kAll, 1, 1>()>);
+    return go(line_units_kernel<line_bands_at_once<kLineVel, 1, 2>()>);
 }
 
 size_t line_rates_lds(int W, int N0, int nm, bool f32, bool lw) {

@@ -663,3 +663,54 @@ def test_line_extensions_together(lib, nW, nat, mesh, smearing):
     assert np.max(out["direct"][0]) > 0
     for a, b in zip(out["factored"], out["direct"]):
         assert rel_err(a, b)[0] < 1e-10
+
+
+@pytest.mark.parametrize("nW,nat,mesh", [(6, 2, (37, 3, 2)), (16, 4, (40, 2, 1)), (20, 3, (33, 2, 2))])
+def test_adaptive_line_bytes(lib, nW, nat, mesh):
+    """The bytes recorded for the line kernel with adaptive widths: T2 of every live line and the
+    eigenvector rows of each list's bands at its units of 16 points, lists formed by the
+    kernel's rule from the oracle's tables."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem, Library
+    s = synth.small_system(140 + nW, n_wannier=nW, n_atoms=nat, r=1)
+    s.h_r *= 0.3
+    t, par = _params(s, mesh, sigma=0.002)
+    par = dict(par, smearing="adaptive", adaptive_scale=0.4, win_lo=-1e30, win_hi=1e30)
+    n0, n1, n2 = mesh
+    N, NL = n0 * n1 * n2, n1 * n2
+    idx = np.arange(N)
+    pts = np.stack([idx // NL / n0, idx // n2 % n1 / n1, idx % n2 / n2], axis=1)
+    v = velocity.group_velocities(pts, s.rh, s.h_r)[1]
+    wmax = np.max(t["omega"])
+    k_idx, most = np.array([0, 17, N - 1]), 2 if nW > 16 else 3
+    lines = units = 0
+    for k in k_idx:
+        kk = np.array([k // NL, k // n2 % n1, k % n2])
+        for n in range(nW):
+            for q1 in range(n1):
+                for q2 in range(n2):
+                    kq = ((kk[0] + np.arange(n0)) % n0) * NL + (kk[1] + q1) % n1 * n2 + (kk[2] + q2) % n2
+                    sg = velocity.adaptive_sigma(v[k, n], v[kq], mesh, 0.002, 0.4)  # [n0, nW]
+                    live = np.abs(t["eps"][k, n] - t["eps"][kq]) <= 27.5 * sg + wmax
+                    left = list(np.flatnonzero(live.any(axis=0)))
+                    lines += len(left) > 0
+                    of = lambda g: -(-int(live[:, g].any(axis=1).sum()) // 16)
+                    while left:
+                        g = [left.pop(0)]
+                        while left and len(g) < most:
+                            joined = of(g + [left[0]])
+                            if joined * (3 + len(g)) > of(g) * (2 + len(g)) + 3 * of([left[0]]):
+                                break
+                            g.append(left.pop(0))
+                        units += len(g) * of(g)
+    own = Library(0)
+    try:
+        own.set_mesh_sum("factored")
+        own.set_timing(True)
+        gam = torch.zeros((3, nW), dtype=torch.float64, device="cuda")
+        own.scatter_rates(DeviceSystem.from_host(s), mesh, par, gam,
+                          k_idx=torch.from_numpy(k_idx.astype(np.int32)).cuda())
+        got = own.kernel_bytes("line_rates")
+    finally:
+        own.close()
+    assert got == 16.0 * 3 * s.n_modes * nW * lines + 16.0 * nW * 16 * units
