@@ -501,15 +501,13 @@ phoebe_status phoebe_gpu_interp_g_mesh(void* handle, const phoebe_system* sys,
 }  // extern "C"
 
 // Lists of one batch for launch_re_reg, appended to rbh with their offsets in rbo:
-// (chunks, -, offsets of pair_k1, ent, chunks).  kmesh: the rows' mesh indices;
-// row_end[i]: states before row i; prs: the distinct (k0, k1) = k0 n1 + k1, ascending.  A
-// chunk holds pairs of one k0 and at most the kernel's numbers of pairs and k; a pair
-// with more k continues in the next chunk.
-static void append_reg_batch(const int32_t* kmesh, int rows, const int32_t* row_end,
-                             const std::vector<int32_t>& prs, const Mesh& mesh, int rmax_e,
+// (chunks, entries, offsets of pair_k1, ent, chunks).  kmesh: the rows' mesh indices;
+// row_end[i]: states before row i; prs: the distinct (k0, k1) = k0 n1 + k1, ascending.  An
+// entry is a state with the fold, otherwise a row.  A chunk holds pairs of one k0 and as
+// many entries as the kernel has room for; a pair with more continues in the next chunk.
+static void append_reg_batch(const int32_t* kmesh, int rows, const int32_t* row_end, bool fold,
+                             const std::vector<int32_t>& prs, const Mesh& mesh, const ReRegLimits& lim,
                              std::vector<int32_t>& rbh, std::vector<std::array<int64_t, 11>>& rbo) {
-    int max_pairs = 0, max_ks = 0;
-    re_reg_limits(rmax_e, &max_pairs, &max_ks);
     const int np = (int)prs.size();
     std::vector<int32_t> row_pair(rows), off(np + 1, 0), order(rows);
     for (int i = 0, last = -1; i < rows; ++i) {
@@ -526,30 +524,37 @@ static void append_reg_batch(const int32_t* kmesh, int rows, const int32_t* row_
     }
     std::vector<int32_t> chunks, ent;
     int32_t* cur = nullptr;  // chunk being filled: k0, first pair, pairs, first entry, entries
-    for (int p = 0; p < np; ++p)
-        for (int i = off[p]; i < off[p + 1];) {
-            const int32_t k0 = prs[p] / mesh.n1;
-            if (!cur || cur[0] != k0 || cur[4] == max_ks || (p - cur[1] == max_pairs)) {
-                const int32_t c[8] = {k0, p, 0, i, 0, 0, 0, 0};
-                chunks.insert(chunks.end(), c, c + 8);
-                cur = chunks.data() + chunks.size() - 8;
-            }
-            cur[2] = p - cur[1] + 1;
-            for (; i < off[p + 1] && cur[4] < max_ks; ++i, ++cur[4]) {
-                const int32_t row = order[i];
-                ent.insert(ent.end(), {row_end[row] - row_end[0], row_end[row + 1] - row_end[0],
-                                       (p - cur[1]) | (kmesh[row] % mesh.n2) << 8, row});
+    for (int p = 0; p < np; ++p) {
+        const int32_t k0 = prs[p] / mesh.n1;
+        for (int i = off[p]; i < off[p + 1]; ++i) {
+            const int32_t row = order[i], k2 = kmesh[row] % mesh.n2;
+            const int32_t first = fold ? row_end[row] - row_end[0] : row;
+            const int32_t end = fold ? row_end[row + 1] - row_end[0] : row + 1;
+            for (int32_t e = first; e < end; ++e) {
+                const int n = cur ? p - cur[1] + 1 : 0;  // pairs with this one
+                if (!cur || cur[0] != k0 || cur[4] == lim.ents || n > lim.pairs ||
+                    (n + lim.group - 1) / lim.group * lim.group * lim.slot + (cur[4] + 4) * lim.row > lim.pool) {
+                    const int32_t c[8] = {k0, p, 0, (int32_t)(ent.size() / 2), 0, 0, 0, 0};
+                    chunks.insert(chunks.end(), c, c + 8);
+                    cur = chunks.data() + chunks.size() - 8;
+                }
+                cur[2] = p - cur[1] + 1;
+                ++cur[4];
+                ent.insert(ent.end(), {e, (p - cur[1]) | k2 << 8});
             }
         }
-    ent.insert(ent.end(), 12, 0);  // read ahead of, never used
+    }
     std::array<int64_t, 11> o{};
     o[0] = (int64_t)chunks.size() / 8;
+    o[1] = (int64_t)ent.size() / 2;
+    ent.insert(ent.end(), 6, 0);  // read ahead of, never used
     o[2] = (int64_t)rbh.size();
     for (int32_t pr : prs) rbh.push_back(pr % mesh.n1);
     rbh.insert(rbh.end(), 8, 0);  // (read ahead of, as the entries)
     while (rbh.size() % 4) rbh.push_back(0);
     o[3] = (int64_t)rbh.size();
     rbh.insert(rbh.end(), ent.begin(), ent.end());
+    while (rbh.size() % 4) rbh.push_back(0);
     o[4] = (int64_t)rbh.size();
     rbh.insert(rbh.end(), chunks.begin(), chunks.end());
     rbo.push_back(o);
@@ -831,6 +836,15 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         // once per call and the batches are no longer limited by their k0 count).
         const size_t plane_bytes = (size_t)We * We * NC2 * g_elem;
         const int64_t planes_cap = std::min<int64_t>(mesh.n0, rows_cap);
+        // grouping lists of stage 1 (int32), the one-pass form's: at most two an entry, a pair
+        // and a chunk's eight a row, what a batch (16 rows or the call) adds, and slack
+        const size_t lists_cap =
+            re_reg ? (size_t)rows_cap * (fold_fused ? 2 * nW + 14 : 16) + 64 : (size_t)rows_cap * 176;
+        const size_t t2_bytes = factored ? (size_t)nsb * Wbox * NL * nc_pad * g_elem : 0;
+        // U_k rows of a batch's states, where T2 is later (the one-pass form with the fold)
+        const size_t ue_bytes = re_reg && fold_fused
+                                    ? ((size_t)std::min<int64_t>(max_states, rows_cap * nW) + 4) * 16 * sizeof(cd)
+                                    : 0;
         const size_t batch_bytes = 4 * 256 + (size_t)BK * n_re * sizeof(cd) +
                                    (fold_fused ? 0 : (size_t)BK * NC2 * g_elem) +
                                    (size_t)max_states * rp_pad * nc_pad * f_elem +
@@ -841,10 +855,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                                                    2 * (size_t)(rows_cap * nW + rows_cap + 1) *
                                                        sizeof(uint32_t) + 512
                                              : 0) +
-                                   (re_fact ? (size_t)rows_cap * (re_reg ? 40 : 176) * sizeof(int32_t) +
-                                                  1024
-                                            : 0) +
-                                   (re_reg && fold_fused ? (size_t)(rows_cap + 4) * 256 + 512 : 0) +
+                                   (re_fact ? lists_cap * sizeof(int32_t) + 1024 : 0) +
+                                   (ue_bytes > t2_bytes ? ue_bytes - t2_bytes : 0) +
                                    (lw_out ? (factored ? (size_t)nsb * NL * n0_line
                                                        : (size_t)max_states * N) *
                                                      nm * sizeof(double) + 256
@@ -1147,8 +1159,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 std::sort(k0s.begin(), k0s.end());
                 std::sort(prs.begin(), prs.end());
                 if (re_reg) {
-                    append_reg_batch(kh.data() + r, (int)(e - r), row_end.data() + r, prs, mesh,
-                                     rmax_e, rbh, rbo);
+                    append_reg_batch(kh.data() + r, (int)(e - r), row_end.data() + r, fold_fused, prs,
+                                     mesh, re_reg_limits(rmax_e, lowp, fold_fused), rbh, rbo);
                     batches.push_back({r, e - r});
                     r = e;
                     continue;
@@ -1223,16 +1235,13 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
                 rbo.push_back({(int64_t)planes.size(), 0, (int64_t)rbh.size(), 0, 0, 0, 0, 0, 0, 0, 0});
                 rbh.insert(rbh.end(), planes.begin(), planes.end());
             }
-            REQUIRE(h, rbh.size() <= (size_t)rows_cap * (re_reg ? 40 : 176),
-                    "stage-1 grouping lists too long");
+            REQUIRE(h, rbh.size() <= lists_cap, "stage-1 grouping lists too long");
         }
         int32_t* rbd = re_fact ? ar.take<int32_t>(std::max<size_t>(rbh.size(), 1)) : nullptr;
         if (re_fact)
             HIPCHK(h, hipMemcpyAsync(rbd, rbh.data(), sizeof(int32_t) * rbh.size(),
                                      hipMemcpyHostToDevice, s));
         char* T0re = t0_bytes ? ar.take<char>(t0_bytes) : nullptr;
-        // U_k rows of a batch's k
-        cd* ue = re_reg && fold_fused ? ar.take<cd>((size_t)(rows + 4) * 16) : nullptr;
         cd* P1 = ar.take<cd>((size_t)BK * n_re);
         char* Gbuf = fold_fused ? nullptr : ar.take<char>((size_t)BK * NC2 * g_elem);
         char* Fbuf = ar.take<char>((size_t)max_states * rp_pad * nc_pad * f_elem);
@@ -1240,7 +1249,8 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
         char* T1buf = factored && !axes_fused
                           ? ar.take<char>((size_t)nsb * Wbox * Wbox * mesh.n2 * nc_pad * g_elem)
                           : nullptr;
-        char* T2buf = factored ? ar.take<char>((size_t)nsb * Wbox * NL * nc_pad * g_elem) : nullptr;
+        char* T2buf = factored ? ar.take<char>(std::max(t2_bytes, ue_bytes)) : nullptr;
+        cd* ue = ue_bytes ? reinterpret_cast<cd*>(T2buf) : nullptr;
         uint32_t* livebuf = factored ? ar.take<uint32_t>((size_t)nsb * NL * n0_line) : nullptr;
         uint32_t* lineany = factored ? ar.take<uint32_t>((size_t)nsb * NL) : nullptr;
         double* lwbuf = lw_out ? ar.take<double>((factored ? (size_t)nsb * NL * n0_line
@@ -1290,7 +1300,7 @@ static phoebe_status scatter_rates_impl(void* handle, const phoebe_system* sys,
             if (ns == 0) continue;
             if (re_fact) {
                 const auto& o = rbo[bi];
-                ReRegBatch rr{(int)o[0], (int)nb, rbd + o[2], rbd + o[3], rbd + o[4], ue};
+                ReRegBatch rr{(int)o[0], (int)o[1], rbd + o[2], rbd + o[3], rbd + o[4], ue};
                 ReBatch rb{(int)o[0], (int)o[1], rbd + o[2], rbd + o[3], rbd + o[4],
                            rbd + o[5], rbd + o[6], rbd + o[7], all_planes ? rbd + o[8] : nullptr,
                            rbd + o[10]};

@@ -184,17 +184,23 @@ struct FoldOut {
 };
 // The whole sum in one pass, no T0 (boxes up to 7 wide); P is the phase table in the
 // working type (launch_axis_phases, _f32).  Device lists: pair_k1 [pairs + 8] of the distinct
-// (k0, k1); ent [nent + 3][4] (16-byte aligned), the k grouped by pair: first state, end of
-// its states, pair within its chunk + 256 k2, batch row; chunks [nchunk][8] k0, first pair,
-// pairs, first entry, entries, -, -, - (limits: re_reg_limits).  The entries past the
-// ends are read ahead of and hold zeros.  ue: scratch [nent + 4, 16] with a fold.
+// (k0, k1); ent [nent + 3][2] (8-byte aligned), the batch's rows, with the fold its states,
+// grouped by pair: row or state, pair within its chunk + 256 k2; chunks [nchunk][8]
+// (16-byte aligned) k0, first pair, pairs, first entry, entries, -, -, - (limits:
+// re_reg_limits).  The entries past the ends are read ahead of and hold zeros.  ue: scratch
+// [nent + 4, 16] with a fold.
 struct ReRegBatch {
     int nchunk, nent;
     const int32_t *pair_k1, *ent, *chunks;
     cd* ue;
 };
 bool re_reg_supported(int rmax, int64_t NC, bool f32, bool fold);
-void re_reg_limits(int rmax, int* pairs, int* ks);
+// What a chunk may hold: at most `pairs` pairs and `ents` entries, and its pairs rounded up to
+// whole groups times `slot` plus (entries + 3) times `row` within `pool` bytes.
+struct ReRegLimits {
+    int pairs, group, slot, row, pool, ents;
+};
+ReRegLimits re_reg_limits(int rmax, bool f32, bool fold);
 hipError_t launch_re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rmax, Mesh m,
                          const cd* P, const ReRegBatch& b, const FoldOut* fo, cd* G, int64_t ldg,
                          hipStream_t s);

@@ -15,6 +15,7 @@
 // smeared rate terms as the direct kernel; X never reaches memory.  The sum
 // is the same as the direct one up to the order of the additions.
 #include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -811,10 +812,10 @@ __global__ __launch_bounds__(64 * kFoldWaves, fold_waves_per_simd<WT>()) void re
 // and F (or G) reaches memory.  A work-group takes 64 columns; wave w (w < WT) holds
 // g[R0, R1, R2 = w] of its columns in registers (49 complex values at WT = 7) and goes
 // through the chunks of the call, each some pairs (k0, k1) of one plane k0 and some of
-// their k:
+// their k, with the fold of their states:
 //   T0[R1] = sum_R0 P0[k0, R0] g[R0, R1, w]      registers
 //   T1[p]  = sum_R1 P1[k1_p, R1] T0[R1]          registers -> LDS [pair][R2 = w][column]
-// and after a barrier the waves share the chunk's k in equal contiguous ranges:
+// and after a barrier the waves share the chunk's k or states in equal contiguous ranges:
 //   G[k]   = sum_R2 P2[k2, R2] T1[p(k), R2]      then the U_k fold (FOLD) or G itself.
 // g is read once per launch, so a launch covers as many k as F (or G) has rows for.
 //
@@ -824,12 +825,16 @@ __global__ __launch_bounds__(64 * kFoldWaves, fold_waves_per_simd<WT>()) void re
 // out of order, so a wait is for all of them) from the small per-axis tables, which
 // stay in the scalar cache (rows copied out in the order of use did not, and were
 // slower), and the chunk's eigenvector rows go from memory to LDS during the pair sums: a
-// vector load inside the k loop would wait for every F store before it.
+// vector load inside the loop would wait for every F store before it.  So an entry of the
+// loop is a state, not a k with its later states' rows read in it; 256 k of a 20^3 mesh with
+// all 16 states, 15 modes: 28.1 -> 15.2 ms (FP32 29.1 -> 10.8; T0 in HBM 18.1 and 14.7) at
+// 343 x 343 vectors, 13.4 -> 3.6 (T0 in HBM 4.4) at 125 x 125.  Where such a k set lies in
+// very few planes T0 in HBM is ahead (four planes of 30 x 30: 11.5 ms against 12.7).
 //
 // Against T0 in HBM (one plane per distinct k0, at 40 planes 5 times the size of g)
 // this takes out its write and its read, and the pair sums read no LDS.  nW = 16, 15
 // modes, 343 x 343 vectors, 1,964 k of a 40^3 mesh: 9.8 + 17.4 ms (planes, then pairs and
-// k) -> 15.6 ms, of which the k and fold 6.3; 454 k of a 24^3 mesh: 6.1 + 7.2 -> 6.4 ms.
+// k) -> 15.4 ms, of which the k and fold 6.3; 454 k of a 24^3 mesh: 6.1 + 7.2 -> 6.2 ms.
 // Without the folded axes (RegAxis) 20.3 and 8.3 ms.  What bounds it is the scalar
 // phase loads (three pairs at a time instead of two is no faster) and FP64 VALU.
 //
@@ -837,32 +842,45 @@ __global__ __launch_bounds__(64 * kFoldWaves, fold_waves_per_simd<WT>()) void re
 // g as 64-byte pieces; the four qb of a group run on one XCD, next to one another,
 // so that every line of g comes from HBM once.
 constexpr int kRegW = 7;
-constexpr int kRegK = 8;  // k of a wave in a chunk
-constexpr int reg_waves(int W) { return W == 7 ? 8 : (W == 1 ? 4 : W); }
-constexpr int reg_pairs(int W) { return W == 7 ? 16 : 12; }  // pairs of a chunk: its T1 in LDS
-template <int WT, class C>
-constexpr int reg_wps() { return WT == 7 ? 2 : (WT == 5 && sizeof(C) == 16 ? 3 : 4); }
+constexpr int kRegK = 8;  // entries (rows) of a wave in a chunk of the G form
 
-// Values of g that a lane keeps in LDS, not in registers: at WT = 7 in FP64 all 49 (196
-// VGPRs) beside the 28 of T0 or T1 spilled, and a spill's reload waits for every F store.
-template <int WT, class C>
-constexpr int reg_stash() { return WT == 7 && sizeof(C) == 16 ? 4 : 0; }
+// Shape of re_reg_kernel<W, C>: waves of a work-group; pairs of a chunk; states of a chunk of
+// that many pairs; values of g that a lane keeps in LDS, not in registers (at W = 7 in FP64
+// all 49, 196 VGPRs beside the 28 of T0 or T1, spilled, and a spill's reload waits for every F
+// store); waves per SIMD.  Waves beyond W take no part of g and are there for the entries: of
+// 5 waves at W = 5, FP64, a CU holds one work-group (three waves per SIMD), and 12 waves
+// of one are 20 to 50 % faster than those 5 where a k has 16 states (256 k, 125 x 125
+// vectors, 15 modes: 4.7 -> 3.6 ms with 8 -> 12).  G has few entries per pair and gains
+// nothing from more (FP32 W = 5 and W = 3 lose up to a third).
+struct RegShape {
+    int waves, pairs, rows, stash, wps;
+};
+constexpr RegShape reg_shape(int W, bool f32, bool fold) {
+    return W == 7 ? (f32 ? RegShape{8, 12, 32, 6, 4} : RegShape{8, 16, 64, 4, 2})
+         : W == 5 ? (f32 ? (fold ? RegShape{8, 12, 64, 0, 6} : RegShape{5, 12, 60, 0, 4})
+                         : (fold ? RegShape{12, 16, 192, 0, 3} : RegShape{8, 12, 128, 0, 3}))
+         : W == 3 ? RegShape{fold ? 8 : 4, 12, 64, 0, 4}
+                  : RegShape{4, 12, 64, 0, 4};
+}
 // pairs whose phases are in scalar registers at a time (and as many of the next)
-template <int WT, class C>
-constexpr int reg_group() { return sizeof(C) == 16 ? 2 : 1; }
+constexpr int reg_group(bool f32) { return f32 ? 1 : 2; }
 
-void re_reg_limits(int rmax, int* pairs, int* ks) {
-    const int W = 2 * rmax + 1;
-    *pairs = reg_pairs(W);
-    *ks = kRegK * reg_waves(W);
+// LDS of a chunk: T1 of its pairs, a slot of W x 64 values each, as many as whole passes over
+// the pairs write, then with the fold the U_k rows of its states.  A chunk of fewer pairs
+// holds more states, and so fewer chunks form T0 and T1 anew where a k has many (16 bands,
+// every state: 2.7 times as many at W = 7).
+ReRegLimits re_reg_limits(int rmax, bool f32, bool fold) {
+    const int W = 2 * rmax + 1, slot = W * 64 * (int)(f32 ? sizeof(cf) : sizeof(cd));
+    const RegShape r = reg_shape(W, f32, fold);
+    return {r.pairs, 2 * reg_group(f32), slot, fold ? 256 : 0, r.pairs * slot + (fold ? r.rows * 256 : 0),
+            fold ? INT_MAX : kRegK * r.waves};
 }
 
-// U_k of the first state of every entry, in the order re_reg_kernel uses them
-__global__ void re_urows_kernel(const int4* ent, int nent, const int32_t* st_urow, const cd* U, cd* ue) {
+// U_k of the state of every entry, in the order re_reg_kernel uses them
+__global__ void re_urows_kernel(const int2* ent, int nent, const int32_t* st_urow, const cd* U, cd* ue) {
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= nent * 16) return;
-    const int4 e = ent[t >> 4];
-    ue[t] = e.x < e.y ? U[(int64_t)st_urow[e.x] * 16 + (t & 15)] : cd{0.0, 0.0};
+    ue[t] = U[(int64_t)st_urow[ent[t >> 4].x] * 16 + (t & 15)];
 }
 
 // One axis sum sum_R P[n, R] v[R].  FP64 folds the axis: P[n, -r] = conj(P[n, r]) and
@@ -920,21 +938,20 @@ struct RegAxis {
 };
 
 template <int WT, class C, bool FOLD>
-__global__ __launch_bounds__(64 * reg_waves(WT), (reg_wps<WT, C>())) void re_reg_kernel(
+__global__ __launch_bounds__(64 * reg_shape(WT, sizeof(C) == 8, FOLD).waves, reg_shape(WT, sizeof(C) == 8, FOLD).wps) void re_reg_kernel(
     const cd* __restrict__ gmat, int64_t NC, const int32_t* __restrict__ box_re,
     const C* __restrict__ P0, const C* __restrict__ P1, const C* __restrict__ P2,
     const int32_t* __restrict__ pair_k1, const cd* __restrict__ ue, const int32_t* __restrict__ chunks, int nchunk,
-    const int4* __restrict__ ent, int64_t ncb, FoldOut fo, C* __restrict__ G, int64_t ldg) {
+    const int2* __restrict__ ent, int64_t ncb, FoldOut fo, C* __restrict__ G, int64_t ldg) {
     using R = decltype(C::x);
     using X = RegAxis<WT, C>;
     using Row = typename X::Row;
-    constexpr int NWV = reg_waves(WT), PC = reg_pairs(WT), NS = reg_stash<WT, C>();
-    constexpr int GP = reg_group<WT, C>();
-    static_assert(PC % (2 * GP) == 0, "pairs are taken GP at a time, twice a pass");
+    constexpr RegShape RS = reg_shape(WT, sizeof(C) == 8, FOLD);
+    constexpr int NWV = RS.waves, NS = RS.stash, GP = reg_group(sizeof(C) == 8);
+    static_assert(RS.pairs % (2 * GP) == 0, "pairs are taken GP at a time, twice a pass");
     extern __shared__ char smem_raw[];
-    C* sT = reinterpret_cast<C*>(smem_raw);             // [PC][WT][64]
-    C* sG = sT + PC * WT * 64;                          // [WT][NS][64]
-    cd* sU = reinterpret_cast<cd*>(sG + WT * NS * 64);  // FOLD: [NWV][kRegK][16]
+    C* sG = reinterpret_cast<C*>(smem_raw);  // [WT][NS][64]
+    C* sT = sG + WT * NS * 64;               // [pairs of the chunk, whole groups][WT][64]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15, lg = lane >> 4;
     int64_t cb;
@@ -950,7 +967,7 @@ __global__ __launch_bounds__(64 * reg_waves(WT), (reg_wps<WT, C>())) void re_reg
     const int64_t cg = FOLD ? (cb >> 2) * 256 + li * 16 + 4 * (int)(cb & 3) + lg : (c < NC ? c : NC - 1);
     const uint32_t cgb = (uint32_t)cg * 16u;  // (a row of g is below 4 GB, checked at launch)
     C g[WT][WT];
-    C* const gs = sG + wave * NS * 64 + lane;  // the last NS values (see reg_stash)
+    C* const gs = sG + wave * NS * 64 + lane;  // the last NS values (see RegShape)
     if (wave < WT) {
         auto value = [&](int r0, int r1) {
             const int row = box_re[(r0 * WT + r1) * WT + wave];
@@ -1002,12 +1019,15 @@ __global__ __launch_bounds__(64 * reg_waves(WT), (reg_wps<WT, C>())) void re_reg
         for (int j = 0; j < GP; ++j) X::load(pha[j], P1, pair_k1[p0 + j]);
 #pragma unroll
         for (int j = 0; j < GP; ++j) k1n[j] = pair_k1[p0 + GP + j];
-        if constexpr (FOLD) {  // this wave's eigenvector rows, four per load, straight to LDS
-            cd* dst = sU + wave * kRegK * 16;
+        // FOLD: [entries][16], after the chunk's pairs
+        const cd* sU = reinterpret_cast<const cd*>(sT + (np + 2 * GP - 1) / (2 * GP) * (2 * GP) * WT * 64);
+        if constexpr (FOLD) {
+            // this wave's eigenvector rows, four per load, straight to LDS (the last load may
+            // bring rows of the next wave as well: the same values)
             for (int i = ibeg; i < iend; i += 4)
                 __builtin_amdgcn_global_load_lds(
                     (const __attribute__((address_space(1))) void*)(ue + (int64_t)i * 16 + lane),
-                    (__attribute__((address_space(3))) void*)(dst + (i - ibeg) * 16), 16, 0, 0);
+                    (__attribute__((address_space(3))) void*)(sU + (i - e0) * 16), 16, 0, 0);
         }
         if (wave < WT) {
             C t0[WT];
@@ -1053,46 +1073,43 @@ __global__ __launch_bounds__(64 * reg_waves(WT), (reg_wps<WT, C>())) void re_reg
                 group(p + GP, phb, pha);
             }
         }
-        // the first k's phases and record, ahead of the barrier
-        // (entry: first state, end of its states, pair of the chunk + 256 k2, batch row)
-        int4 en = ent[ibeg], en1 = ent[ibeg + 1];
-        X::load(pha[0], P2, en.z >> 8);
+        // the first entry's phases and record, ahead of the barrier
+        // (entry: row or state, pair of the chunk + 256 k2)
+        int2 en = ent[ibeg], en1 = ent[ibeg + 1];
+        X::load(pha[0], P2, en.y >> 8);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (FOLD) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): sU
         __syncthreads();
         if (ibeg < iend) {  // (wave-uniform)
-            int cur = -1;
-            C t1[WT];
+            int cur = -1, key = -1;
+            C t1[WT], acc = {0, 0};
             auto one = [&](int i, const Row& ph, Row& nx) {
-                if ((en.z & 255) != cur) {
-                    cur = en.z & 255;
+                if ((en.y & 255) != cur) {
+                    cur = en.y & 255;
 #pragma unroll
                     for (int r2 = 0; r2 < WT; ++r2) t1[r2] = ld_vec(sT + (cur * WT + r2) * 64 + lane);
                     X::prepare(t1);
                 }
                 C u = {0, 0};
-                if constexpr (FOLD) u = to_c<C>(ld_vec(sU + (wave * kRegK + i - ibeg) * 16 + li));
+                if constexpr (FOLD) u = to_c<C>(ld_vec(sU + (i - e0) * 16 + li));
                 __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): nothing but the prefetch below
                 __builtin_amdgcn_sched_barrier(0);
-                const int4 ec = en;
+                const int2 ec = en;
                 en = en1;
-                X::load(nx, P2, en.z >> 8);
+                X::load(nx, P2, en.y >> 8);
                 en1 = ent[i + 2];
                 __builtin_amdgcn_sched_barrier(0);
-                C acc = X::first(ph, t1);
-                X::rest(acc, ph, t1);
+                if (!FOLD || ec.y != key) {  // (the states of one k share its G)
+                    key = ec.y;
+                    acc = X::first(ph, t1);
+                    X::rest(acc, ph, t1);
+                }
                 if constexpr (FOLD) {
                     // sum over the 16 lanes of a row: conj(U_k[a, n]) G
-                    auto fold = [&](const C& v, int st) {
-                        const R f = row16_sum2(v.x * acc.x + v.y * acc.y, v.x * acc.y - v.y * acc.x,
-                                               li & 1);
-                        if (li < 2) reinterpret_cast<R*>(Fo + st * fst)[li] = f;
-                    };
-                    if (ec.x < ec.y) fold(u, ec.x);
-                    for (int st = ec.x + 1; st < ec.y; ++st)
-                        fold(to_c<C>(fo.U[(int64_t)fo.st_urow[st] * 16 + li]), st);
+                    const R f = row16_sum2(u.x * acc.x + u.y * acc.y, u.x * acc.y - u.y * acc.x, li & 1);
+                    if (li < 2) reinterpret_cast<R*>(Fo + ec.x * fst)[li] = f;
                 } else if (c < NC) {
-                    G[(int64_t)ec.w * ldg + c] = acc;
+                    G[(int64_t)ec.x * ldg + c] = acc;
                 }
             };
             for (int i = ibeg; i < iend; i += 2) {
@@ -1114,12 +1131,13 @@ static hipError_t go_re_reg(const cd* g, int64_t NC, const int32_t* box_re, Mesh
                             const ReRegBatch& b, const FoldOut& fo, C* G, int64_t ldg, hipStream_t s) {
     const C* P1 = P + (int64_t)m.n0 * WT;
     const C* P2 = P1 + (int64_t)m.n1 * WT;
-    const int4* ent = reinterpret_cast<const int4*>(b.ent);
+    const int2* ent = reinterpret_cast<const int2*>(b.ent);
     if (FOLD)
         hipLaunchKernelGGL(re_urows_kernel, dim3((unsigned)((b.nent + 15) / 16)), dim3(256), 0, s, ent,
                            b.nent, fo.st_urow, fo.U, b.ue);
-    const size_t shm = (size_t)(reg_pairs(WT) + reg_stash<WT, C>()) * WT * 64 * sizeof(C) +
-                       (FOLD ? (size_t)reg_waves(WT) * kRegK * 16 * sizeof(cd) : 0);
+    constexpr RegShape RS = reg_shape(WT, sizeof(C) == 8, FOLD);
+    const ReRegLimits lim = re_reg_limits(WT / 2, sizeof(C) == 8, FOLD);
+    const size_t shm = (size_t)RS.stash * lim.slot + lim.pool;
     hipError_t e = hipFuncSetAttribute((const void*)re_reg_kernel<WT, C, FOLD>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
@@ -1130,7 +1148,7 @@ static hipError_t go_re_reg(const cd* g, int64_t NC, const int32_t* box_re, Mesh
     // (they read the block of g again, from L2)
     const int split = (int)std::min<int64_t>(b.nchunk, std::max<int64_t>(1, 1024 / groups));
     hipLaunchKernelGGL((re_reg_kernel<WT, C, FOLD>), dim3((unsigned)groups, split),
-                       dim3(64 * reg_waves(WT)), shm, s, g, NC, box_re, P, P1, P2, b.pair_k1, b.ue,
+                       dim3(64 * RS.waves), shm, s, g, NC, box_re, P, P1, P2, b.pair_k1, b.ue,
                        b.chunks, b.nchunk, ent, ncb, fo, G, ldg);
     return hipGetLastError();
 }
@@ -1247,7 +1265,8 @@ static hipError_t re_reg(const cd* g, int64_t NC, const int32_t* box_re, int rma
                          const C* P, const ReRegBatch& b, const FoldOut* fo, C* G, int64_t ldg,
                          hipStream_t s) {
     if (!re_reg_supported(rmax, NC, sizeof(C) == sizeof(cf), fo != nullptr) || b.nchunk <= 0 || b.nent <= 0 || m.n2 >= (1 << 23) ||
-        !fold_ok(fo, NC) || ((reinterpret_cast<uintptr_t>(b.ent) | reinterpret_cast<uintptr_t>(b.ue)) & 15))
+        !fold_ok(fo, NC) || (reinterpret_cast<uintptr_t>(b.ent) & 7) ||
+        ((reinterpret_cast<uintptr_t>(b.chunks) | reinterpret_cast<uintptr_t>(b.ue)) & 15))
         return hipErrorInvalidValue;
     auto go = [&](auto wt) {
         constexpr int WT = decltype(wt)::value;

@@ -443,6 +443,56 @@ def test_one_pass_stage1(lib, r_e, nW, mesh, order):
     assert rel_err(g32.cpu().numpy(), ref)[0] < 1e-5
 
 
+@pytest.mark.parametrize("r_e,nW,mesh,window", [
+    (0, 16, (2, 3, 11), 1e30),    # one vector
+    (1, 16, (1, 2, 40), 1e30),    # 640 states a pair: a k's states on both sides of a chunk's end
+    (2, 16, (2, 1, 45), 1e30),
+    (2, 16, (1, 40, 2), 0.3),     # many pairs of few states
+    (3, 16, (1, 2, 33), 1e30),
+    (3, 16, (2, 7, 9), 0.3),
+    (1, 5, (1, 2, 90), 1e30),     # G written: a pair of more k than a chunk's
+])
+def test_one_pass_stage1_states(lib, r_e, nW, mesh, window):
+    """The one-pass Re sum where its chunks fill with a k's states (or a pair's k) before
+    they fill with pairs, and the other way round: against the direct contraction, FP64 and
+    FP32, with k's repeated; and the same bits under a budget that splits the batches."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem, Library
+    rng = np.random.default_rng(300 + 10 * r_e + nW)
+    s = synth.small_system(60 + r_e, n_wannier=nW, n_atoms=1, r=1)
+    box = synth.box_vectors(r_e)
+    inner = box[rng.choice(len(box), size=min(len(box), 30), replace=False)]
+    s.re = np.ascontiguousarray(np.unique(np.concatenate([inner, [[-r_e, 0, r_e]]]), axis=0),
+                                dtype=np.int32)
+    shape = (len(s.re), 27, 3, nW, nW)
+    s.g_rr = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    N = int(np.prod(mesh))
+    mu = float(np.median(rates.mesh_tables(s, mesh)["eps"]))
+    par = dict(mu=mu, kT=constants.kT_of(300.0), sigma=0.1, win_lo=mu - window, win_hi=mu + window,
+               omega_min=1e-4)
+    k_idx = np.concatenate([rng.permutation(N), rng.integers(0, N, size=9)])
+    ds = DeviceSystem.from_host(s)
+    small = Library(0, workspace_budget=60 * 10**6)
+    try:
+        lib.set_mesh_sum("direct")
+        n, ref, _, _ = _gpu_rates(lib, s, mesh, par, k_idx=k_idx, ds=ds)
+        lib.set_mesh_sum("factored")
+        small.set_mesh_sum("factored")
+        _, got, _, _ = _gpu_rates(lib, s, mesh, par, k_idx=k_idx, ds=ds)
+        _, split, _, _ = _gpu_rates(small, s, mesh, par, k_idx=k_idx, ds=ds)
+        g32 = torch.zeros((len(k_idx), nW), dtype=torch.float64, device="cuda")
+        kd = torch.from_numpy(k_idx.astype(np.int32)).cuda()
+        lib.scatter_rates(ds, mesh, par, g32, k_idx=kd, precision="fp32")
+        torch.cuda.synchronize()
+    finally:
+        lib.set_mesh_sum("auto")
+        small.close()
+    assert n > 1 and np.max(ref) > 0
+    assert rel_err(got, ref)[0] < 1e-11
+    assert np.array_equal(got, split)
+    assert rel_err(g32.cpu().numpy()[:n], ref)[0] < 1e-5
+
+
 @pytest.mark.parametrize("nW,r,mesh", [
     (3, 2, (24, 24, 24)),    # box 5 wide
     (5, 3, (16, 17, 15)),    # box 7 wide, odd axes
