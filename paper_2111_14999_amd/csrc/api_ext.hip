@@ -45,10 +45,10 @@ phoebe_status phoebe_gpu_interp_v3(void* handle, const phoebe_system3* sys, cons
         for (int i = 0; i < 3 * n1; ++i) nr1[i] = -sys->r1[i];
         for (int i = 0; i < 3 * n2; ++i) nr2[i] = -sys->r2[i];
         const int64_t qb = std::min<int64_t>(nq, 16);  // q of one stage-1 batch
-        // q whose X is formed and rotated at once, up to 1 GB of it: 1,024 q' make 848
-        // work-groups of the product and 1,024 of the rotations, a few rounds of the chip (4 q,
-        // 15 modes: 350 + 200 us one by one, 284 + 190 together); one where the budget has no
-        // room for more
+        // q whose X is formed and rotated at once, up to 1 GB of it: a q's 1,024 q' are 864
+        // work-groups of the product (two by two tiles, three a CU at once: the second
+        // round is nearly empty) and 1,024 of the rotations (4 q, 15 modes, 125 R': products
+        // 289 us one by one, 238 together); one where the budget has no room for more
         int64_t xb = std::max<int64_t>(1, std::min<int64_t>(qb, ((int64_t)1 << 30) / (16 * nqp * m3)));
         auto plan = [&](Arena& ar) {
             int32_t* rd = upload_r(h, ar, sys->rd, sys->n_rd, s);

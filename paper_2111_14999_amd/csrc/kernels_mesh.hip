@@ -701,17 +701,12 @@ __device__ inline R row16_sum2(R a, R b, bool odd) {
 //   F[st, Rp, sa*16 + b] = sum_a conj(U_k[a, n_st]) G[k, Rp, sa, a, b]
 // is a sum over the 16 lanes of a row.  G never leaves the registers; F is
 // written once per state.
-constexpr int kFoldWaves = 8;  // waves of the folded pair kernel sharing one T0 slab
-// Waves per SIMD the folded pair kernel is compiled for: with a box of at most 7
-// its FP64 slab (49 x 64 x 16 B) lets three work-groups share a CU, which needs
-// six waves per SIMD (80 VGPRs); wider boxes fit one work-group per CU anyway.
-template <int WT>
-constexpr int fold_waves_per_simd() {
-    return WT > 0 && WT <= 7 ? 6 : 2;
-}
+// Boxes above 7 wide come here (narrower ones: re_reg_kernel), whose FP64 slab
+// (81 x 64 x 16 B and more) leaves a CU one work-group, two waves per SIMD.
+constexpr int kFoldWaves = 8;  // waves sharing one T0 slab
 
 template <int WT, class C>
-__global__ __launch_bounds__(64 * kFoldWaves, fold_waves_per_simd<WT>()) void re_axis12_fold_kernel(
+__global__ __launch_bounds__(64 * kFoldWaves, 2) void re_axis12_fold_kernel(
     const C* __restrict__ T0, int64_t NC, int Wr, const cd* __restrict__ P1,
     const cd* __restrict__ P2, const int32_t* __restrict__ pair_k1,
     const int32_t* __restrict__ pair_off, const int32_t* __restrict__ kp_off,
@@ -1168,7 +1163,8 @@ static hipError_t go_re_axis12(const C* T0, int64_t NC, int W, Mesh m, const cd*
     const cd* P1 = P + (int64_t)m.n0 * W;
     const cd* P2 = P1 + (int64_t)m.n1 * W;
     const size_t shm = (size_t)W * W * 64 * sizeof(C);
-    const void* kern = fo ? (const void*)re_axis12_fold_kernel<WT, C>
+    constexpr int WF = WT == 7 ? 0 : WT;  // (the fold comes here above 7, or with rows of 4 GB)
+    const void* kern = fo ? (const void*)re_axis12_fold_kernel<WF, C>
                           : (const void*)re_axis12_kernel<WT, C>;
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
@@ -1176,7 +1172,7 @@ static hipError_t go_re_axis12(const C* T0, int64_t NC, int W, Mesh m, const cd*
     if ((int64_t)b.d0 * ncb > 2147483647LL) return hipErrorInvalidValue;
     if (fo && (!b.k_ent || (reinterpret_cast<uintptr_t>(b.k_ent) & 15))) return hipErrorInvalidValue;
     if (fo)
-        hipLaunchKernelGGL((re_axis12_fold_kernel<WT, C>), dim3((unsigned)(b.d0 * ncb)),
+        hipLaunchKernelGGL((re_axis12_fold_kernel<WF, C>), dim3((unsigned)(b.d0 * ncb)),
                            dim3(64 * kFoldWaves),
                            shm, s, T0, NC, W, P1, P2, b.pair_k1, b.pair_off, b.kp_off, b.k_row,
                            b.k_k2, b.d_plane, reinterpret_cast<const int4*>(b.k_ent), ncb, *fo);
