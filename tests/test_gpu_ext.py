@@ -485,6 +485,28 @@ def test_v3_q_batches(lib):
     assert float((V - one).abs().max()) < 1e-13 * float(V.abs().max())
 
 
+def test_v3_q_groups(lib):
+    """Two batches of q and a last group of q smaller than the others (17 q: groups of 5, 5, 5
+    and 1, then 1) against calls of one q."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem3
+    nat, nq, nqp = 5, 17, 3900
+    nm = 3 * nat
+    assert (1 << 30) // (16 * nqp * nm**3) == 5
+    s = synth.small_system(4, n_wannier=1, n_atoms=nat, r=1)
+    r, phi3 = synth.third_order_constants(4, nat)
+    g = np.random.default_rng(4)
+    q = torch.from_numpy(g.uniform(-1, 1, size=(nq, 3))).cuda()
+    qp = torch.from_numpy(g.uniform(-1, 1, size=(nqp, 3))).cuda()
+    d3 = DeviceSystem3.from_host(s, r, phi3)
+    V = torch.zeros((nq, nqp, nm, nm, nm), dtype=torch.complex128, device="cuda")
+    one = torch.zeros((1, nqp, nm, nm, nm), dtype=torch.complex128, device="cuda")
+    lib.interp_v3(d3, q, qp, V)
+    for i in range(nq):
+        lib.interp_v3(d3, q[i:i + 1].contiguous(), qp, one)
+        assert float((V[i] - one[0]).abs().max()) < 1e-13 * float(one.abs().max()), i
+
+
 # ---------------------------------------------------------------------------
 # Philox streams, initialisation, training set, gather
 # ---------------------------------------------------------------------------

@@ -493,6 +493,58 @@ def test_one_pass_stage1_states(lib, r_e, nW, mesh, window):
     assert rel_err(g32.cpu().numpy()[:n], ref)[0] < 1e-5
 
 
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-11), ("fp32", 1e-5)])
+@pytest.mark.parametrize("r_e,nW,mb", [
+    (4, 16, 600), (5, 16, 800),  # fold in the pair step; box 9 wide, and a run-time width
+    (4, 5, 110), (5, 5, 130),    # G written
+])
+def test_planes_stage1(lib, r_e, nW, mb, precision, tol):
+    """Stage 1 with planes in memory (boxes above 7 wide), k's out of order and repeated, in
+    more planes than a batch holds by itself: against the direct contraction, and the planes
+    of the call against those of a batch, the same bits."""
+    torch = torch_cuda()
+    from paper_2111_14999_amd import DeviceSystem, Library
+    rng = np.random.default_rng(500 + 10 * r_e + nW)
+    s = synth.small_system(70 + r_e, n_wannier=nW, n_atoms=1, r=1)
+    box = synth.box_vectors(r_e)
+    inner = box[rng.choice(len(box), size=30, replace=False)]
+    s.re = np.ascontiguousarray(np.unique(np.concatenate([inner, [[-r_e, 0, r_e]]]), axis=0),
+                                dtype=np.int32)
+    shape = (len(s.re), 27, 3, nW, nW)
+    s.g_rr = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    mesh, N = (20, 3, 4), 240
+    par = dict(mu=float(np.median(rates.mesh_tables(s, mesh)["eps"])), kT=constants.kT_of(300.0),
+               sigma=0.1, win_lo=-1e30, win_hi=1e30, omega_min=1e-4)
+    k_idx = np.concatenate([rng.permutation(N), rng.integers(0, N, size=30)]).astype(np.int32)
+    kd = torch.from_numpy(k_idx).cuda()
+    ds = DeviceSystem.from_host(s)
+
+    def run(L, mode, precision=precision):
+        gamma = torch.zeros((len(k_idx), nW), dtype=torch.float64, device="cuda")
+        L.set_mesh_sum(mode)
+        L.set_timing(True)
+        L.reset_timing()
+        try:
+            assert L.scatter_rates(ds, mesh, par, gamma, k_idx=kd, precision=precision) == len(k_idx)
+            torch.cuda.synchronize()
+            return gamma.cpu().numpy(), L.kernel_time("stage1_planes")[0]
+        finally:
+            L.set_timing(False)
+            L.set_mesh_sum("auto")
+
+    ref, _ = run(lib, "direct", "fp64")
+    got, planes = run(lib, "factored")
+    small = Library(0, workspace_budget=mb * 10**6 // (2 if precision == "fp32" else 1))
+    try:
+        split, split_planes = run(small, "factored")
+    finally:
+        small.close()
+    assert planes == 1 and split_planes == 0
+    assert np.max(ref) > 0
+    assert rel_err(got, ref)[0] < tol
+    assert np.array_equal(got, split)
+
+
 @pytest.mark.parametrize("nW,r,mesh", [
     (3, 2, (24, 24, 24)),    # box 5 wide
     (5, 3, (16, 17, 15)),    # box 7 wide, odd axes
@@ -512,6 +564,31 @@ def test_mesh_bands_by_axes(lib, nW, r, mesh):
                                 h_r=np.ascontiguousarray(h2))
     assert len(s.rh) * int(np.prod(mesh)) >= 1 << 20 and 2 * (2 * r + 1) <= len(s.rh)
     k_idx = np.arange(0, int(np.prod(mesh)), max(1, int(np.prod(mesh)) // 7))[:7]
+    par = dict(mu=0.0, kT=constants.kT_of(300.0), sigma=0.1, win_lo=-1e30, win_hi=1e30,
+               omega_min=1e-4)
+    _, got, _, _ = _gpu_rates(lib, s, mesh, par, k_idx=k_idx, ds=DeviceSystem.from_host(s))
+    _, ref, _, _ = _gpu_rates(lib, twice, mesh, par, k_idx=k_idx, ds=DeviceSystem.from_host(twice))
+    assert np.max(np.abs(ref)) > 0
+    assert rel_err(got, ref)[0] < 1e-10
+
+
+@pytest.mark.parametrize("r,mesh", [
+    (5, (7, 11, 13)),   # box 11 wide, the last axis wider than the box and the first narrower
+    (10, (6, 5, 7)),
+    (15, (4, 3, 5)),    # box 31 wide, the widest that goes axis by axis
+])
+def test_mesh_bands_by_axes_wide(lib, r, mesh):
+    """The same for boxes wider than 9."""
+    torch_cuda()
+    import dataclasses
+    from paper_2111_14999_amd import DeviceSystem
+    s = synth.make_system(150 + r, 3, np.zeros((1, 3)), [1.0], r_h=r, r_e=1, r_p=1)
+    h2 = np.concatenate([s.h_r, 0.5 * s.h_r[-1:]])
+    h2[len(s.rh) - 1] *= 0.5
+    twice = dataclasses.replace(s, rh=np.ascontiguousarray(np.concatenate([s.rh, s.rh[-1:]])),
+                                h_r=np.ascontiguousarray(h2))
+    assert len(s.rh) * int(np.prod(mesh)) >= 1 << 20 and 2 * (2 * r + 1) <= len(s.rh)
+    k_idx = np.arange(0, int(np.prod(mesh)), int(np.prod(mesh)) // 7)[:7]
     par = dict(mu=0.0, kT=constants.kT_of(300.0), sigma=0.1, win_lo=-1e30, win_hi=1e30,
                omega_min=1e-4)
     _, got, _, _ = _gpu_rates(lib, s, mesh, par, k_idx=k_idx, ds=DeviceSystem.from_host(s))
