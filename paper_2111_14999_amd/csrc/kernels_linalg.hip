@@ -595,51 +595,51 @@ __global__ __launch_bounds__(64 * EigShape<N>::NW) void eig_herm_kernel(const cd
                 swap_if(swj, z00, z01);
                 swap_if(swj, z10, z11);
             } else {
-            // in lane (I, I) the block is the pair's own
-            const JacobiRot rd = jacobi_rot(x00.x, x11.x, x01, fi > gi, eps2, skip);
-            JacobiRot ri, rj;
-            if constexpr (NW == 1) {
-                const int si = base + I * (H + 1), sj = base + J * (H + 1);
-                ri = JacobiRot{__shfl(rd.c, si, 64), __shfl(rd.sx, si, 64), __shfl(rd.sy, si, 64), 0.0};
-                rj = JacobiRot{__shfl(rd.c, sj, 64), __shfl(rd.sx, sj, 64), __shfl(rd.sy, sj, 64), 0.0};
-            } else {
-                if (act && I == J) {
-                    sprm[I][0] = rd.c;
-                    sprm[I][1] = rd.sx;
-                    sprm[I][2] = rd.sy;
+                // in lane (I, I) the block is the pair's own
+                const JacobiRot rd = jacobi_rot(x00.x, x11.x, x01, fi > gi, eps2, skip);
+                JacobiRot ri, rj;
+                if constexpr (NW == 1) {
+                    const int si = base + I * (H + 1), sj = base + J * (H + 1);
+                    ri = JacobiRot{__shfl(rd.c, si, 64), __shfl(rd.sx, si, 64), __shfl(rd.sy, si, 64), 0.0};
+                    rj = JacobiRot{__shfl(rd.c, sj, 64), __shfl(rd.sx, sj, 64), __shfl(rd.sy, sj, 64), 0.0};
+                } else {
+                    if (act && I == J) {
+                        sprm[I][0] = rd.c;
+                        sprm[I][1] = rd.sx;
+                        sprm[I][2] = rd.sy;
+                    }
+                    __syncthreads();  // (and every block has been read)
+                    ri = JacobiRot{sprm[I][0], sprm[I][1], sprm[I][2], 0.0};
+                    rj = JacobiRot{sprm[J][0], sprm[J][1], sprm[J][2], 0.0};
                 }
-                __syncthreads();  // (and every block has been read)
-                ri = JacobiRot{sprm[I][0], sprm[I][1], sprm[I][2], 0.0};
-                rj = JacobiRot{sprm[J][0], sprm[J][1], sprm[J][2], 0.0};
-            }
-            const bool any = ri.sx != 0.0 || ri.sy != 0.0;
-            rotated = rotated || any;
-            // rows: A'_f = c A_f - s e A_g ; A'_g = s conj(e) A_f + c A_g
-            auto rot_f = [](double c, double sx, double sy, cd u, cd w) {  // c u - s w
-                return cd{fma(c, u.x, fma(sy, w.y, -sx * w.x)), fma(c, u.y, -fma(sx, w.y, sy * w.x))};
-            };
-            auto rot_g = [](double c, double sx, double sy, cd u, cd w) {  // conj(s) u + c w
-                return cd{fma(c, w.x, fma(sy, u.y, sx * u.x)), fma(c, w.y, fma(sx, u.y, -sy * u.x))};
-            };
-            const double af = x00.x - rd.dlt, ag = x11.x + rd.dlt;
-            const cd y00 = rot_f(ri.c, ri.sx, ri.sy, x00, x10), y01 = rot_f(ri.c, ri.sx, ri.sy, x01, x11);
-            const cd y10 = rot_g(ri.c, ri.sx, ri.sy, x00, x10), y11 = rot_g(ri.c, ri.sx, ri.sy, x01, x11);
-            // columns: A'_f = c A_f - s conj(e) A_g ; A'_g = s e A_f + c A_g ; V the same
-            x00 = rot_f(rj.c, rj.sx, -rj.sy, y00, y01);
-            x01 = rot_g(rj.c, rj.sx, -rj.sy, y00, y01);
-            x10 = rot_f(rj.c, rj.sx, -rj.sy, y10, y11);
-            x11 = rot_g(rj.c, rj.sx, -rj.sy, y10, y11);
-            // the rotated pair: exact zero off the diagonal, and a diagonal changed by t |A_fg|
-            // only: multiplied by c^2 and s^2 it would gather their rounding at every rotation
-            if (I == J && any) {
-                x01 = x10 = cd{0.0, 0.0};
-                x00 = cd{af, 0.0};
-                x11 = cd{ag, 0.0};
-            }
-            z00 = rot_f(rj.c, rj.sx, -rj.sy, vf0, vg0);
-            z01 = rot_g(rj.c, rj.sx, -rj.sy, vf0, vg0);
-            z10 = rot_f(rj.c, rj.sx, -rj.sy, vf1, vg1);
-            z11 = rot_g(rj.c, rj.sx, -rj.sy, vf1, vg1);
+                const bool any = ri.sx != 0.0 || ri.sy != 0.0;
+                rotated = rotated || any;
+                // rows: A'_f = c A_f - s e A_g ; A'_g = s conj(e) A_f + c A_g
+                auto rot_f = [](double c, double sx, double sy, cd u, cd w) {  // c u - s w
+                    return cd{fma(c, u.x, fma(sy, w.y, -sx * w.x)), fma(c, u.y, -fma(sx, w.y, sy * w.x))};
+                };
+                auto rot_g = [](double c, double sx, double sy, cd u, cd w) {  // conj(s) u + c w
+                    return cd{fma(c, w.x, fma(sy, u.y, sx * u.x)), fma(c, w.y, fma(sx, u.y, -sy * u.x))};
+                };
+                const double af = x00.x - rd.dlt, ag = x11.x + rd.dlt;
+                const cd y00 = rot_f(ri.c, ri.sx, ri.sy, x00, x10), y01 = rot_f(ri.c, ri.sx, ri.sy, x01, x11);
+                const cd y10 = rot_g(ri.c, ri.sx, ri.sy, x00, x10), y11 = rot_g(ri.c, ri.sx, ri.sy, x01, x11);
+                // columns: A'_f = c A_f - s conj(e) A_g ; A'_g = s e A_f + c A_g ; V the same
+                x00 = rot_f(rj.c, rj.sx, -rj.sy, y00, y01);
+                x01 = rot_g(rj.c, rj.sx, -rj.sy, y00, y01);
+                x10 = rot_f(rj.c, rj.sx, -rj.sy, y10, y11);
+                x11 = rot_g(rj.c, rj.sx, -rj.sy, y10, y11);
+                // the rotated pair: exact zero off the diagonal, and a diagonal changed by t |A_fg|
+                // only: multiplied by c^2 and s^2 it would gather their rounding at every rotation
+                if (I == J && any) {
+                    x01 = x10 = cd{0.0, 0.0};
+                    x00 = cd{af, 0.0};
+                    x11 = cd{ag, 0.0};
+                }
+                z00 = rot_f(rj.c, rj.sx, -rj.sy, vf0, vg0);
+                z01 = rot_g(rj.c, rj.sx, -rj.sy, vf0, vg0);
+                z10 = rot_f(rj.c, rj.sx, -rj.sy, vf1, vg1);
+                z11 = rot_g(rj.c, rj.sx, -rj.sy, vf1, vg1);
             }
             if constexpr (NW == 1) eig_sync<1>();  // (reads before writes)
             if (act) {
