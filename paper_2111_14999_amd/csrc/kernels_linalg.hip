@@ -347,13 +347,13 @@ __device__ inline double wave_sum(double v) {
 // the indices move round the slots as on a conveyor (f_J -> f_{J-1}, f_1 -> g_0, g_J ->
 // g_{J+1}, g_{H-1} -> f_{H-1}, f_0 stays), so a lane always reads the same addresses and
 // writes its results where the next round expects them.  With this offset of the g slots
-// and a row stride of H modulo 8 (in 16-byte units), the eight lanes served in one LDS
-// cycle fall on distinct banks in reads and writes; stored by index they met 45 % of
-// extra cycles.  After a sweep every index is back at its first position.
+// and a row stride of H modulo 8 (in 16-byte units), bank conflicts add 22 % to the
+// accesses' cycles (order 16, by counter); stored by index they added 76 %.  After a
+// sweep every index is back at its first position.
 //
 // 64,000 matrices of order 16: 3.06 ms (parameters through LDS between two barriers,
 // sorted pairs stored by index) -> 2.89 ms (pairs per lane, no barriers) -> 2.72 ms (by
-// slot; LDS busy 0.8 of the time); 29,791 of order 20: 7.49 ms (row and column passes by
+// slot; LDS busy 0.76 of the time); 29,791 of order 20: 7.49 ms (row and column passes by
 // one wave) -> 3.25 ms; 9,384 of order 9: 325 -> 178 us; 301 of order 16: 108 -> 75 us.
 // ---------------------------------------------------------------------------
 // orders whose lanes fit a wave: no barrier, but the accesses keep their order

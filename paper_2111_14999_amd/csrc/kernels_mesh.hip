@@ -830,8 +830,10 @@ __global__ __launch_bounds__(64 * kFoldWaves, 2) void re_axis12_fold_kernel(
 // this takes out its write and its read, and the pair sums read no LDS.  nW = 16, 15
 // modes, 343 x 343 vectors, 1,964 k of a 40^3 mesh: 9.8 + 17.4 ms (planes, then pairs and
 // k) -> 15.4 ms, of which the k and fold 6.3; 454 k of a 24^3 mesh: 6.1 + 7.2 -> 6.2 ms.
-// Without the folded axes (RegAxis) 20.3 and 8.3 ms.  What bounds it is the scalar
-// phase loads (three pairs at a time instead of two is no faster) and FP64 VALU.
+// Without the folded axes (RegAxis) 20.3 and 8.3 ms.  What bounds it is latency at two
+// waves per SIMD: by counter (2,985 k of a 40^3 mesh) the waves wait 0.44 of their cycles,
+// for the scalar phase loads above all (three pairs at a time instead of two is no
+// faster), VALU issues 0.38 of the SIMDs' cycles, LDS is busy 0.15.
 //
 // FOLD: the 64 columns are b = 4 qb + g, a = i of one (Rp, mode) for lane (g, i), read from
 // g as 64-byte pieces; the four qb of a group run on one XCD, next to one another,
@@ -1528,9 +1530,9 @@ constexpr int kLineLW = 1, kLinePol = 2, kLineVel = 4;
 // adaptive widths leave about four live bands at a point (24^3 mesh, 16 bands: 52,900 live
 // (q, band) against 13,800 live q a state), where one list per band computes X four times.
 // Adaptive rates of that mesh, 543 states, ms in this kernel: MB 1 25.1; MB 2, 3, 4, 6 16.9,
-// 16.5, 18.0, 18.1 (three waves per SIMD up to MB 3, two above); four waves of MB 4 18.5.  What
-// is left is the terms' FP64 arithmetic (the two exponentials; 5 ms), the MFMA part (4 ms),
-// Y (2 ms) and the waits between them.  The plain Gaussian takes one band a list, whatever
+// 16.5, 18.0, 18.1 (three waves per SIMD up to MB 3, two above); four waves of MB 4 18.5; MB 3
+// with E of the next atom loaded ahead 15.2.  What is left is the terms' FP64 arithmetic
+// (the two exponentials; 5 ms), the MFMA part (4 ms), Y (2 ms) and the waits between them.  The plain Gaussian takes one band a list, whatever
 // its width against the bands: at a band edge it leaves one live band at a point, and the
 // registers of the further ones only cost occupancy (linewidths of a polar crystal, 9 bands,
 // 9 modes, 20^3: 470 us with one, 685 with up to three); where every band is live, as in a
