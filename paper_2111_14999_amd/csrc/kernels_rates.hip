@@ -311,7 +311,21 @@ __global__ __launch_bounds__(256, (TN >= 12 ? 1 : 2)) void stage2_rates_kernel(R
                 const cd* Yr = sY + (c * kMB + mb) * nm;
                 const cd* Eq = a.E + (q * nm + nu) * nm;
                 cd z = {0.0, 0.0};
-                for (int sa = 0; sa < nm; ++sa) z = cfma(Eq[sa], Yr[sa], z);
+                // an atom's three axes at a time, the next three on their way: the lanes' rows are
+                // nm values apart, and a load waited for at once costs more than with the modes
+                // side by side (64 states x 5,832 q, 1 band, 15 modes, us: 351 without, 249 by
+                // side, now 214; 16 bands, 125 Rp, 64 k of a 12^3 mesh: 510, 543, 465)
+                cd e0 = Eq[0], e1 = Eq[1], e2 = Eq[2];
+                for (int sa = 0; sa < nm; sa += 3) {
+                    const cd v0 = e0, v1 = e1, v2 = e2;
+                    const cd* En = Eq + (sa + 3 < nm ? sa + 3 : 0);
+                    e0 = En[0];
+                    e1 = En[1];
+                    e2 = En[2];
+                    z = cfma(v0, Yr[sa], z);
+                    z = cfma(v1, Yr[sa + 1], z);
+                    z = cfma(v2, Yr[sa + 2], z);
+                }
                 const int m = m0 + mb;
                 if (a.Lpol) {  // + i L(q, nu) [U_k^dagger U_{k+q}]_{n m}
                     const cd* Ukq = a.U + ((int64_t)kq * nW + m) * nW;
